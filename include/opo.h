@@ -145,10 +145,14 @@ typedef struct {
                                handle's fields fill the chip (at least 2^20
                                complex samples in all: batch entries) or not
                                (one instance or a few), chosen by timing the
-                               candidates on MI355X (one shape in one kind of
-                               handle always gets the same schedule; an instance
-                               alone and the same instance in a full batch may
-                               differ in rounding);
+                               candidates on MI355X. A handle that does not fill
+                               the chip and has few instances (up to 14 in FP32, 8
+                               in FP64, of 2^10 points or more and one field count)
+                               runs two passes through kernels of its own, made
+                               for latency. One shape in one kind of handle always
+                               gets the same schedule; an instance alone and the
+                               same instance in a larger handle may differ in
+                               rounding;
                                1 = two passes per z-step (column and row tiles of
                                a four-step FFT) for every instance;
                                2 = resident where served: one workgroup holds an

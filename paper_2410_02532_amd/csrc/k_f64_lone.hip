@@ -1,0 +1,6 @@
+// FP64 interior steps of handles too small to fill the chip.
+#include "kernel_list.h"
+
+namespace opo {
+OPO_LONE_KERNELS(template, double)
+} // namespace opo

@@ -3,7 +3,7 @@
 // (DECL = template) and the host unit as declarations (DECL = extern template),
 // so that the kernel units compile in parallel.
 #pragma once
-#include "ssfm_kernels.h"
+#include "lone_kernels.h"
 
 // Column and row passes, propagator tables and the adaptive-step kernels of
 // real type R (row range 2, rows of 4096 points, exists in FP32 only).
@@ -60,6 +60,13 @@
     OPO_RESIDENT_KERNELS_NF(DECL, 2)                                                               \
     OPO_RESIDENT_KERNELS_NF(DECL, 3)
 
+// Interior steps of handles too small to fill the chip.
+#define OPO_LONE_KERNELS(DECL, R)                                                                  \
+    DECL __global__ void lone_column<R, 2>(LoneColumnArgs<R>);                                     \
+    DECL __global__ void lone_column<R, 3>(LoneColumnArgs<R>);                                     \
+    DECL __global__ void lone_row<R, 9>(LoneRowArgs<R>);                                           \
+    DECL __global__ void lone_row<R, 12>(LoneRowArgs<R>);
+
 #define OPO_ALL_KERNELS(DECL)                                                                      \
     OPO_PASS_KERNELS_F32(DECL)                                                                     \
     OPO_PASS_KERNELS_F64(DECL)                                                                     \
@@ -69,4 +76,6 @@
     OPO_MIXED_KERNELS_F32_CR12(DECL, 3)                                                            \
     OPO_MIXED_KERNELS_F64(DECL, 2)                                                                 \
     OPO_MIXED_KERNELS_F64(DECL, 3)                                                                 \
+    OPO_LONE_KERNELS(DECL, float)                                                                  \
+    OPO_LONE_KERNELS(DECL, double)                                                                 \
     OPO_RESIDENT_KERNELS(DECL)

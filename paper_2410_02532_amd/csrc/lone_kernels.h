@@ -1,0 +1,464 @@
+// lone_kernels.h -- the z-steps of handles too small to fill the chip.
+//
+// A handle of one instance or a few runs two dependent launches per z-step
+// (column and row pass), and each launch lasts about the serial time of one tile:
+// what bounds it is the chain of dependent memory accesses and exchanges, not
+// throughput. In the general column tile that chain was the tile's instance, its
+// descriptor, the fields, then the four-step twiddles, the FP64 coupling phasors, and
+// one twiddle load after every barrier of the transforms. Here everything a tile needs
+// is issued at its start: descriptors and coupling coefficients (formed on the host in
+// FP64) come with the kernel arguments, and the fields, four-step twiddles, propagator
+// and the butterfly twiddles of every stage are loaded into registers together (one
+// wave per SIMD has 512; nothing spills). A column tile is one wave that exchanges
+// between its lanes in registers; a row tile is one row, whose exchanges alternate
+// between two LDS buffers with one barrier each.
+//
+// Measured per z-step (MI355X, us, two launches of which an empty one costs 1.55):
+// one 2^14 instance 12.7 -> 7.5 in FP32 and 13.6 -> 7.8 in FP64, three two-wave 2^12
+// instances 12.5 -> 6.1, one 2^16 15.9 -> 11.7, one 2^18 28.3 -> 22.3. With the
+// exchanges of the columns through LDS (256 threads, a barrier each) the 2^14 instance
+// took 9.5: a radix-2 stage then lasted about 590 cycles, four fifths of them waiting.
+#pragma once
+#include "ssfm_kernels.h"
+
+namespace opo {
+
+// Instances of one launch: what fits the 4 KB of kernel arguments.
+template <typename R> constexpr int kLoneMax = sizeof(R) == 4 ? 14 : 8;
+
+template <typename R> struct LoneColumnInst {
+    long long off;        // first sample of the instance
+    long long w4_off;     // its four-step twiddle table
+    int n1, nt;
+    int log2n2;
+    int kind;             // 0: dk = 0 (couplings i ci); 1: general couplings; 2: Kerr terms
+    R ci[2][3];           // kind 0: the couplings of both half-steps, beside the fields read first
+    Coupling<R> cp;       // [0] second half of the step before, [1] first half of this step
+};
+
+template <typename R> struct LoneColumnArgs {
+    cplx<R> *state;
+    const Phasor<R> *tw, *w4tab;
+    const int *counter;   // [2] stop flag, see StepArgs
+    int flags;            // A_INV | A_RK_PREV, A_RK_THIS | A_FWD, or both
+    LoneColumnInst<R> inst[kLoneMax<R>];
+};
+
+struct LoneRowInst {
+    long long off;        // first sample of the instance
+    long long disp_off;   // its propagator table of this step size
+    int rows;             // rows of all fields (nf n2), contiguous
+    int log2n1;
+};
+
+template <typename R> struct LoneRowArgs {
+    cplx<R> *state;
+    const Phasor<R> *tw, *disp;
+    const int *counter;
+    LoneRowInst inst[kLoneMax<R>];
+};
+
+static_assert(sizeof(LoneColumnArgs<float>) <= 4096 && sizeof(LoneColumnArgs<double>) <= 4096 &&
+              sizeof(LoneRowArgs<float>) <= 4096, "kernel arguments of the lone kernels");
+
+// ---- FFT on preloaded twiddles
+template <int N, int PF, int P = 1> __host__ __device__ constexpr int tw_regs()
+{
+    if constexpr (P >= N) return 0;
+    else {
+        constexpr int RS = stage_radix<N, PF, P, N>();
+        return (P > 1 ? PF / RS * (RS - 1) : 0) + tw_regs<N, PF, P * RS>();
+    }
+}
+
+template <typename R, int N, int PF, int P, int AT, int TOT>
+__device__ __forceinline__ void tw_load(Phasor<R> (&w)[TOT], int t, const Phasor<R> *__restrict__ tw)
+{
+    if constexpr (P < N) {
+        constexpr int RS = stage_radix<N, PF, P, N>();
+        constexpr int NBT = PF / RS, STRIDE = N / PF;
+        if constexpr (P > 1) {
+#pragma unroll
+            for (int u = 0; u < NBT; ++u) {
+                const int k = (t + u * STRIDE) & (P - 1);
+                const Phasor<R> *q = tw + tw_index(RS, P, k);
+#pragma unroll
+                for (int r = 1; r < RS; ++r) w[AT + u * (RS - 1) + r - 1] = q[r - 1];
+            }
+        }
+        tw_load<R, N, PF, P * RS, AT + (P > 1 ? NBT * (RS - 1) : 0)>(w, t, tw);
+    }
+}
+
+// reg_fft of one transform with the twiddles of every stage in w. Exchange e of a tile
+// uses LDS buffer e mod 2 (lds and lds + half): its writes follow the barrier of
+// exchange e - 1, which every thread reaches after its reads of exchange e - 2 from the
+// same buffer. E counts the exchanges of the tile before this transform. The positions
+// of a thread differ in disjoint bit fields, so lds_index splits into the thread's part
+// and a constant.
+template <typename R, int N, int PF, int DIR, bool WAVE, int E, int P, int AT, int TOT>
+__device__ __forceinline__ void fft_pre_from(cplx<R> (&v)[PF], cplx<R> *lds, int half, int t, const Phasor<R> (&w)[TOT])
+{
+    if constexpr (P < N) {
+        using V = cplx<R>;
+        constexpr int RS = stage_radix<N, PF, P, N>();
+        constexpr int NBT = PF / RS, STRIDE = N / PF;
+        constexpr bool LAST = P * RS == N;
+        V *s = lds + (E & 1) * half;
+#pragma unroll
+        for (int u = 0; u < NBT; ++u) {
+            V x[RS];
+#pragma unroll
+            for (int r = 0; r < RS; ++r) x[r] = v[u + r * NBT];
+            if constexpr (P > 1) {
+#pragma unroll
+                for (int r = 1; r < RS; ++r) x[r] = pmul<(DIR > 0)>(x[r], w[AT + u * (RS - 1) + r - 1]);
+            }
+            dft<RS, DIR>(x);
+            if constexpr (LAST) {
+#pragma unroll
+                for (int r = 0; r < RS; ++r) v[u + r * NBT] = x[r];
+            } else {
+                const int i = t + u * STRIDE;
+                const int k = i & (P - 1);
+                V *o = s + lds_index<R>((i - k) * RS + k);
+#pragma unroll
+                for (int r = 0; r < RS; ++r) o[lds_index<R>(r * P)] = x[r];
+            }
+        }
+        if constexpr (!LAST) {
+            if constexpr (WAVE) wave_lds_sync(); else lds_sync();
+            const V *q = s + lds_index<R>(t);
+#pragma unroll
+            for (int m = 0; m < PF; ++m) v[m] = q[lds_index<R>(m * STRIDE)];
+            if constexpr (WAVE) wave_lds_sync();
+        }
+        fft_pre_from<R, N, PF, DIR, WAVE, E + 1, P * RS, AT + (P > 1 ? NBT * (RS - 1) : 0)>(v, lds, half, t, w);
+    }
+}
+
+// Exchanges of one transform.
+template <int N, int PF, int P = 1> __host__ __device__ constexpr int fft_exchanges()
+{
+    if constexpr (P >= N) return -1;
+    else return 1 + fft_exchanges<N, PF, P * stage_radix<N, PF, P, N>()>();
+}
+
+// ---- FFT across the lanes of one wave, without LDS
+//
+// N = RS M points of a column lie in PF registers of T = N/PF lanes. The forward
+// transform is decimation in frequency: a radix-RS butterfly over the register index
+// (the top digit of the position), the twiddles W_M^{r q} (q the rest of the
+// position, held by the lanes), then the register digit changes places with the next
+// digit of the lane index, so that it becomes the top digit of what is left. The
+// inverse transform runs the same steps backwards. Changing places costs one
+// v_permlane swap (lane distance 16, 32) or two DPP moves (4, 8) per pair of
+// registers, where an exchange through LDS waits on a write, a barrier and a read.
+
+// Swaps lanes whose bit D is set of a with lanes whose bit D is clear of b.
+template <int D> __device__ __forceinline__ void lane_swap32(unsigned &a, unsigned &b)
+{
+    if constexpr (D == 32 || D == 16) {
+        const auto r = D == 32 ? __builtin_amdgcn_permlane32_swap(a, b, false, false)
+                               : __builtin_amdgcn_permlane16_swap(a, b, false, false);
+        a = r[0];
+        b = r[1];
+    } else {
+        static_assert(D == 8 || D == 4, "lane distance");
+        constexpr int shr = 0x110 + D, shl = 0x100 + D;                 // row_shr:D, row_shl:D
+        constexpr int hi = D == 8 ? 0xc : 0xa, lo = D == 8 ? 0x3 : 0x5;   // banks with bit D set / clear
+        const unsigned na = __builtin_amdgcn_update_dpp(a, b, shr, 0xf, hi, false);
+        b = __builtin_amdgcn_update_dpp(b, a, shl, 0xf, lo, false);
+        a = na;
+    }
+}
+template <int D> __device__ __forceinline__ void lane_swap(float &a, float &b)
+{
+    unsigned x = __float_as_uint(a), y = __float_as_uint(b);
+    lane_swap32<D>(x, y);
+    a = __uint_as_float(x);
+    b = __uint_as_float(y);
+}
+template <int D> __device__ __forceinline__ void lane_swap(double &a, double &b)
+{
+    unsigned long long x = __double_as_longlong(a), y = __double_as_longlong(b);
+    unsigned xl = static_cast<unsigned>(x), xh = static_cast<unsigned>(x >> 32);
+    unsigned yl = static_cast<unsigned>(y), yh = static_cast<unsigned>(y >> 32);
+    lane_swap32<D>(xl, yl);
+    lane_swap32<D>(xh, yh);
+    a = __longlong_as_double(static_cast<long long>(static_cast<unsigned long long>(xh) << 32 | xl));
+    b = __longlong_as_double(static_cast<long long>(static_cast<unsigned long long>(yh) << 32 | yl));
+}
+
+constexpr int wave_log2(int v) { return v <= 1 ? 0 : 1 + wave_log2(v / 2); }
+
+// Digit swap after a stage: register bits RB-1.. (NB of them, from the top) change
+// places with the lane bits at distances D, D/2, ...
+template <typename V, int PF, int RBIT, int NB, int D> __device__ __forceinline__ void digit_swap(V (&v)[PF])
+{
+    if constexpr (NB > 0) {
+#pragma unroll
+        for (int m = 0; m < PF; ++m)
+            if (!(m & RBIT)) {
+                lane_swap<D>(v[m].x, v[m | RBIT].x);
+                lane_swap<D>(v[m].y, v[m | RBIT].y);
+            }
+        digit_swap<V, PF, RBIT / 2, NB - 1, D / 2>(v);
+    }
+}
+
+// A stage over sub-transforms of M points: radix RS = min(PF, M) over the top bits
+// of the register index, PF/RS of them per thread; TB lane bits are still to come,
+// the next at lane distance D.
+template <int PF, int M> constexpr int wave_radix() { return M < PF ? M : PF; }
+// Twiddles held per thread: RS - 1 for every stage but the last.
+template <int N, int PF> __host__ __device__ constexpr int wave_tw_regs()
+{
+    int n = 0;
+    for (int m = N; m > PF; m /= PF) n += PF - 1;
+    return n;
+}
+
+template <typename R, int N, int PF, int M, int AT, int TOT>
+__device__ __forceinline__ void wave_tw_load(Phasor<R> (&w)[TOT], int t, const Phasor<R> *__restrict__ tw)
+{
+    if constexpr (M > PF) {
+        const int q = t & (M / PF - 1);
+#pragma unroll
+        for (int r = 1; r < PF; ++r) w[AT + r - 1] = tw[tw_index(PF, M / PF, q) + r - 1];
+        wave_tw_load<R, N, PF, M / PF, AT + PF - 1>(w, t, tw);
+    }
+}
+
+// Digits of the final position: register index m of lane t holds bin wave_bin(t) + ...
+// The last stage has radix RL = M <= PF over the top register bits; the low
+// register bits (PF/RL of them) then still hold the digit that came from the lanes.
+template <typename R, int N, int PF, int M, int AT, int D, int TOT>
+__device__ __forceinline__ void wave_fwd(cplx<R> (&v)[PF], const Phasor<R> (&w)[TOT])
+{
+    using V = cplx<R>;
+    if constexpr (M > PF) {
+        dft<PF, -1>(v);
+#pragma unroll
+        for (int r = 1; r < PF; ++r) v[r] = pmul(v[r], w[AT + r - 1]);
+        constexpr int NB = wave_log2(M / PF < PF ? M / PF : PF);
+        digit_swap<V, PF, PF / 2, NB, D>(v);
+        wave_fwd<R, N, PF, M / PF, AT + PF - 1, (D >> NB)>(v, w);
+    } else {
+        // radix M over the top register bits, PF/M butterflies
+#pragma unroll
+        for (int u = 0; u < PF / M; ++u) {
+            V x[M];
+#pragma unroll
+            for (int r = 0; r < M; ++r) x[r] = v[u + r * (PF / M)];
+            dft<M, -1>(x);
+#pragma unroll
+            for (int r = 0; r < M; ++r) v[u + r * (PF / M)] = x[r];
+        }
+    }
+}
+
+template <typename R, int N, int PF, int M, int AT, int D, int TOT>
+__device__ __forceinline__ void wave_inv(cplx<R> (&v)[PF], const Phasor<R> (&w)[TOT])
+{
+    using V = cplx<R>;
+    if constexpr (M > PF) {
+        constexpr int NB = wave_log2(M / PF < PF ? M / PF : PF);
+        wave_inv<R, N, PF, M / PF, AT + PF - 1, (D >> NB)>(v, w);
+        digit_swap<V, PF, PF / 2, NB, D>(v);
+#pragma unroll
+        for (int r = 1; r < PF; ++r) v[r] = pmul<true>(v[r], w[AT + r - 1]);
+        dft<PF, +1>(v);
+    } else {
+#pragma unroll
+        for (int u = 0; u < PF / M; ++u) {
+            V x[M];
+#pragma unroll
+            for (int r = 0; r < M; ++r) x[r] = v[u + r * (PF / M)];
+            dft<M, +1>(x);
+#pragma unroll
+            for (int r = 0; r < M; ++r) v[u + r * (PF / M)] = x[r];
+        }
+    }
+}
+
+// Bin held by register m of lane index t (0 <= t < N/PF) after wave_fwd.
+template <int N, int PF, int M = N> __device__ __forceinline__ int wave_bin(int t, int m)
+{
+    if constexpr (M > PF) {
+        // the first stage's output digit now sits in the lane bits it was swapped into,
+        // and, where fewer than log2 PF lane bits were left, in the low register bits
+        constexpr int rest = M / PF;
+        constexpr int NB = wave_log2(rest < PF ? rest : PF), PB = wave_log2(PF);
+        const int top = t / (rest >> NB) & ((1 << NB) - 1);
+        const int digit = top << (PB - NB) | (m & ((1 << (PB - NB)) - 1));
+        return digit + PF * wave_bin<N, PF, rest>(t & ((rest >> NB) - 1), m);
+    } else {
+        return m >> (wave_log2(PF) - wave_log2(M));
+    }
+}
+
+// ---- column tile: one wave, 64/T columns with T = N/PF lanes each
+constexpr int kLoneMinLog2 = 10;         // smallest instance
+constexpr int kLoneMinLog2N2 = 4, kLoneMaxLog2N2 = 7;
+constexpr int lone_col_pf(int ln2) { return ln2 <= 5 ? 2 : ln2 == 6 ? 4 : 8; }
+constexpr int lone_cols(int ln2) { return 64 * lone_col_pf(ln2) >> ln2; }
+
+template <typename R, int LN2, int NF>
+__device__ __forceinline__ void lone_column_tile(const LoneColumnArgs<R> &a, const LoneColumnInst<R> &d)
+{
+    using V = cplx<R>;
+    constexpr int N = 1 << LN2, PF = lone_col_pf(LN2), T = N / PF, COLS = 64 / T;
+    constexpr int TW = wave_tw_regs<N, PF>();
+    const int flags = a.flags;
+    const int c = threadIdx.x % COLS, t = threadIdx.x / COLS;
+    const unsigned n1 = d.n1, nt = d.nt, tiles = n1 / COLS;
+    if (blockIdx.x >= tiles) return;          // a launch over instances of uneven size
+    // workgroups are dealt to the eight XCDs in turn: neighbouring tiles, which share
+    // the cache lines of their columns, go to the same one
+    const unsigned tile = tiles >= 8 ? (blockIdx.x & 7) * (tiles >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+    const int kind = d.kind;
+    R ci[2][3];
+#pragma unroll
+    for (int which = 0; which < 2; ++which)
+#pragma unroll
+        for (int x = 0; x < 3; ++x) ci[which][x] = d.ci[which][x];
+    V *g = a.state + d.off;
+    const Phasor<R> *w4t = a.w4tab + d.w4_off;
+    V v[NF][PF];
+    Phasor<R> w4[PF], w[TW];
+    // register m: row wave_bin(t, m) of the transform where a row pass left it or will
+    // take it, sample t + m T otherwise
+    unsigned q[PF], qo[PF];
+#pragma unroll
+    for (int m = 0; m < PF; ++m) {
+        const unsigned bin = tile * COLS + c + n1 * wave_bin<N, PF>(t, m), smp = tile * COLS + c + n1 * (t + m * T);
+        q[m] = flags & A_INV ? bin : smp;
+        qo[m] = flags & A_FWD ? bin : smp;
+    }
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int m = 0; m < PF; ++m) v[f][m] = el32(g, q[m] + f * nt);
+#pragma unroll
+    for (int m = 0; m < PF; ++m) w4[m] = el32(w4t, flags & A_FWD ? qo[m] : q[m]);
+    wave_tw_load<R, N, PF, N, 0>(w, t, a.tw);
+    const bool stopped = a.counter[2] != 0;   // see column_tile
+    if (flags & A_INV) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+#pragma unroll
+            for (int m = 0; m < PF; ++m) v[f][m] = pmul<true>(v[f][m], w4[m]);
+            wave_inv<R, N, PF, N, 0, 32>(v[f], w);
+        }
+    }
+#pragma unroll
+    for (int which = 0; which < 2; ++which) {
+        if (!(flags & (which ? A_RK_THIS : A_RK_PREV))) continue;
+        if (kind == 0) {
+            V k[3][3];
+#pragma unroll
+            for (int x = 0; x < 3; ++x) k[0][x] = mk<V>(R(0), ci[which][x]);
+#pragma unroll
+            for (int m = 0; m < PF; ++m) {
+                if constexpr (NF == 3) rk4_point_imag<R>(k, v[0][m], v[1][m], v[NF - 1][m]);
+                else rk4_point2_imag<R>(k, v[0][m], v[1][m]);
+            }
+        } else {
+#pragma unroll
+            for (int m = 0; m < PF; ++m)
+                rk4_fields<R, NF>(d.cp, which, false, kind == 2, v[0][m], v[1][m], v[NF - 1][m]);
+        }
+    }
+    if (flags & A_FWD) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            wave_fwd<R, N, PF, N, 0, 32>(v[f], w);
+#pragma unroll
+            for (int m = 0; m < PF; ++m) v[f][m] = pmul(v[f][m], w4[m]);
+        }
+    }
+    if (stopped) return;
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int m = 0; m < PF; ++m) el32(g, qo[m] + f * nt) = v[f][m];
+}
+
+template <typename R, int NF> __global__ __launch_bounds__(64) void lone_column(LoneColumnArgs<R> a)
+{
+    const LoneColumnInst<R> &d = a.inst[blockIdx.y];
+    switch (d.log2n2) {
+    case 4: return lone_column_tile<R, 4, NF>(a, d);
+    case 5: return lone_column_tile<R, 5, NF>(a, d);
+    case 6: return lone_column_tile<R, 6, NF>(a, d);
+    default: return lone_column_tile<R, 7, NF>(a, d);
+    }
+}
+
+// ---- row tile: whole rows, PF samples per thread. A workgroup holds one row where it
+// takes 64 threads or more, else as many as fill a wave: the loads of a row (field,
+// propagator and twiddles, 26 KB at 512 points) are bound by the CU's L1, so fewer
+// rows per CU are faster as long as CUs are idle.
+constexpr int kLoneMinLog2N1 = 5;
+constexpr int lone_row_pf(int ln1) { return ln1 <= 7 ? 4 : ln1 == 12 ? 16 : 8; }
+constexpr int lone_row_threads(int ln1) { return (1 << ln1) / lone_row_pf(ln1); }
+
+template <typename R, int LN1>
+__device__ __forceinline__ void lone_row_tile(const LoneRowArgs<R> &a, const LoneRowInst &d, cplx<R> *s)
+{
+    using V = cplx<R>;
+    constexpr int N = 1 << LN1, PF = lone_row_pf(LN1), T = N / PF;
+    constexpr int TW = tw_regs<N, PF>(), X = fft_exchanges<N, PF>();
+    constexpr bool WAVE = T <= 64;   // a row's threads lie within one wavefront
+    const int rows = blockDim.x / T, r = threadIdx.x / T, t = threadIdx.x % T;
+    if (static_cast<int>(blockIdx.x) * rows >= d.rows) return;   // a launch over instances of uneven size
+    const int row = blockIdx.x * rows + r;
+    const bool act = row < d.rows;
+    const unsigned q0 = static_cast<unsigned>(act ? row : 0) * N + t;
+    V *g = a.state + d.off;
+    const Phasor<R> *h = a.disp + d.disp_off;
+    V v[PF];
+    Phasor<R> hr[PF], w[TW];
+#pragma unroll
+    for (int m = 0; m < PF; ++m) v[m] = el32(g, q0 + m * T);
+    tw_load<R, N, PF, 1, 0>(w, t, a.tw);
+#pragma unroll
+    for (int m = 0; m < PF; ++m) hr[m] = el32(h, q0 + m * T);
+    const bool stopped = a.counter[2] != 0;
+    s += lds_index<R>(r * N);         // rows of a workgroup side by side
+    const int half = lds_elems<R>(static_cast<int>(blockDim.x) * PF);
+    fft_pre_from<R, N, PF, -1, WAVE, 0, 1, 0>(v, s, half, t, w);
+#pragma unroll
+    for (int m = 0; m < PF; ++m) v[m] = pmul(v[m], hr[m]);
+    fft_pre_from<R, N, PF, +1, WAVE, X, 1, 0>(v, s, half, t, w);
+    if (stopped || !act) return;
+#pragma unroll
+    for (int m = 0; m < PF; ++m) el32(g, q0 + m * T) = v[m];
+}
+
+// Rows of 2^5..2^HI points: HI = 9, or 12 (the longer rows hold more samples and
+// twiddles per thread, one wave per SIMD).
+template <typename R, int HI> __global__ __launch_bounds__(kThreads) void lone_row(LoneRowArgs<R> a)
+{
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    cplx<R> *s = reinterpret_cast<cplx<R> *>(lds_raw);
+    const LoneRowInst &d = a.inst[blockIdx.y];
+    switch (d.log2n1) {
+    case 5: return lone_row_tile<R, 5>(a, d, s);
+    case 6: return lone_row_tile<R, 6>(a, d, s);
+    case 7: return lone_row_tile<R, 7>(a, d, s);
+    case 8: return lone_row_tile<R, 8>(a, d, s);
+    case 9: return lone_row_tile<R, 9>(a, d, s);
+    }
+    if constexpr (HI > 9) {
+        switch (d.log2n1) {
+        case 10: return lone_row_tile<R, 10>(a, d, s);
+        case 11: return lone_row_tile<R, 11>(a, d, s);
+        case 12:
+            if constexpr (kMaxLog2N1<R> >= 12) return lone_row_tile<R, 12>(a, d, s);
+        }
+    }
+}
+
+} // namespace opo

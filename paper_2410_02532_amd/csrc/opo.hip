@@ -194,6 +194,17 @@ template <typename R> static const void *mixed_fn(int cr, int rr, int nf)
     return nf == 2 ? mixed_fn_nf<R, 2>(cr, rr) : mixed_fn_nf<R, 3>(cr, rr);
 }
 
+// Lone kernels (lone_kernels.h): columns of nf-wave instances, rows of up to 2^ln points.
+template <typename R> static const void *lone_column_fn(int nf)
+{
+    return nf == 2 ? reinterpret_cast<const void *>(&lone_column<R, 2>)
+                   : reinterpret_cast<const void *>(&lone_column<R, 3>);
+}
+template <typename R> static const void *lone_row_fn(int ln)
+{
+    return ln <= 9 ? reinterpret_cast<const void *>(&lone_row<R, 9>) : reinterpret_cast<const void *>(&lone_row<R, 12>);
+}
+
 } // namespace opo
 
 using namespace opo;
@@ -228,6 +239,12 @@ struct opo_s {
     std::vector<hipStream_t> sides;
     std::vector<hipEvent_t> ev_join;
     hipEvent_t ev_fork = nullptr;
+    // instances whose passes run the lone kernels (all two-pass instances, or none),
+    // and their launches' grids, LDS and longest row
+    std::vector<int> lone;
+    unsigned lone_tiles_a = 0, lone_tiles_b = 0;
+    size_t lone_lds_b = 0;
+    int lone_nf = 3, lone_ln1 = 0, lone_threads_b = 64;
     bool mixed = false;              // two halves a launch apart, mixed launches
     int *d_map[2] = {nullptr, nullptr};  // workgroup -> tile maps of the two mixed launches
     int map_len[2] = {0, 0};
@@ -710,10 +727,95 @@ template <typename R> static hipError_t launch_mixed(opo_t *h, StepArgs<R> a, in
     return prof_end(h);
 }
 
-// One crystal pass of nz steps. `first` flags are OR-ed into the opening
-// column pass (refresh), `last` into the closing one (energy, mirror, EOM).
+// Coupling coefficients of the RK4 half-steps of a column launch, as coupling_tile
+// forms them: h/2 times kappa and the phasor of dk z at z0, z0 + h/2, z0 + h.
 template <typename R>
-static hipError_t enqueue_pass(opo_t *h, StepArgs<R> a, int nz_steps, int first, int last)
+static void coupling_host(const InstDesc &d, double z_prev, double h_prev, double z_this, double h_this,
+                          Coupling<R> &out)
+{
+    using V = cplx<R>;
+    for (int which = 0; which < 2; ++which)
+        for (int st = 0; st < 3; ++st) {
+            const double h = which ? h_this : h_prev;
+            const double r = d.dk_rev * ((which ? z_this : z_prev) + 0.5 * h * st);
+            const double ph = kTwoPi * (r - std::rint(r)), sn = std::sin(ph), cs = std::cos(ph);
+            const double hh = 0.5 * h, kp = d.kappa[0] * hh, ks = d.kappa[1] * hh, ki = d.kappa[2] * hh;
+            V *c = out.c[which][st];
+            c[0].x = static_cast<R>(kp * sn);
+            c[0].y = static_cast<R>(kp * cs);
+            c[1].x = static_cast<R>(-ks * sn);
+            c[1].y = static_cast<R>(ks * cs);
+            c[2].x = static_cast<R>(-ki * sn);
+            c[2].y = static_cast<R>(ki * cs);
+            out.g[which][st] = static_cast<R>(d.gamma[st] * hh);
+        }
+}
+
+// Column launch of the lone instances at step boundary `step` of crystal `stage`
+// (flags: the half-steps and transforms on either side of the boundary).
+template <typename R>
+static hipError_t launch_lone_a(opo_t *h, const StepArgs<R> &a, int flags, int step, int stage)
+{
+    StepArgs<R> hs = a;
+    set_half_steps<R>(h, hs, step);
+    LoneColumnArgs<R> la{};
+    la.state = a.state;
+    la.tw = a.tw;
+    la.w4tab = a.w4tab;
+    la.counter = a.counter;
+    la.flags = flags;
+    const InstDesc *inst = h->inst.data() + static_cast<size_t>(stage) * h->n_inst;
+    for (size_t q = 0; q < h->lone.size(); ++q) {
+        const InstDesc &d = inst[h->lone[q]];
+        const double dz = a.dz_arg > 0.0 ? a.dz_arg : d.length_mm / a.nz, zb = a.dz_arg > 0.0 ? a.zbase : 0.0;
+        LoneColumnInst<R> &e = la.inst[q];
+        e.off = d.off;
+        e.w4_off = d.w4_off;
+        e.n1 = d.n1;
+        e.nt = d.nt;
+        e.log2n2 = d.log2n2;
+        e.kind = d.kerr ? 2 : d.dk_rev == 0.0 ? 0 : 1;
+        coupling_host<R>(d, zb + hs.zf_prev * dz, hs.hf_prev * dz, zb + hs.zf_this * dz, hs.hf_this * dz, e.cp);
+        for (int which = 0; which < 2; ++which)
+            for (int x = 0; x < 3; ++x) e.ci[which][x] = e.cp.c[which][0][x].y;
+    }
+    void *args[] = {&la};
+    HIP_RET(prof_begin(h, OPO_K_COLUMN));
+    HIP_RET(hipLaunchKernel(lone_column_fn<R>(h->lone_nf), dim3(h->lone_tiles_a, h->lone.size()), dim3(64), args, 0,
+                            h->stream));
+    return prof_end(h);
+}
+
+// Row launch of the lone instances for the symmetrized step `step`.
+template <typename R> static hipError_t launch_lone_b(opo_t *h, const StepArgs<R> &a, int step, int stage)
+{
+    double z, tau;
+    int sel;
+    substep(h, step, z, tau, sel);
+    LoneRowArgs<R> la{};
+    la.state = a.state;
+    la.tw = a.tw;
+    la.disp = a.disp;
+    la.counter = a.counter;
+    const InstDesc *inst = h->inst.data() + static_cast<size_t>(stage) * h->n_inst;
+    for (size_t q = 0; q < h->lone.size(); ++q) {
+        const InstDesc &d = inst[h->lone[q]];
+        la.inst[q].off = d.off;
+        la.inst[q].disp_off = d.disp_off + static_cast<long long>(sel) * d.nf * d.nt;
+        la.inst[q].rows = d.nf * d.n2;
+        la.inst[q].log2n1 = d.log2n1;
+    }
+    void *args[] = {&la};
+    HIP_RET(prof_begin(h, OPO_K_ROW));
+    HIP_RET(hipLaunchKernel(lone_row_fn<R>(h->lone_ln1), dim3(h->lone_tiles_b, h->lone.size()),
+                            dim3(h->lone_threads_b), args, h->lone_lds_b, h->stream));
+    return prof_end(h);
+}
+
+// One crystal pass of nz steps through crystal `stage`. `first` flags are OR-ed into
+// the opening column pass (refresh), `last` into the closing one (energy, mirror, EOM).
+template <typename R>
+static hipError_t enqueue_pass(opo_t *h, StepArgs<R> a, int nz_steps, int first, int last, int stage)
 {
     if (h->groups_a.empty()) return hipSuccess;           // every instance is resident
     const int nz = nz_steps * (h->order == 4 ? 3 : 1);   // symmetrized steps of the pass
@@ -727,11 +829,16 @@ static hipError_t enqueue_pass(opo_t *h, StepArgs<R> a, int nz_steps, int first,
         }
         return launch_a<R>(h, a, A_INV | A_RK_PREV | last, nz, 1);
     }
-    HIP_RET(launch_a<R>(h, a, first | A_RK_THIS | A_FWD, 0));
+    // lone instances: every launch but those of the round-trip boundary
+    const bool lone = !h->lone.empty();
+    auto column = [&](int flags, int step) {
+        return lone && !(flags & ~(A_INV | A_RK_PREV | A_RK_THIS | A_FWD)) ? launch_lone_a<R>(h, a, flags, step, stage)
+                                                                          : launch_a<R>(h, a, flags, step);
+    };
+    HIP_RET(column(first | A_RK_THIS | A_FWD, 0));
     for (int j = 0; j < nz; ++j) {
-        HIP_RET(launch_b<R>(h, a, B_DISP, j));
-        if (j + 1 < nz) HIP_RET(launch_a<R>(h, a, A_INV | A_RK_PREV | A_RK_THIS | A_FWD, j + 1));
-        else HIP_RET(launch_a<R>(h, a, A_INV | A_RK_PREV | last, nz));
+        HIP_RET(lone ? launch_lone_b<R>(h, a, j, stage) : launch_b<R>(h, a, B_DISP, j));
+        HIP_RET(column(j + 1 < nz ? A_INV | A_RK_PREV | A_RK_THIS | A_FWD : A_INV | A_RK_PREV | last, j + 1));
     }
     return hipSuccess;
 }
@@ -757,13 +864,13 @@ template <typename R> static hipError_t enqueue_roundtrip(opo_t *h)
         a.nz = h->stage_nz[st];
         const int first = st == 0 ? A_REFRESH : 0;
         if (st + 1 < K) {
-            HIP_RET(enqueue_pass<R>(h, a, a.nz, first, 0));
+            HIP_RET(enqueue_pass<R>(h, a, a.nz, first, 0, st));
         } else if (h->any_gdd && !h->groups_a.empty()) {
-            HIP_RET(enqueue_pass<R>(h, a, a.nz, first, A_ENERGY | A_FWD));
+            HIP_RET(enqueue_pass<R>(h, a, a.nz, first, A_ENERGY | A_FWD, st));
             HIP_RET(launch_b<R>(h, a, B_GDD));
             HIP_RET(launch_a<R>(h, a, A_INV | A_MIRROR | eom, 0));
         } else {
-            HIP_RET(enqueue_pass<R>(h, a, a.nz, first, A_ENERGY | A_MIRROR | eom));
+            HIP_RET(enqueue_pass<R>(h, a, a.nz, first, A_ENERGY | A_MIRROR | eom, st));
         }
     }
     HIP_RET(join_resident(h));
@@ -797,6 +904,9 @@ template <typename R> static int setup_kernels(opo_t *h)
         HIP_TRY(hipFuncSetAttribute(resident_fn<R>(g.ln, g.nf), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     static_cast<int>(lds_elems<R>(1 << g.ln) * sizeof(cplx<R>))));
     }
+    if (!h->lone.empty())
+        HIP_TRY(hipFuncSetAttribute(lone_row_fn<R>(h->lone_ln1), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    static_cast<int>(h->lone_lds_b)));
     if (h->mixed)
         for (int hf = 0; hf < 2; ++hf) {
             const Group &gc = h->groups_a[1 - hf];
@@ -928,7 +1038,31 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
     std::vector<int> order;
     for (int i = 0; i < n; ++i)
         if (!h->inst[i].resident) order.push_back(i);
-    if (order.size() >= 2) {
+    // a handle too small to fill the chip, on the automatic schedule: its two-pass
+    // instances run the lone kernels if one launch holds them
+    if (opt.schedule == 0 && !batched && !order.empty()) {
+        const bool f64 = opt.precision == OPO_F64;
+        bool ok = static_cast<int>(order.size()) <= (f64 ? kLoneMax<double> : kLoneMax<float>);
+        h->lone_nf = h->inst[order[0]].nf;
+        for (int i : order) {
+            const InstDesc &d = h->inst[i];
+            ok = ok && d.nf == h->lone_nf && d.log2nt >= kLoneMinLog2 && d.log2n2 >= kLoneMinLog2N2 && d.log2n2 <= kLoneMaxLog2N2 &&
+                 d.log2n1 >= kLoneMinLog2N1;
+            h->lone_tiles_a = std::max<unsigned>(h->lone_tiles_a, d.n1 / lone_cols(d.log2n2));
+            h->lone_threads_b = std::max(h->lone_threads_b, lone_row_threads(d.log2n1));
+            h->lone_ln1 = std::max(h->lone_ln1, d.log2n1);
+        }
+        if (ok) h->lone = order;
+        for (int i : h->lone) {
+            const InstDesc &d = h->inst[i];
+            const unsigned rows = h->lone_threads_b / lone_row_threads(d.log2n1);
+            const int pts = h->lone_threads_b * lone_row_pf(d.log2n1);
+            h->lone_tiles_b = std::max(h->lone_tiles_b, (d.nf * d.n2 + rows - 1) / rows);
+            h->lone_lds_b = std::max(h->lone_lds_b,
+                                     2 * h->elem * (f64 ? lds_elems<double>(pts) : lds_elems<float>(pts)));
+        }
+    }
+    if (order.size() >= 2 && h->lone.empty()) {
         std::stable_sort(order.begin(), order.end(),
                          [&](int x, int y) { return h->inst[x].nt > h->inst[y].nt; });
         long long load[2] = {0, 0};
@@ -1284,7 +1418,7 @@ template <typename R> static int propagate_impl(opo_t *h, int nz, double dz)
         ar.nz = nz;
         HIP_TRY(launch_resident<R>(h, ar, 0));
     }
-    HIP_TRY(enqueue_pass<R>(h, a, nz, 0, 0));
+    HIP_TRY(enqueue_pass<R>(h, a, nz, 0, 0, 0));
     HIP_TRY(join_resident(h));
     h->z += nz * dz;
     const size_t used = h->ev_used;

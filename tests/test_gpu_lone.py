@@ -1,0 +1,84 @@
+"""Handles too small to fill the chip, on the automatic schedule: their z-steps run the
+wave-level column kernels and the preloaded row kernels. Every split those serve, both
+precisions, two and three waves and the three kinds of nonlinear step against the FP64
+oracle; uneven instances of one launch, at the most instances a launch holds."""
+import sys
+
+import numpy as np
+import pytest
+
+import torch  # noqa: F401  (imported at collection: the first import can take minutes)
+
+import oracle
+from paper_2410_02532_amd import opo as B
+from paper_2410_02532_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+# the per-pass bars of the library: 1e-11 in complex128, 1e-4 in complex64
+TOL = {"f64": 1e-11, "f32": 1e-4}
+
+
+def rel_l2(got, ref):
+    return float(np.linalg.norm(got - ref) / np.linalg.norm(ref))
+
+
+def phase_rounding(cr, nz, dz):
+    """Rounding of the dispersion phase itself, in the oracle and in the library: its largest
+    value per step (third order, at the edge of the band), half a unit each, nz steps."""
+    w = np.pi * cr["nt"] / cr["t_window_ps"]
+    ph = max(abs(b3) * 1e-9 * w ** 3 / 6 + abs(b2) * 1e-6 * w ** 2 / 2
+             for b2, b3 in zip(cr["b2_fs2_per_mm"], cr["b3_fs3_per_mm"]))
+    return nz * ph * dz * 2.0 ** -53
+
+
+def _instance(nt, nf, seed, dk=0.0, n2=0.0):
+    mk = W.crystal if nf == 3 else W.crystal2
+    cr = mk(nt, t_window_ps=40.0, deff=40.0, b3=(300.0, -150.0, 100.0), dk_per_mm=dk,
+            alpha=(0.02, 0.01, 0.03), db1=(0.25, 0.0, -0.15))
+    cr["n2_m2_per_w"] = n2
+    t = W.time_grid(nt, 40.0)
+    a = np.empty((nf, nt), complex)
+    a[0] = 2.0e6 * np.exp(-t * t / (2 * 8.0 ** 2)) * np.exp(0.3j)
+    a[1] = 3.0e5 * np.exp(-(t - 1.0) ** 2 / (2 * 4.0 ** 2)) + W.noise(nt, 1e3, seed + 1)
+    if nf == 3:
+        a[2] = W.noise(nt, 2e4, seed + 2)
+    return dict(crystal=cr, cavity=W.cavity(refl=(0.0, 0.85, 0.0)), fields=a, pump_in=a[0].copy())
+
+
+# (log2 nt, col_log2): columns of 2^4..2^7 points, rows of 2^5 up to the longest
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("l, col, nf, dk, n2", [
+    (10, 0, 3, 0.0, 0.0), (11, 4, 2, 0.0, 0.0), (11, 5, 3, 0.6, 0.0), (12, 4, 3, 0.0, 1e-17), (12, 6, 2, 0.6, 0.0),
+    (13, 5, 3, 0.0, 0.0), (14, 7, 2, 0.0, 1e-17), (14, 4, 3, 0.0, 0.0), (15, 5, 2, 0.0, 0.0), (16, 5, 3, 0.6, 0.0),
+    (17, 6, 3, 0.0, 0.0), (18, 7, 2, 0.0, 0.0), (18, 0, 3, 0.0, 0.0)])
+def test_lone_pass_parity(l, col, nf, dk, n2, precision):
+    print("lone 2^%d col %d nf %d dk %g n2 %g %s" % (l, col, nf, dk, n2, precision), file=sys.stderr, flush=True)
+    ins = _instance(1 << l, nf, l + col, dk, n2)
+    nz, dz = 12, 0.125
+    ref = oracle.ssfm_pass(ins["crystal"], ins["fields"], nz, dz)
+    with B.Opo([ins], nz, precision=precision, col_log2=col) as h:
+        h.ssfm_propagate(nz - 5, dz)
+        h.ssfm_propagate(5, dz)
+        got = h.get_fields()
+    tol = TOL[precision] + phase_rounding(ins["crystal"], nz, dz)
+    for x in range(nf):
+        assert rel_l2(got[x], ref[x]) <= tol, (x, rel_l2(got[x], ref[x]), tol)
+
+
+@pytest.mark.parametrize("precision, count", [("f32", 14), ("f32", 15), ("f64", 8), ("f64", 9)])
+def test_lone_uneven_handle(precision, count):
+    """As many uneven instances as one launch holds, and one more (which runs the mixed
+    launches): round trips match the oracle."""
+    print("lone uneven %s x%d" % (precision, count), file=sys.stderr, flush=True)
+    insts = [_instance(1 << (10 + b % 4), 3, 50 + b, dk=0.3 * (b % 3), n2=1e-17 * (b % 2)) for b in range(count)]
+    nz, nrt = 6, 2
+    with B.Opo(insts, nz, precision=precision) as h:
+        h.cavity_roundtrip(nrt)
+        got = [(h.get_fields(i), h.energy_history(i)) for i in range(count)]
+    for ins, (f, e) in zip(insts, got):
+        ref, en = oracle.roundtrips(ins["crystal"], ins["cavity"], ins["fields"], ins["pump_in"], nz, nrt)
+        for x in range(3):
+            assert rel_l2(f[x], ref[x]) <= TOL[precision], (x, rel_l2(f[x], ref[x]))
+        # |E - E0|/E0 <= 2 eps + eps^2 for a field within eps
+        assert np.max(np.abs(e - en) / en) <= 3 * TOL[precision]
