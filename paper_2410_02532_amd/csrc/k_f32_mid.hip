@@ -1,0 +1,6 @@
+// FP32 interior launches of batches.
+#include "kernel_list.h"
+
+namespace opo {
+OPO_MID_KERNELS_F32(template)
+} // namespace opo

@@ -4,6 +4,7 @@
 // so that the kernel units compile in parallel.
 #pragma once
 #include "lone_kernels.h"
+#include "mid_kernels.h"
 
 // Column and row passes, propagator tables and the adaptive-step kernels of
 // real type R (row range 2, rows of 4096 points, exists in FP32 only).
@@ -67,6 +68,18 @@
     DECL __global__ void lone_row<R, 9>(LoneRowArgs<R>);                                           \
     DECL __global__ void lone_row<R, 12>(LoneRowArgs<R>);
 
+// Interior launches of batches: columns of 2^4..2^6 points, rows of 2^5..2^11, or 2^12 (FP32).
+#define OPO_MID_KERNELS(DECL, R)                                                                   \
+    DECL __global__ void mid_pass<R, 5, 11, 2>(MidArgs<R>);                                        \
+    DECL __global__ void mid_pass<R, 5, 11, 3>(MidArgs<R>);                                        \
+    DECL __global__ void coupling_table<R>(const InstDesc *, int, int, double, double, int, int,   \
+                                           int, Coupling<R> *);
+
+#define OPO_MID_KERNELS_F32(DECL)                                                                  \
+    OPO_MID_KERNELS(DECL, float)                                                                   \
+    DECL __global__ void mid_pass<float, 12, 12, 2>(MidArgs<float>);                               \
+    DECL __global__ void mid_pass<float, 12, 12, 3>(MidArgs<float>);
+
 #define OPO_ALL_KERNELS(DECL)                                                                      \
     OPO_PASS_KERNELS_F32(DECL)                                                                     \
     OPO_PASS_KERNELS_F64(DECL)                                                                     \
@@ -78,4 +91,6 @@
     OPO_MIXED_KERNELS_F64(DECL, 3)                                                                 \
     OPO_LONE_KERNELS(DECL, float)                                                                  \
     OPO_LONE_KERNELS(DECL, double)                                                                 \
+    OPO_MID_KERNELS_F32(DECL)                                                                      \
+    OPO_MID_KERNELS(DECL, double)                                                                  \
     OPO_RESIDENT_KERNELS(DECL)

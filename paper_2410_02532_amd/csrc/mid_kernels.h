@@ -1,0 +1,231 @@
+// mid_kernels.h -- the z-steps of batches that fill the chip, inside a pass.
+//
+// mixed_pass without what only the ends of a pass and the round-trip boundary need.
+// Those launches are bound by VALU issue (73 % of the cycles at 791 lane-instructions
+// per field-point-step on the batched sweep) and, in FP64, by the three workgroups a CU
+// holds at 152 registers. Here the column transforms exchange between the lanes of one
+// wave (no LDS, no barrier), the flags of the boundary, the bounds checks and the FP64
+// coupling phasors are gone (the couplings of every step come from a table), and one
+// map entry names a workgroup's instance and tile (two dependent loads before the
+// fields instead of three): 754 lane-instructions.
+//
+// Measured (MI355X, ms per round trip of the 256-instance sweeps of 2^12..2^16):
+// FP32 18.1 -> 17.8, two waves 14.0 -> 12.7, FP64 37.1 -> 31.9. The FP32 launch (87 us)
+// issues VALU 70 % of its cycles at 2.9 waves per SIMD; five workgroups per CU instead of
+// four changed nothing, about 9 us of it are its ramp and tail.
+#pragma once
+#include "ssfm_kernels.h"
+#include "wave_fft.h"
+
+namespace opo {
+
+struct MidInst {
+    long long off;        // first sample of the instance
+    long long w4_off;     // its four-step twiddle table
+    long long disp_off;   // its propagator table
+    int nt, n1;
+    int log2n1, log2n2;
+    int rows;             // rows of all fields (nf n2), contiguous
+    int kind;             // 0: dk = 0 (couplings i c); 1: general couplings; 2: Kerr terms
+};
+
+// A workgroup's tile: instance (-1: none), and column tile (>= 0) or row tile -1-code.
+struct MidTile {
+    int inst, code;
+};
+
+template <typename R> struct MidArgs {
+    cplx<R> *state;
+    const Phasor<R> *tw, *w4tab, *disp;
+    const int *counter;       // [2] stop flag, see StepArgs
+    const MidInst *inst;
+    const Coupling<R> *coef;  // couplings of this launch's column tiles, per instance
+    const MidTile *map;
+    int flags;                // column tiles: A_INV | A_RK_PREV, A_RK_THIS | A_FWD, or both
+    int disp_sel;             // row tiles: propagator table of this step size (0 or 1)
+};
+
+// ---- column tile: four waves of 64/T columns each (T = N/PF lanes a column)
+constexpr int kMidMinLog2N2 = 4, kMidMaxLog2N2 = 6;
+constexpr int mid_col_pf(int ln2) { return ln2 <= 5 ? 2 : 4; }
+constexpr int mid_cols(int ln2) { return kThreads * mid_col_pf(ln2) >> ln2; }
+
+template <typename R, int LN2, int NF>
+__device__ __forceinline__ void mid_column_tile(const MidArgs<R> &a, const MidInst &d, const Coupling<R> &cp, int tile)
+{
+    using V = cplx<R>;
+    constexpr int N = 1 << LN2, PF = mid_col_pf(LN2), T = N / PF, COLS = 64 / T;
+    constexpr int TW = wave_tw_regs<N, PF>();
+    const int flags = a.flags;
+    const int lane = threadIdx.x & 63, c = lane % COLS, t = lane / COLS;
+    const unsigned n1 = d.n1, nt = d.nt;
+    const unsigned j1 = tile * mid_cols(LN2) + (threadIdx.x >> 6) * COLS + c;
+    const int kind = d.kind;
+    V *g = a.state + d.off;
+    const Phasor<R> *w4t = a.w4tab + d.w4_off;
+    const bool stopped = a.counter[2] != 0;   // see column_tile
+    V v[NF][PF];
+    // register m: row wave_bin(t, m) of the transform where a row pass left it or will
+    // take it, sample t + m T otherwise
+    auto at = [&](bool freq, int m) {
+        return j1 + n1 * (freq ? wave_bin<N, PF>(t, m) : t + m * T);
+    };
+#pragma unroll
+    for (int m = 0; m < PF; ++m) {
+        const unsigned q = at(flags & A_INV, m);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) v[f][m] = el32(g, q + f * nt);
+    }
+    Phasor<R> w[TW];
+    wave_tw_load<R, N, PF, N, 0>(w, t, a.tw);
+    if (flags & A_INV) {
+#pragma unroll
+        for (int m = 0; m < PF; ++m) {
+            const Phasor<R> w4 = el32(w4t, at(true, m));
+#pragma unroll
+            for (int f = 0; f < NF; ++f) v[f][m] = pmul<true>(v[f][m], w4);
+        }
+#pragma unroll
+        for (int f = 0; f < NF; ++f) wave_inv<R, N, PF, N, 0, 32>(v[f], w);
+    }
+#pragma unroll
+    for (int which = 0; which < 2; ++which) {
+        if (!(flags & (which ? A_RK_THIS : A_RK_PREV))) continue;
+#pragma unroll
+        for (int m = 0; m < PF; ++m)
+            rk4_fields<R, NF>(cp, which, kind == 0, kind == 2, v[0][m], v[1][m], v[NF - 1][m]);
+    }
+    if (flags & A_FWD) {
+        // the twiddles again from L1 (the opaque index keeps them from being held across
+        // the RK4: 92 registers instead of 116 in FP32, 164 instead of 188 in FP64)
+        int tz = t;
+        asm volatile("" : "+v"(tz));
+        wave_tw_load<R, N, PF, N, 0>(w, tz, a.tw);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) wave_fwd<R, N, PF, N, 0, 32>(v[f], w);
+#pragma unroll
+        for (int m = 0; m < PF; ++m) {
+            const Phasor<R> w4 = el32(w4t, at(true, m));
+#pragma unroll
+            for (int f = 0; f < NF; ++f) v[f][m] = pmul(v[f][m], w4);
+        }
+    }
+    if (stopped) return;
+#pragma unroll
+    for (int m = 0; m < PF; ++m) {
+        const unsigned q = at(flags & A_FWD, m);
+#pragma unroll
+        for (int f = 0; f < NF; ++f) el32(g, q + f * nt) = v[f][m];
+    }
+}
+
+// ---- row tile: row_rows whole rows
+template <typename R, int LN1>
+__device__ __forceinline__ void mid_row_tile(const MidArgs<R> &a, const MidInst &d, int tile, cplx<R> *s)
+{
+    using V = cplx<R>;
+    constexpr int N = 1 << LN1, PF = row_pf<R>(LN1), ROWS = row_rows<R>(LN1), T = N / PF;
+    constexpr bool WAVE = T <= OPO_ROW_WAVE_MAX;
+    const int r = threadIdx.x / T, t = threadIdx.x % T;
+    const int row = tile * ROWS + r;
+    const bool act = row < d.rows;
+    const unsigned q0 = static_cast<unsigned>(act ? row : 0) * N + t;
+    V *g = a.state + d.off;
+    const bool stopped = a.counter[2] != 0;
+    const Phasor<R> *h = a.disp + d.disp_off + static_cast<long long>(a.disp_sel) * d.rows * N;
+    V v[1][PF];
+#pragma unroll
+    for (int m = 0; m < PF; ++m) v[0][m] = el32(g, q0 + m * T);
+    const int base[1] = {r * N};
+    reg_fft<R, N, PF, 1, -1, 1, 2048, false, WAVE>(v, s, base, t, a.tw);
+#pragma unroll
+    for (int m = 0; m < PF; ++m) v[0][m] = pmul(v[0][m], el32(h, q0 + m * T));
+    reg_fft<R, N, PF, 1, +1, 1, 2048, false, WAVE>(v, s, base, t, a.tw);
+    if (stopped || !act) return;
+#pragma unroll
+    for (int m = 0; m < PF; ++m) el32(g, q0 + m * T) = v[0][m];
+}
+
+template <typename R, int L, int HI>
+__device__ __forceinline__ void mid_row_dispatch(const MidArgs<R> &a, const MidInst &d, int tile, cplx<R> *s)
+{
+    if (d.log2n1 == L) mid_row_tile<R, L>(a, d, tile, s);
+    else if constexpr (L < HI) mid_row_dispatch<R, L + 1, HI>(a, d, tile, s);
+}
+
+// Rows of 2^LO..2^HI points: 5..11, or 12 (FP32).
+#ifndef OPO_MID_MIN_BLOCKS
+#define OPO_MID_MIN_BLOCKS 4
+#endif
+template <typename R, int HI> constexpr int mid_min_blocks() { return sizeof(R) == 4 && HI <= 11 ? OPO_MID_MIN_BLOCKS : 1; }
+
+template <typename R, int LO, int HI, int NF>
+__global__ __launch_bounds__(kThreads, (mid_min_blocks<R, HI>())) void mid_pass(MidArgs<R> a)
+{
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    const MidTile mt = a.map[blockIdx.x];
+    if (mt.inst < 0) return;
+    const MidInst &d = a.inst[mt.inst];
+    if (mt.code >= 0) {
+        const Coupling<R> &cp = a.coef[mt.inst];
+        switch (d.log2n2) {
+        case 4: return mid_column_tile<R, 4, NF>(a, d, cp, mt.code);
+        case 5: return mid_column_tile<R, 5, NF>(a, d, cp, mt.code);
+        default: return mid_column_tile<R, 6, NF>(a, d, cp, mt.code);
+        }
+    }
+    mid_row_dispatch<R, LO, HI>(a, d, -1 - mt.code, reinterpret_cast<cplx<R> *>(lds_raw));
+}
+
+// Triple-jump coefficients of the fourth-order composition: a = 1/(2 - 2^(1/3)),
+// b = 1 - 2a (a + b + a = 1, 2a^3 + b^3 = 0).
+constexpr double kTjA = 1.35120719195965763405;
+constexpr double kTjB = -1.70241438391931526810;
+
+// Step i of a pass in units of dz: start z, size tau, and the propagator table it uses.
+// Symmetrized steps are the steps; the fourth-order composition runs three per step, of
+// a, b and a times dz.
+__host__ __device__ inline void substep(int order, int i, double &z, double &tau, int &sel)
+{
+    if (order != 4) {
+        z = i;
+        tau = 1.0;
+        sel = 0;
+        return;
+    }
+    const int j = i >= 0 ? i / 3 : -1, s = i - 3 * j;
+    z = j + (s == 0 ? 0.0 : s == 1 ? kTjA : kTjA + kTjB);
+    tau = s == 1 ? kTjB : kTjA;
+    sel = s == 1 ? 1 : 0;
+}
+
+// Couplings of the column launches at step boundaries s0 .. s0 + count - 1 of a pass:
+// entry (s - s0) n + i is boundary s of instance i, with the second half-step of step
+// s - 1 and the first of step s, formed as in coupling_tile. Six threads an entry.
+template <typename R>
+__global__ __launch_bounds__(kThreads) void coupling_table(const InstDesc *inst, int n, int order, double dz_arg,
+                                                           double zbase, int nz, int s0, int count, Coupling<R> *out)
+{
+    using V = cplx<R>;
+    const int id = blockIdx.x * kThreads + threadIdx.x, e = id / 6, q = id - 6 * e;
+    if (e >= count * n) return;
+    const int s = s0 + e / n, which = q / 3, st = q - 3 * which;
+    const InstDesc &d = inst[e % n];
+    const double dz = dz_arg > 0.0 ? dz_arg : d.length_mm / nz, zb = dz_arg > 0.0 ? zbase : 0.0;
+    double z, tau;
+    int sel;
+    substep(order, which ? s : s - 1, z, tau, sel);
+    if (!which) z += 0.5 * tau;
+    const double h = 0.5 * tau * dz, hh = 0.5 * h;
+    const double r = d.dk_rev * (zb + z * dz + 0.5 * h * st);
+    double sn, cs;
+    sincospi(2.0 * (r - rint(r)), &sn, &cs);
+    const double kp = d.kappa[0] * hh, ks = d.kappa[1] * hh, ki = d.kappa[2] * hh;
+    V *c = out[e].c[which][st];
+    c[0] = mk<V>(static_cast<R>(kp * sn), static_cast<R>(kp * cs));
+    c[1] = mk<V>(static_cast<R>(-ks * sn), static_cast<R>(ks * cs));
+    c[2] = mk<V>(static_cast<R>(-ki * sn), static_cast<R>(ki * cs));
+    out[e].g[which][st] = static_cast<R>(d.gamma[st] * hh);
+}
+
+} // namespace opo

@@ -44,6 +44,7 @@ static int fail(int code, const std::string &msg)
     } while (0)
 
 static constexpr int kHistChunk = 1024;   // round trips buffered on the device per read-back
+static constexpr int kCoefChunk = 128;    // step boundaries whose couplings are held (mid launches)
 static constexpr double kTwoPi = 6.283185307179586476925286766559;
 static constexpr double kPi = 3.1415926535897932384626433832795;
 
@@ -194,6 +195,17 @@ template <typename R> static const void *mixed_fn(int cr, int rr, int nf)
     return nf == 2 ? mixed_fn_nf<R, 2>(cr, rr) : mixed_fn_nf<R, 3>(cr, rr);
 }
 
+// Interior launches of batches (mid_kernels.h) with rows of range rr.
+template <typename R> static const void *mid_fn(int rr, int nf)
+{
+    if constexpr (kMaxLog2N1<R> >= 12)
+        if (rr == 2)
+            return nf == 2 ? reinterpret_cast<const void *>(&mid_pass<R, 12, 12, 2>)
+                           : reinterpret_cast<const void *>(&mid_pass<R, 12, 12, 3>);
+    return nf == 2 ? reinterpret_cast<const void *>(&mid_pass<R, 5, 11, 2>)
+                   : reinterpret_cast<const void *>(&mid_pass<R, 5, 11, 3>);
+}
+
 // Lone kernels (lone_kernels.h): columns of nf-wave instances, rows of up to 2^ln points.
 template <typename R> static const void *lone_column_fn(int nf)
 {
@@ -248,6 +260,15 @@ struct opo_s {
     bool mixed = false;              // two halves a launch apart, mixed launches
     int *d_map[2] = {nullptr, nullptr};  // workgroup -> tile maps of the two mixed launches
     int map_len[2] = {0, 0};
+    // batches on the automatic schedule: launches inside a pass run mid_pass. Maps of the
+    // mixed launches (column half 0, 1) and of the column tiles of a half alone (2, 3)
+    bool mid = false;
+    int mid_rr = 0, mid_nf = 3;      // row range and coupled waves of its kernel
+    MidInst *d_mid_inst = nullptr;   // per (crystal, instance)
+    MidTile *d_mid_map[4] = {nullptr, nullptr, nullptr, nullptr};
+    int mid_len[4] = {0, 0, 0, 0};
+    void *d_coef = nullptr;          // couplings of kCoefChunk step boundaries, per instance
+    size_t mid_lds = 0;
     int *d_tile_a = nullptr, *d_tile_b = nullptr;
     void *d_tw = nullptr;
     void *d_w4tab = nullptr;         // four-step twiddle tables, one per distinct (nt, n1)
@@ -304,11 +325,6 @@ static bool finite3(const double *v)
 {
     return std::isfinite(v[0]) && std::isfinite(v[1]) && std::isfinite(v[2]);
 }
-
-// Triple-jump coefficients of the fourth-order composition: a = 1/(2 - 2^(1/3)),
-// b = 1 - 2a (a + b + a = 1, 2a^3 + b^3 = 0).
-constexpr double kTjA = 1.35120719195965763405;
-constexpr double kTjB = -1.70241438391931526810;
 
 // Coupled waves of an instance: 3 (pump, signal, idler; n_fields 0 or 3) or 2
 // (pump and degenerate signal).
@@ -512,7 +528,8 @@ static void release(opo_t *h)
         if (st) (void)hipStreamDestroy(st);
     void *bufs[] = {h->d_res_inst, h->d_w4tab, h->pump, h->d_inst, h->d_tile_a, h->d_tile_b, h->d_tw, h->d_disp, h->d_map[0], h->d_map[1],
                     h->d_partial, h->d_hist, h->d_counter, h->spec_buf, h->d_record, h->d_snap,
-                    h->a_uc, h->a_uf, h->a_tab, h->d_actl, h->d_apart};
+                    h->a_uc, h->a_uf, h->a_tab, h->d_actl, h->d_apart, h->d_mid_inst, h->d_coef,
+                    h->d_mid_map[0], h->d_mid_map[1], h->d_mid_map[2], h->d_mid_map[3]};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
     for (hipEvent_t e : h->events)
@@ -541,21 +558,6 @@ template <typename R> static StepArgs<R> base_args(opo_t *h, void *state)
     a.record_cap = h->record_cap;
     a.nz = h->nz;
     return a;
-}
-
-static void substep(const opo_t *h, int i, double &z, double &tau, int &sel)
-{
-    if (h->order != 4) {
-        z = i;
-        tau = 1.0;
-        sel = 0;
-        return;
-    }
-    const int j = i >= 0 ? i / 3 : -1, s = i - 3 * j;
-    const double start[3] = {0.0, kTjA, kTjA + kTjB}, size[3] = {kTjA, kTjB, kTjA};
-    z = j + start[s];
-    tau = size[s];
-    sel = s == 1 ? 1 : 0;
 }
 
 // profile option: open an event pair around the next launch of class k
@@ -601,21 +603,16 @@ static int prof_collect(opo_t *h, size_t used)
     return OPO_OK;
 }
 
-// Step i of a pass in units of dz: start z, size tau, and the propagator
-// table it uses. Symmetrized steps are the steps; the fourth-order
-// composition runs three per step, of a, b and a times dz.
-static void substep(const opo_t *h, int i, double &z, double &tau, int &sel);
-
 // The RK4 half-steps a column launch at step boundary i runs: the second
 // half of step i-1 and the first half of step i.
 template <typename R> static void set_half_steps(const opo_t *h, StepArgs<R> &a, int i)
 {
     double z, tau;
     int sel;
-    substep(h, i - 1, z, tau, sel);
+    substep(h->order, i - 1, z, tau, sel);
     a.zf_prev = z + 0.5 * tau;
     a.hf_prev = 0.5 * tau;
-    substep(h, i, z, tau, sel);
+    substep(h->order, i, z, tau, sel);
     a.zf_this = z;
     a.hf_this = 0.5 * tau;
 }
@@ -649,7 +646,7 @@ static hipError_t launch_b(opo_t *h, StepArgs<R> a, int flags, int step = 0, int
     a.tile_inst = h->d_tile_b;
     a.flags = flags;
     double z, tau;
-    substep(h, step, z, tau, a.disp_sel);
+    substep(h->order, step, z, tau, a.disp_sel);
     if (sel >= 0) a.disp_sel = sel;
     HIP_RET(prof_begin(h, OPO_K_ROW));
     for (int set = 0; set < (all_tiles ? 2 : 1); ++set)
@@ -716,7 +713,7 @@ template <typename R> static hipError_t launch_mixed(opo_t *h, StepArgs<R> a, in
     {
         // the other half is a launch ahead (half 0) or behind (half 1)
         double z, tau;
-        substep(h, ch == 1 ? step : step - 1, z, tau, ar.disp_sel);
+        substep(h->order, ch == 1 ? step : step - 1, z, tau, ar.disp_sel);
     }
     ar.tile0 = gr.tile0;
     ar.tile_count = gr.count;
@@ -724,6 +721,43 @@ template <typename R> static hipError_t launch_mixed(opo_t *h, StepArgs<R> a, in
     HIP_RET(prof_begin(h, OPO_K_MIXED));
     HIP_RET(hipLaunchKernel(mixed_fn<R>(gc.ln, gr.ln, gc.nf), dim3(h->map_len[ch]), dim3(kThreads), args,
                             std::max(h->lds_a, h->lds_b), h->stream));
+    return prof_end(h);
+}
+
+// Flags of a column launch inside a pass (no round-trip boundary).
+static constexpr int kInterior = A_INV | A_RK_PREV | A_RK_THIS | A_FWD;
+
+// Couplings of the step boundaries from s0 on (of crystal `stage`) into d_coef.
+template <typename R> static hipError_t fill_couplings(opo_t *h, const StepArgs<R> &a, int s0, int boundaries)
+{
+    const int count = std::min(kCoefChunk, boundaries - s0);
+    const unsigned blocks = (6u * count * h->n_inst + kThreads - 1) / kThreads;
+    coupling_table<R><<<blocks, kThreads, 0, h->stream>>>(a.inst, h->n_inst, h->order, a.dz_arg, a.zbase, a.nz, s0, count,
+                                                          static_cast<Coupling<R> *>(h->d_coef));
+    return hipGetLastError();
+}
+
+// Launch of map `map` inside a pass: the column tiles of a half (flags, step boundary
+// step) and, for maps 0 and 1, the row tiles of the other half, which is a launch ahead
+// (half 0) or behind (half 1).
+template <typename R> static hipError_t launch_mid(opo_t *h, const StepArgs<R> &a, int map, int flags, int step, int stage)
+{
+    MidArgs<R> m{};
+    m.state = a.state;
+    m.tw = a.tw;
+    m.w4tab = a.w4tab;
+    m.disp = a.disp;
+    m.counter = a.counter;
+    m.inst = h->d_mid_inst + static_cast<size_t>(stage) * h->n_inst;
+    m.coef = static_cast<const Coupling<R> *>(h->d_coef) + static_cast<size_t>(step % kCoefChunk) * h->n_inst;
+    m.map = h->d_mid_map[map];
+    m.flags = flags;
+    double z, tau;
+    substep(h->order, map == 0 ? step - 1 : step, z, tau, m.disp_sel);
+    void *args[] = {&m};
+    HIP_RET(prof_begin(h, map < 2 ? OPO_K_MIXED : OPO_K_COLUMN));
+    HIP_RET(hipLaunchKernel(mid_fn<R>(h->mid_rr, h->mid_nf), dim3(h->mid_len[map]), dim3(kThreads), args, h->mid_lds,
+                            h->stream));
     return prof_end(h);
 }
 
@@ -791,7 +825,7 @@ template <typename R> static hipError_t launch_lone_b(opo_t *h, const StepArgs<R
 {
     double z, tau;
     int sel;
-    substep(h, step, z, tau, sel);
+    substep(h->order, step, z, tau, sel);
     LoneRowArgs<R> la{};
     la.state = a.state;
     la.tw = a.tw;
@@ -820,25 +854,37 @@ static hipError_t enqueue_pass(opo_t *h, StepArgs<R> a, int nz_steps, int first,
     if (h->groups_a.empty()) return hipSuccess;           // every instance is resident
     const int nz = nz_steps * (h->order == 4 ? 3 : 1);   // symmetrized steps of the pass
     if (h->mixed) {
-        // half 0 runs one launch ahead of half 1
-        const int mid = A_INV | A_RK_PREV | A_RK_THIS | A_FWD;
-        HIP_RET(launch_a<R>(h, a, first | A_RK_THIS | A_FWD, 0, 0));
+        // half 0 runs one launch ahead of half 1; a launch with nothing of the
+        // round-trip boundary runs mid_pass where the handle has it
+        int chunk = -1;
+        auto columns = [&](int half, bool rows, int flags, int step) -> hipError_t {
+            if (h->mid && !(flags & ~kInterior)) {
+                if (step / kCoefChunk != chunk) {
+                    chunk = step / kCoefChunk;
+                    HIP_RET(fill_couplings<R>(h, a, chunk * kCoefChunk, nz + 1));
+                }
+                return launch_mid<R>(h, a, rows ? half : 2 + half, flags, step, stage);
+            }
+            return rows ? launch_mixed<R>(h, a, half, flags, step) : launch_a<R>(h, a, flags, step, half);
+        };
+        const int open = first | A_RK_THIS | A_FWD, close = A_INV | A_RK_PREV | last;
+        HIP_RET(columns(0, false, open, 0));
         for (int j = 0; j < nz; ++j) {
-            HIP_RET(launch_mixed<R>(h, a, 1, j == 0 ? (first | A_RK_THIS | A_FWD) : mid, j));      // rows of half 0
-            HIP_RET(launch_mixed<R>(h, a, 0, j + 1 < nz ? mid : (A_INV | A_RK_PREV | last), j + 1));  // rows of half 1
+            HIP_RET(columns(1, true, j == 0 ? open : kInterior, j));               // rows of half 0
+            HIP_RET(columns(0, true, j + 1 < nz ? kInterior : close, j + 1));      // rows of half 1
         }
-        return launch_a<R>(h, a, A_INV | A_RK_PREV | last, nz, 1);
+        return columns(1, false, close, nz);
     }
     // lone instances: every launch but those of the round-trip boundary
     const bool lone = !h->lone.empty();
     auto column = [&](int flags, int step) {
-        return lone && !(flags & ~(A_INV | A_RK_PREV | A_RK_THIS | A_FWD)) ? launch_lone_a<R>(h, a, flags, step, stage)
+        return lone && !(flags & ~kInterior) ? launch_lone_a<R>(h, a, flags, step, stage)
                                                                           : launch_a<R>(h, a, flags, step);
     };
     HIP_RET(column(first | A_RK_THIS | A_FWD, 0));
     for (int j = 0; j < nz; ++j) {
         HIP_RET(lone ? launch_lone_b<R>(h, a, j, stage) : launch_b<R>(h, a, B_DISP, j));
-        HIP_RET(column(j + 1 < nz ? A_INV | A_RK_PREV | A_RK_THIS | A_FWD : A_INV | A_RK_PREV | last, j + 1));
+        HIP_RET(column(j + 1 < nz ? kInterior : A_INV | A_RK_PREV | last, j + 1));
     }
     return hipSuccess;
 }
@@ -904,6 +950,9 @@ template <typename R> static int setup_kernels(opo_t *h)
         HIP_TRY(hipFuncSetAttribute(resident_fn<R>(g.ln, g.nf), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     static_cast<int>(lds_elems<R>(1 << g.ln) * sizeof(cplx<R>))));
     }
+    if (h->mid)
+        HIP_TRY(hipFuncSetAttribute(mid_fn<R>(h->mid_rr, h->mid_nf), hipFuncAttributeMaxDynamicSharedMemorySize,
+                                    static_cast<int>(h->mid_lds)));
     if (!h->lone.empty())
         HIP_TRY(hipFuncSetAttribute(lone_row_fn<R>(h->lone_ln1), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     static_cast<int>(h->lone_lds_b)));
@@ -1162,36 +1211,70 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
     // a batch of 2^16 instances 7 % and the two-wave sweep 6 % faster but the
     // batched sweep 1 % and batches of 2^13..2^15 2-3 % slower; column tiles
     // first was slower on the batched sweep too.
+    // Workgroups of a launch from the tiles each XCD runs, column tiles qc and row tiles qr.
+    constexpr int kXcd = 8;
+    auto interleave = [&](const std::vector<MidTile> (&qc)[kXcd], std::vector<MidTile> (&qr)[kXcd]) {
+        size_t len = 0;
+        for (int x = 0; x < kXcd; ++x) {
+            // longer rows first within each XCD (stable: tile order otherwise)
+            std::stable_sort(qr[x].begin(), qr[x].end(), [&](const MidTile &p, const MidTile &q) {
+                return h->inst[p.inst].log2n1 > h->inst[q.inst].log2n1;
+            });
+            len = std::max(len, qc[x].size() + qr[x].size());
+        }
+        std::vector<MidTile> map(len * kXcd, MidTile{-1, 0});
+        for (int x = 0; x < kXcd; ++x) {
+            const long long nc = static_cast<long long>(qc[x].size());
+            const long long tot = nc + static_cast<long long>(qr[x].size());
+            for (long long q = 0; q < tot; ++q) {
+                const long long before = q * nc / tot;
+                const bool col = (q + 1) * nc / tot > before;
+                map[q * kXcd + x] = col ? qc[x][before] : qr[x][q - before];
+            }
+        }
+        return map;
+    };
     std::vector<int> maps[2];
     if (h->mixed) {
-        constexpr int kXcd = 8;
         for (int ch = 0; ch < 2; ++ch) {
             const Group &gc = h->groups_a[ch], &gr = h->groups_b[1 - ch];
-            std::vector<int> qc[kXcd], qr[kXcd];
-            for (int t = 0; t < gc.count; ++t) qc[t % kXcd].push_back(gc.tile0 + t);
+            std::vector<MidTile> qc[kXcd], qr[kXcd];
+            for (int t = 0; t < gc.count; ++t) qc[t % kXcd].push_back({tile_a_inst[gc.tile0 + t], gc.tile0 + t});
             for (int t = 0; t < gr.count; ++t) {
-                const int tile = gr.tile0 + t;
-                const int local = tile - h->inst[tile_b_inst[tile]].tile_b0;
-                qr[local % kXcd].push_back(tile);
+                const int tile = gr.tile0 + t, i = tile_b_inst[tile];
+                qr[(tile - h->inst[i].tile_b0) % kXcd].push_back({i, -1 - tile});
             }
-            // longer rows first within each XCD (stable: tile order otherwise)
-            for (int x = 0; x < kXcd; ++x)
-                std::stable_sort(qr[x].begin(), qr[x].end(), [&](int p, int q) {
-                    return h->inst[tile_b_inst[p]].log2n1 > h->inst[tile_b_inst[q]].log2n1;
-                });
-            size_t len = 0;
-            for (int x = 0; x < kXcd; ++x) len = std::max(len, qc[x].size() + qr[x].size());
-            maps[ch].assign(len * kXcd, kNoTile);
-            for (int x = 0; x < kXcd; ++x) {
-                const long long nc = static_cast<long long>(qc[x].size());
-                const long long tot = nc + static_cast<long long>(qr[x].size());
-                for (long long q = 0; q < tot; ++q) {
-                    const long long before = q * nc / tot;
-                    const bool col = (q + 1) * nc / tot > before;
-                    maps[ch][q * kXcd + x] = col ? qc[x][before] : -1 - qr[x][q - before];
+            for (const MidTile &m : interleave(qc, qr)) maps[ch].push_back(m.inst < 0 ? kNoTile : m.code);
+            h->map_len[ch] = static_cast<int>(maps[ch].size());
+        }
+    }
+    // mid_pass serves the launches inside a pass of a mixed batch on the automatic
+    // schedule whose columns fit a wave's registers (2^4..2^6 points)
+    std::vector<MidTile> mid_maps[4];
+    if (h->mixed && opt.schedule == 0 && h->groups_a[0].ln == 0 && h->groups_a[1].ln == 0 &&
+        h->groups_a[0].nf == h->groups_a[1].nf && (h->groups_b[0].ln == 2) == (h->groups_b[1].ln == 2)) {
+        const bool f64 = opt.precision == OPO_F64;
+        h->mid = batched;
+        for (int i : order)
+            h->mid = h->mid && h->inst[i].log2n2 >= kMidMinLog2N2 && h->inst[i].log2n1 >= 5;
+        h->mid_rr = h->groups_b[0].ln;
+        h->mid_nf = h->groups_a[0].nf;
+        for (int ch = 0; h->mid && ch < 2; ++ch) {
+            std::vector<MidTile> qc[kXcd], qr[kXcd], none[kXcd];
+            int nc = 0;
+            for (int i : order) {
+                const InstDesc &d = h->inst[i];
+                const int rows = f64 ? row_rows<double>(d.log2n1) : row_rows<float>(d.log2n1);
+                h->mid_lds = std::max(h->mid_lds, (f64 ? lds_elems<double>(rows << d.log2n1)
+                                                       : lds_elems<float>(rows << d.log2n1)) * h->elem);
+                if (half[i] == ch) {
+                    for (int t = 0; t < d.n1 / mid_cols(d.log2n2); ++t) qc[nc++ % kXcd].push_back({i, t});
+                } else {
+                    for (int t = 0; t < (d.nf * d.n2 + rows - 1) / rows; ++t) qr[t % kXcd].push_back({i, -1 - t});
                 }
             }
-            h->map_len[ch] = static_cast<int>(maps[ch].size());
+            mid_maps[ch] = interleave(qc, qr);
+            mid_maps[2 + ch] = interleave(qc, none);
         }
     }
 
@@ -1268,6 +1351,20 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
                       hipMalloc(reinterpret_cast<void **>(&h->d_map[1]), maps[1].size() * sizeof(int)) != hipSuccess)))
         return bail(fail(OPO_ENOMEM, "hipMalloc of the tables failed"));
 
+    std::vector<MidInst> mid_inst;
+    if (h->mid) {
+        for (const InstDesc &d : h->inst)
+            mid_inst.push_back({d.off, d.w4_off, d.disp_off, d.nt, d.n1, d.log2n1, d.log2n2, d.nf * d.n2,
+                                d.kerr ? 2 : d.dk_rev == 0.0 ? 0 : 1});
+        const size_t cb = opt.precision == OPO_F64 ? sizeof(Coupling<double>) : sizeof(Coupling<float>);
+        bool ok = hipMalloc(reinterpret_cast<void **>(&h->d_mid_inst), mid_inst.size() * sizeof(MidInst)) == hipSuccess &&
+                  hipMalloc(&h->d_coef, kCoefChunk * cb * n) == hipSuccess;
+        for (int q = 0; q < 4; ++q) {
+            h->mid_len[q] = static_cast<int>(mid_maps[q].size());
+            ok = ok && hipMalloc(reinterpret_cast<void **>(&h->d_mid_map[q]), mid_maps[q].size() * sizeof(MidTile)) == hipSuccess;
+        }
+        if (!ok) return bail(fail(OPO_ENOMEM, "hipMalloc of the batch tables failed"));
+    }
     if (!res_inst.empty()) {
         if (hipMalloc(reinterpret_cast<void **>(&h->d_res_inst), res_inst.size() * sizeof(int)) != hipSuccess)
             return bail(fail(OPO_ENOMEM, "hipMalloc of the resident instance list failed"));
@@ -1308,6 +1405,15 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
                                              hipMemcpyHostToDevice, st) != hipSuccess) ||
         hipStreamSynchronize(st) != hipSuccess)
         return bail(fail(OPO_EDEVICE, "upload of the instance tables failed"));
+    if (h->mid) {
+        bool ok = hipMemcpyAsync(h->d_mid_inst, mid_inst.data(), mid_inst.size() * sizeof(MidInst), hipMemcpyHostToDevice,
+                                 st) == hipSuccess;
+        for (int q = 0; q < 4; ++q)
+            ok = ok && hipMemcpyAsync(h->d_mid_map[q], mid_maps[q].data(), mid_maps[q].size() * sizeof(MidTile),
+                                      hipMemcpyHostToDevice, st) == hipSuccess;
+        if (!ok || hipStreamSynchronize(st) != hipSuccess)
+            return bail(fail(OPO_EDEVICE, "upload of the batch tables failed"));
+    }
     if ((opt.precision == OPO_F64 ? upload_phasors<double>(h->d_tw, twre, twim, st)
                                   : upload_phasors<float>(h->d_tw, twre, twim, st)) != hipSuccess)
         return bail(fail(OPO_EDEVICE, "upload of the FFT twiddles failed"));

@@ -1,0 +1,67 @@
+"""Batches that fill the chip, on the automatic schedule: the launches inside a pass run
+mid_pass (wave-level columns of 2^4..2^6 points, rows of 2^5 up to the longest, couplings
+from a table refilled every 128 step boundaries). Members against the FP64 oracle."""
+import sys
+
+import numpy as np
+import pytest
+
+import torch  # noqa: F401  (imported at collection: the first import can take minutes)
+
+import oracle
+from paper_2410_02532_amd import opo as B
+from test_gpu_lone import TOL, _instance, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+def _batch(sizes, nf, dk, n2):
+    return [_instance(1 << l, nf, 70 + b, dk=dk * (b % 3), n2=n2 * (b % 2)) for b, l in enumerate(sizes)]
+
+
+CASES = [
+    ("f32", 3, [16, 13, 14, 15] * 3, 0.0, 0.0, 2),
+    ("f32", 3, [16, 16, 15, 14, 14, 13], 0.4, 1e-17, 2),
+    ("f32", 2, [16, 15, 14, 13] * 5, 0.0, 0.0, 4),
+    ("f32", 3, [18, 18, 18], 0.4, 0.0, 2),
+    ("f64", 3, [16, 13, 14, 15, 12] * 3, 0.4, 1e-17, 2),
+    ("f64", 2, [17, 16, 15, 13] * 3, 0.0, 0.0, 4),
+]
+
+
+@pytest.mark.parametrize("precision, nf, sizes, dk, n2, order", CASES)
+def test_batch_round_trips(precision, nf, sizes, dk, n2, order):
+    """Two round trips of every member; the first and last sizes' members are checked."""
+    print("batch %s nf %d %s order %d" % (precision, nf, sizes, order), file=sys.stderr, flush=True)
+    insts = _batch(sizes, nf, dk, n2)
+    nz, nrt = 5, 2
+    with B.Opo(insts, nz, precision=precision, split_order=order) as h:
+        h.cavity_roundtrip(nrt)
+        got = [h.get_fields(i) for i in range(len(insts))]
+    for i in sorted({sizes.index(l) for l in sizes} | {len(sizes) - 1}):
+        ins = insts[i]
+        ref, _ = oracle.roundtrips(dict(ins["crystal"], order=order), ins["cavity"], ins["fields"], ins["pump_in"],
+                                   nz, nrt)
+        for x in range(nf):
+            assert rel_l2(got[i][x], ref[x]) <= TOL[precision], (i, x, rel_l2(got[i][x], ref[x]))
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+def test_batch_pass_over_the_coupling_chunk(precision):
+    """More steps than the coupling table holds, with mismatch; two calls equal one bit for
+    bit (the second call's table starts elsewhere)."""
+    print("batch chunk %s" % precision, file=sys.stderr, flush=True)
+    insts = _batch([14] * 22 + [13], 3, 0.4, 0.0)
+    nz, dz = 140, 2.0 ** -5      # z of every step is exact, so both splits form the same phases
+    out = []
+    for calls in ((nz,), (131, 9)):
+        with B.Opo(insts, nz, precision=precision) as h:
+            for n in calls:
+                h.ssfm_propagate(n, dz)
+            out.append([h.get_fields(i) for i in (0, 1, 22)])
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+    for i, a in zip((1, 22), out[0][1:]):
+        ref = oracle.ssfm_pass(insts[i]["crystal"], insts[i]["fields"], nz, dz)
+        for x in range(3):
+            assert rel_l2(a[x], ref[x]) <= TOL[precision], (i, x, rel_l2(a[x], ref[x]))
