@@ -146,10 +146,10 @@ typedef struct {
                                complex samples in all: batch entries) or not
                                (one instance or a few), chosen by timing the
                                candidates on MI355X. A handle that does not fill
-                               the chip and has few instances (up to 14 in FP32, 8
-                               in FP64, of 2^10 points or more and one field count)
-                               runs two passes through kernels of its own, made
-                               for latency. One shape in one kind of handle always
+                               the chip and has few instances (up to 48, of 2^10
+                               points or more and one field count) runs two
+                               passes through kernels of its own, made for
+                               latency. One shape in one kind of handle always
                                gets the same schedule; an instance alone and the
                                same instance in a larger handle may differ in
                                rounding;

@@ -1,0 +1,6 @@
+// FP64 passes of small instances in one launch.
+#include "kernel_list.h"
+
+namespace opo {
+OPO_TEAM_KERNELS(template, double)
+} // namespace opo

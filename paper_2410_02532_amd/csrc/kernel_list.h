@@ -4,6 +4,7 @@
 // so that the kernel units compile in parallel.
 #pragma once
 #include "lone_kernels.h"
+#include "team_kernels.h"
 #include "mid_kernels.h"
 
 // Column and row passes, propagator tables and the adaptive-step kernels of
@@ -68,6 +69,11 @@
     DECL __global__ void lone_row<R, 9>(LoneRowArgs<R>);                                           \
     DECL __global__ void lone_row<R, 12>(LoneRowArgs<R>);
 
+// All interior steps of small instances in one launch.
+#define OPO_TEAM_KERNELS(DECL, R)                                                                  \
+    DECL __global__ void team_pass<R, 2>(TeamArgs<R>);                                             \
+    DECL __global__ void team_pass<R, 3>(TeamArgs<R>);
+
 // Interior launches of batches: columns of 2^4..2^6 points, rows of 2^5..2^11, or 2^12 (FP32).
 #define OPO_MID_KERNELS(DECL, R)                                                                   \
     DECL __global__ void mid_pass<R, 5, 11, 2>(MidArgs<R>);                                        \
@@ -91,6 +97,8 @@
     OPO_MIXED_KERNELS_F64(DECL, 3)                                                                 \
     OPO_LONE_KERNELS(DECL, float)                                                                  \
     OPO_LONE_KERNELS(DECL, double)                                                                 \
+    OPO_TEAM_KERNELS(DECL, float)                                                                  \
+    OPO_TEAM_KERNELS(DECL, double)                                                                 \
     OPO_MID_KERNELS_F32(DECL)                                                                      \
     OPO_MID_KERNELS(DECL, double)                                                                  \
     OPO_RESIDENT_KERNELS(DECL)

@@ -6,8 +6,8 @@
 // throughput. In the general column tile that chain was the tile's instance, its
 // descriptor, the fields, then the four-step twiddles, the FP64 coupling phasors, and
 // one twiddle load after every barrier of the transforms. Here everything a tile needs
-// is issued at its start: descriptors and coupling coefficients (formed on the host in
-// FP64) come with the kernel arguments, and the fields, four-step twiddles, propagator
+// is issued at its start: descriptors come with the kernel arguments, coupling
+// coefficients from a table, and the fields, four-step twiddles, propagator
 // and the butterfly twiddles of every stage are loaded into registers together (one
 // wave per SIMD has 512; nothing spills). A column tile is one wave that exchanges
 // between its lanes in registers; a row tile is one row, whose exchanges alternate
@@ -19,30 +19,28 @@
 // exchanges of the columns through LDS (256 threads, a barrier each) the 2^14 instance
 // took 9.5: a radix-2 stage then lasted about 590 cycles, four fifths of them waiting.
 #pragma once
-#include "ssfm_kernels.h"
+#include "coupling_table.h"
+#include "schedule.h"
 #include "wave_fft.h"
 
 namespace opo {
 
-// Instances of one launch: what fits the 4 KB of kernel arguments.
-template <typename R> constexpr int kLoneMax = sizeof(R) == 4 ? 14 : 8;
-
-template <typename R> struct LoneColumnInst {
+struct LoneColumnInst {
     long long off;        // first sample of the instance
     long long w4_off;     // its four-step twiddle table
     int n1, nt;
     int log2n2;
-    int kind;             // 0: dk = 0 (couplings i ci); 1: general couplings; 2: Kerr terms
-    R ci[2][3];           // kind 0: the couplings of both half-steps, beside the fields read first
-    Coupling<R> cp;       // [0] second half of the step before, [1] first half of this step
+    int kind;             // see half_step
+    int index;            // instance (couplings)
 };
 
 template <typename R> struct LoneColumnArgs {
     cplx<R> *state;
     const Phasor<R> *tw, *w4tab;
     const int *counter;   // [2] stop flag, see StepArgs
+    const Coupling<R> *coef;   // couplings of this launch, per instance
     int flags;            // A_INV | A_RK_PREV, A_RK_THIS | A_FWD, or both
-    LoneColumnInst<R> inst[kLoneMax<R>];
+    LoneColumnInst inst[kLoneMax];
 };
 
 struct LoneRowInst {
@@ -56,11 +54,8 @@ template <typename R> struct LoneRowArgs {
     cplx<R> *state;
     const Phasor<R> *tw, *disp;
     const int *counter;
-    LoneRowInst inst[kLoneMax<R>];
+    LoneRowInst inst[kLoneMax];
 };
-
-static_assert(sizeof(LoneColumnArgs<float>) <= 4096 && sizeof(LoneColumnArgs<double>) <= 4096 &&
-              sizeof(LoneRowArgs<float>) <= 4096, "kernel arguments of the lone kernels");
 
 // ---- FFT on preloaded twiddles
 template <int N, int PF, int P = 1> __host__ __device__ constexpr int tw_regs()
@@ -146,13 +141,40 @@ template <int N, int PF, int P = 1> __host__ __device__ constexpr int fft_exchan
 }
 
 // ---- column tile: one wave, 64/T columns with T = N/PF lanes each
-constexpr int kLoneMinLog2 = 10;         // smallest instance
 constexpr int kLoneMinLog2N2 = 4, kLoneMaxLog2N2 = 7;
 constexpr int lone_col_pf(int ln2) { return ln2 <= 5 ? 2 : ln2 == 6 ? 4 : 8; }
 constexpr int lone_cols(int ln2) { return 64 * lone_col_pf(ln2) >> ln2; }
 
+// What a column tile computes, from its samples and four-step and stage twiddles.
+// (flags stay a run-time value in every kernel, so that all of them run, and round in,
+// the same instructions.)
+template <typename R, int N, int PF, int NF, int TW>
+__device__ __forceinline__ void lone_column_math(cplx<R> (&v)[NF][PF], const Phasor<R> (&w4)[PF],
+                                                 const Phasor<R> (&w)[TW], int kind, const ImagCoupling<R> &imag,
+                                                 const Coupling<R> *coef, int flags)
+{
+    if (flags & A_INV) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+#pragma unroll
+            for (int m = 0; m < PF; ++m) v[f][m] = pmul<true>(v[f][m], w4[m]);
+            wave_inv<R, N, PF, N, 0, 32>(v[f], w);
+        }
+    }
+    if (flags & A_RK_PREV) half_step<R, NF, PF>(v, kind, imag, coef, 0);
+    if (flags & A_RK_THIS) half_step<R, NF, PF>(v, kind, imag, coef, 1);
+    if (flags & A_FWD) {
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            wave_fwd<R, N, PF, N, 0, 32>(v[f], w);
+#pragma unroll
+            for (int m = 0; m < PF; ++m) v[f][m] = pmul(v[f][m], w4[m]);
+        }
+    }
+}
+
 template <typename R, int LN2, int NF>
-__device__ __forceinline__ void lone_column_tile(const LoneColumnArgs<R> &a, const LoneColumnInst<R> &d)
+__device__ __forceinline__ void lone_column_tile(const LoneColumnArgs<R> &a, const LoneColumnInst &d)
 {
     using V = cplx<R>;
     constexpr int N = 1 << LN2, PF = lone_col_pf(LN2), T = N / PF, COLS = 64 / T;
@@ -165,11 +187,7 @@ __device__ __forceinline__ void lone_column_tile(const LoneColumnArgs<R> &a, con
     // the cache lines of their columns, go to the same one
     const unsigned tile = tiles >= 8 ? (blockIdx.x & 7) * (tiles >> 3) + (blockIdx.x >> 3) : blockIdx.x;
     const int kind = d.kind;
-    R ci[2][3];
-#pragma unroll
-    for (int which = 0; which < 2; ++which)
-#pragma unroll
-        for (int x = 0; x < 3; ++x) ci[which][x] = d.ci[which][x];
+    const Coupling<R> *coef = a.coef + d.index;
     V *g = a.state + d.off;
     const Phasor<R> *w4t = a.w4tab + d.w4_off;
     V v[NF][PF];
@@ -191,40 +209,8 @@ __device__ __forceinline__ void lone_column_tile(const LoneColumnArgs<R> &a, con
     for (int m = 0; m < PF; ++m) w4[m] = el32(w4t, flags & A_FWD ? qo[m] : q[m]);
     wave_tw_load<R, N, PF, N, 0>(w, t, a.tw);
     const bool stopped = a.counter[2] != 0;   // see column_tile
-    if (flags & A_INV) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-#pragma unroll
-            for (int m = 0; m < PF; ++m) v[f][m] = pmul<true>(v[f][m], w4[m]);
-            wave_inv<R, N, PF, N, 0, 32>(v[f], w);
-        }
-    }
-#pragma unroll
-    for (int which = 0; which < 2; ++which) {
-        if (!(flags & (which ? A_RK_THIS : A_RK_PREV))) continue;
-        if (kind == 0) {
-            V k[3][3];
-#pragma unroll
-            for (int x = 0; x < 3; ++x) k[0][x] = mk<V>(R(0), ci[which][x]);
-#pragma unroll
-            for (int m = 0; m < PF; ++m) {
-                if constexpr (NF == 3) rk4_point_imag<R>(k, v[0][m], v[1][m], v[NF - 1][m]);
-                else rk4_point2_imag<R>(k, v[0][m], v[1][m]);
-            }
-        } else {
-#pragma unroll
-            for (int m = 0; m < PF; ++m)
-                rk4_fields<R, NF>(d.cp, which, false, kind == 2, v[0][m], v[1][m], v[NF - 1][m]);
-        }
-    }
-    if (flags & A_FWD) {
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-            wave_fwd<R, N, PF, N, 0, 32>(v[f], w);
-#pragma unroll
-            for (int m = 0; m < PF; ++m) v[f][m] = pmul(v[f][m], w4[m]);
-        }
-    }
+    const ImagCoupling<R> imag(coef);
+    lone_column_math<R, N, PF, NF>(v, w4, w, kind, imag, coef, flags);
     if (stopped) return;
 #pragma unroll
     for (int f = 0; f < NF; ++f)
@@ -234,7 +220,7 @@ __device__ __forceinline__ void lone_column_tile(const LoneColumnArgs<R> &a, con
 
 template <typename R, int NF> __global__ __launch_bounds__(64) void lone_column(LoneColumnArgs<R> a)
 {
-    const LoneColumnInst<R> &d = a.inst[blockIdx.y];
+    const LoneColumnInst &d = a.inst[blockIdx.y];
     switch (d.log2n2) {
     case 4: return lone_column_tile<R, 4, NF>(a, d);
     case 5: return lone_column_tile<R, 5, NF>(a, d);

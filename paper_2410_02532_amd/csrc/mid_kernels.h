@@ -14,7 +14,7 @@
 // issues VALU 70 % of its cycles at 2.9 waves per SIMD; five workgroups per CU instead of
 // four changed nothing, about 9 us of it are its ramp and tail.
 #pragma once
-#include "ssfm_kernels.h"
+#include "coupling_table.h"
 #include "wave_fft.h"
 
 namespace opo {
@@ -175,57 +175,6 @@ __global__ __launch_bounds__(kThreads, (mid_min_blocks<R, HI>())) void mid_pass(
         }
     }
     mid_row_dispatch<R, LO, HI>(a, d, -1 - mt.code, reinterpret_cast<cplx<R> *>(lds_raw));
-}
-
-// Triple-jump coefficients of the fourth-order composition: a = 1/(2 - 2^(1/3)),
-// b = 1 - 2a (a + b + a = 1, 2a^3 + b^3 = 0).
-constexpr double kTjA = 1.35120719195965763405;
-constexpr double kTjB = -1.70241438391931526810;
-
-// Step i of a pass in units of dz: start z, size tau, and the propagator table it uses.
-// Symmetrized steps are the steps; the fourth-order composition runs three per step, of
-// a, b and a times dz.
-__host__ __device__ inline void substep(int order, int i, double &z, double &tau, int &sel)
-{
-    if (order != 4) {
-        z = i;
-        tau = 1.0;
-        sel = 0;
-        return;
-    }
-    const int j = i >= 0 ? i / 3 : -1, s = i - 3 * j;
-    z = j + (s == 0 ? 0.0 : s == 1 ? kTjA : kTjA + kTjB);
-    tau = s == 1 ? kTjB : kTjA;
-    sel = s == 1 ? 1 : 0;
-}
-
-// Couplings of the column launches at step boundaries s0 .. s0 + count - 1 of a pass:
-// entry (s - s0) n + i is boundary s of instance i, with the second half-step of step
-// s - 1 and the first of step s, formed as in coupling_tile. Six threads an entry.
-template <typename R>
-__global__ __launch_bounds__(kThreads) void coupling_table(const InstDesc *inst, int n, int order, double dz_arg,
-                                                           double zbase, int nz, int s0, int count, Coupling<R> *out)
-{
-    using V = cplx<R>;
-    const int id = blockIdx.x * kThreads + threadIdx.x, e = id / 6, q = id - 6 * e;
-    if (e >= count * n) return;
-    const int s = s0 + e / n, which = q / 3, st = q - 3 * which;
-    const InstDesc &d = inst[e % n];
-    const double dz = dz_arg > 0.0 ? dz_arg : d.length_mm / nz, zb = dz_arg > 0.0 ? zbase : 0.0;
-    double z, tau;
-    int sel;
-    substep(order, which ? s : s - 1, z, tau, sel);
-    if (!which) z += 0.5 * tau;
-    const double h = 0.5 * tau * dz, hh = 0.5 * h;
-    const double r = d.dk_rev * (zb + z * dz + 0.5 * h * st);
-    double sn, cs;
-    sincospi(2.0 * (r - rint(r)), &sn, &cs);
-    const double kp = d.kappa[0] * hh, ks = d.kappa[1] * hh, ki = d.kappa[2] * hh;
-    V *c = out[e].c[which][st];
-    c[0] = mk<V>(static_cast<R>(kp * sn), static_cast<R>(kp * cs));
-    c[1] = mk<V>(static_cast<R>(-ks * sn), static_cast<R>(ks * cs));
-    c[2] = mk<V>(static_cast<R>(-ki * sn), static_cast<R>(ki * cs));
-    out[e].g[which][st] = static_cast<R>(d.gamma[st] * hh);
 }
 
 } // namespace opo

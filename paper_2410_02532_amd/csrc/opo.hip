@@ -206,6 +206,11 @@ template <typename R> static const void *mid_fn(int rr, int nf)
                    : reinterpret_cast<const void *>(&mid_pass<R, 5, 11, 3>);
 }
 
+template <typename R> static const void *team_fn(int nf)
+{
+    return nf == 2 ? reinterpret_cast<const void *>(&team_pass<R, 2>) : reinterpret_cast<const void *>(&team_pass<R, 3>);
+}
+
 // Lone kernels (lone_kernels.h): columns of nf-wave instances, rows of up to 2^ln points.
 template <typename R> static const void *lone_column_fn(int nf)
 {
@@ -255,6 +260,8 @@ struct opo_s {
     // and their launches' grids, LDS and longest row
     std::vector<int> lone;
     unsigned lone_tiles_a = 0, lone_tiles_b = 0;
+    bool team = false;               // ... or team_pass (team_kernels.h)
+    TeamSync *d_team = nullptr;
     size_t lone_lds_b = 0;
     int lone_nf = 3, lone_ln1 = 0, lone_threads_b = 64;
     bool mixed = false;              // two halves a launch apart, mixed launches
@@ -278,7 +285,8 @@ struct opo_s {
     double *d_partial = nullptr;
     double *d_hist = nullptr;
     int *d_counter = nullptr;        // [0] history slot in the chunk, [1] round trips completed,
-                                     // [2] stop flag, [3] non-finite boundary value (ssfm_kernels.h)
+                                     // [2] stop flag, [3] non-finite boundary value (ssfm_kernels.h),
+                                     // [4] a wait of team_pass gave up
     void *d_snap = nullptr;          // state at the start of the current round trip
     void *d_record = nullptr;        // [record_cap][state] fields leaving the crystal per round trip
     int record_cap = 0;
@@ -528,7 +536,7 @@ static void release(opo_t *h)
         if (st) (void)hipStreamDestroy(st);
     void *bufs[] = {h->d_res_inst, h->d_w4tab, h->pump, h->d_inst, h->d_tile_a, h->d_tile_b, h->d_tw, h->d_disp, h->d_map[0], h->d_map[1],
                     h->d_partial, h->d_hist, h->d_counter, h->spec_buf, h->d_record, h->d_snap,
-                    h->a_uc, h->a_uf, h->a_tab, h->d_actl, h->d_apart, h->d_mid_inst, h->d_coef,
+                    h->a_uc, h->a_uf, h->a_tab, h->d_actl, h->d_apart, h->d_team, h->d_mid_inst, h->d_coef,
                     h->d_mid_map[0], h->d_mid_map[1], h->d_mid_map[2], h->d_mid_map[3]};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
@@ -730,7 +738,7 @@ static constexpr int kInterior = A_INV | A_RK_PREV | A_RK_THIS | A_FWD;
 // Couplings of the step boundaries from s0 on (of crystal `stage`) into d_coef.
 template <typename R> static hipError_t fill_couplings(opo_t *h, const StepArgs<R> &a, int s0, int boundaries)
 {
-    const int count = std::min(kCoefChunk, boundaries - s0);
+    const int count = std::min(kCoefChunk + 1, boundaries - s0);
     const unsigned blocks = (6u * count * h->n_inst + kThreads - 1) / kThreads;
     coupling_table<R><<<blocks, kThreads, 0, h->stream>>>(a.inst, h->n_inst, h->order, a.dz_arg, a.zbase, a.nz, s0, count,
                                                           static_cast<Coupling<R> *>(h->d_coef));
@@ -761,57 +769,22 @@ template <typename R> static hipError_t launch_mid(opo_t *h, const StepArgs<R> &
     return prof_end(h);
 }
 
-// Coupling coefficients of the RK4 half-steps of a column launch, as coupling_tile
-// forms them: h/2 times kappa and the phasor of dk z at z0, z0 + h/2, z0 + h.
+// Column launch of the lone instances in crystal `stage` (flags: the half-steps and
+// transforms on either side of a step boundary, whose couplings are row `row` of d_coef).
 template <typename R>
-static void coupling_host(const InstDesc &d, double z_prev, double h_prev, double z_this, double h_this,
-                          Coupling<R> &out)
+static hipError_t launch_lone_a(opo_t *h, const StepArgs<R> &a, int flags, int row, int stage)
 {
-    using V = cplx<R>;
-    for (int which = 0; which < 2; ++which)
-        for (int st = 0; st < 3; ++st) {
-            const double h = which ? h_this : h_prev;
-            const double r = d.dk_rev * ((which ? z_this : z_prev) + 0.5 * h * st);
-            const double ph = kTwoPi * (r - std::rint(r)), sn = std::sin(ph), cs = std::cos(ph);
-            const double hh = 0.5 * h, kp = d.kappa[0] * hh, ks = d.kappa[1] * hh, ki = d.kappa[2] * hh;
-            V *c = out.c[which][st];
-            c[0].x = static_cast<R>(kp * sn);
-            c[0].y = static_cast<R>(kp * cs);
-            c[1].x = static_cast<R>(-ks * sn);
-            c[1].y = static_cast<R>(ks * cs);
-            c[2].x = static_cast<R>(-ki * sn);
-            c[2].y = static_cast<R>(ki * cs);
-            out.g[which][st] = static_cast<R>(d.gamma[st] * hh);
-        }
-}
-
-// Column launch of the lone instances at step boundary `step` of crystal `stage`
-// (flags: the half-steps and transforms on either side of the boundary).
-template <typename R>
-static hipError_t launch_lone_a(opo_t *h, const StepArgs<R> &a, int flags, int step, int stage)
-{
-    StepArgs<R> hs = a;
-    set_half_steps<R>(h, hs, step);
     LoneColumnArgs<R> la{};
     la.state = a.state;
     la.tw = a.tw;
     la.w4tab = a.w4tab;
     la.counter = a.counter;
+    la.coef = static_cast<const Coupling<R> *>(h->d_coef) + static_cast<size_t>(row) * h->n_inst;
     la.flags = flags;
     const InstDesc *inst = h->inst.data() + static_cast<size_t>(stage) * h->n_inst;
     for (size_t q = 0; q < h->lone.size(); ++q) {
         const InstDesc &d = inst[h->lone[q]];
-        const double dz = a.dz_arg > 0.0 ? a.dz_arg : d.length_mm / a.nz, zb = a.dz_arg > 0.0 ? a.zbase : 0.0;
-        LoneColumnInst<R> &e = la.inst[q];
-        e.off = d.off;
-        e.w4_off = d.w4_off;
-        e.n1 = d.n1;
-        e.nt = d.nt;
-        e.log2n2 = d.log2n2;
-        e.kind = d.kerr ? 2 : d.dk_rev == 0.0 ? 0 : 1;
-        coupling_host<R>(d, zb + hs.zf_prev * dz, hs.hf_prev * dz, zb + hs.zf_this * dz, hs.hf_this * dz, e.cp);
-        for (int which = 0; which < 2; ++which)
-            for (int x = 0; x < 3; ++x) e.ci[which][x] = e.cp.c[which][0][x].y;
+        la.inst[q] = {d.off, d.w4_off, d.n1, d.nt, d.log2n2, d.kerr ? 2 : d.dk_rev == 0.0 ? 0 : 1, h->lone[q]};
     }
     void *args[] = {&la};
     HIP_RET(prof_begin(h, OPO_K_COLUMN));
@@ -846,6 +819,43 @@ template <typename R> static hipError_t launch_lone_b(opo_t *h, const StepArgs<R
     return prof_end(h);
 }
 
+// Phases begin .. end - 1 of the team instances (TeamArgs) from step s0 on, in one launch.
+template <typename R>
+static hipError_t launch_team(opo_t *h, const StepArgs<R> &a, int s0, int begin, int end, int open, int close, int stage)
+{
+    TeamArgs<R> t{};
+    t.state = a.state;
+    t.tw = a.tw;
+    t.w4tab = a.w4tab;
+    t.disp = a.disp;
+    t.counter = a.counter;
+    t.coef = static_cast<const Coupling<R> *>(h->d_coef);
+    t.sync = h->d_team;
+    t.failed = h->d_counter + 4;
+    t.n = h->n_inst;
+    t.count = static_cast<int>(h->lone.size());
+    t.begin = begin;
+    t.end = end;
+    t.open = open;
+    t.close = close;
+    t.s0 = s0;
+    t.order = h->order;
+    const InstDesc *inst = h->inst.data() + static_cast<size_t>(stage) * h->n_inst;
+    for (size_t q = 0; q < h->lone.size(); ++q) {
+        const InstDesc &d = inst[h->lone[q]];
+        const int rows = d.nf * d.n2, per = team_rows(d.log2n1);
+        t.inst[q] = {d.off, d.w4_off, d.disp_off, d.nt, d.n1, d.log2n1, d.log2n2, rows,
+                     d.kerr ? 2 : d.dk_rev == 0.0 ? 0 : 1, h->lone[q],
+                     std::min(kTeamMax, std::max(d.n1 / lone_cols(d.log2n2), (rows + per - 1) / per))};
+    }
+    team_init<<<1, kThreads, 0, h->stream>>>(h->d_team, t.count);
+    HIP_RET(hipGetLastError());
+    void *args[] = {&t};
+    HIP_RET(prof_begin(h, OPO_K_MIXED));
+    HIP_RET(hipLaunchKernel(team_fn<R>(h->lone_nf), dim3(8 * kTeamMax), dim3(64), args, 0, h->stream));
+    return prof_end(h);
+}
+
 // One crystal pass of nz steps through crystal `stage`. `first` flags are OR-ed into
 // the opening column pass (refresh), `last` into the closing one (energy, mirror, EOM).
 template <typename R>
@@ -877,10 +887,27 @@ static hipError_t enqueue_pass(opo_t *h, StepArgs<R> a, int nz_steps, int first,
     }
     // lone instances: every launch but those of the round-trip boundary
     const bool lone = !h->lone.empty();
-    auto column = [&](int flags, int step) {
-        return lone && !(flags & ~kInterior) ? launch_lone_a<R>(h, a, flags, step, stage)
-                                                                          : launch_a<R>(h, a, flags, step);
+    int held = -1;   // chunk of the coupling table
+    auto column = [&](int flags, int step) -> hipError_t {
+        if (!lone || (flags & ~kInterior)) return launch_a<R>(h, a, flags, step);
+        if (held < 0 || step < held || step > held + kCoefChunk) {
+            held = step - step % kCoefChunk;
+            HIP_RET(fill_couplings<R>(h, a, held, nz + 1));
+        }
+        return launch_lone_a<R>(h, a, flags, step - held, stage);
     };
+    if (h->team) {
+        // the boundary's launches only where there is something of the boundary to do
+        if (first) HIP_RET(launch_a<R>(h, a, first | A_RK_THIS | A_FWD, 0));
+        for (int s0 = 0; s0 < nz; s0 += kCoefChunk) {
+            const int s1 = std::min(nz, s0 + kCoefChunk), steps = s1 - s0;
+            HIP_RET(fill_couplings<R>(h, a, s0, nz + 1));
+            const bool open = s0 == 0 && !first, close = s1 == nz && !last;
+            HIP_RET(launch_team<R>(h, a, s0, open ? 0 : 1, s1 == nz && last ? 2 * steps : 2 * steps + 1, open ? 0 : -1,
+                                   close ? 2 * steps : -1, stage));
+        }
+        return last ? launch_a<R>(h, a, A_INV | A_RK_PREV | last, nz) : hipSuccess;
+    }
     HIP_RET(column(first | A_RK_THIS | A_FWD, 0));
     for (int j = 0; j < nz; ++j) {
         HIP_RET(lone ? launch_lone_b<R>(h, a, j, stage) : launch_b<R>(h, a, B_DISP, j));
@@ -1035,12 +1062,15 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
     long long total_points = 0;
     for (int i = 0; i < n; ++i) total_points += static_cast<long long>(nfields(f[i])) * f[i].nt;
     const bool batched = total_points >= kBatchPoints;
+    bool few = opt.schedule == 0 && !batched && n <= kLoneMax && opt.col_log2 <= kLoneMaxLog2N2;
+    for (int i = 0; i < n; ++i) few = few && nfields(f[i]) == nfields(f[0]) && ilog2(f[i].nt) >= kLoneMinLog2;
     for (int i = 0; i < n; ++i) {
         InstDesc &d = h->inst[i];
         // schedule: the table's entry for this shape (schedule 0), or two-pass
         // (1) / resident where served (2); an explicit col_log2 sets the split
         const int l2 = ilog2(f[i].nt);
-        const Schedule sc = opt.schedule == 0 ? schedule_lookup(opt.precision == OPO_F64, nfields(f[i]), l2, batched)
+        const Schedule sc = few ? Schedule{lone_split(opt.precision == OPO_F64, nfields(f[i]), l2), 0}
+                            : opt.schedule == 0 ? schedule_lookup(opt.precision == OPO_F64, nfields(f[i]), l2, batched)
                                               : Schedule{0, opt.schedule == 2 ? 1 : 0};
         const Plan p = make_plan(f[i].nt, opt.precision, opt.col_log2 != 0 ? opt.col_log2 : sc.col_log2);
         fill_desc(d, f[i], c[i * K], k[i], p);
@@ -1087,22 +1117,23 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
     std::vector<int> order;
     for (int i = 0; i < n; ++i)
         if (!h->inst[i].resident) order.push_back(i);
-    // a handle too small to fill the chip, on the automatic schedule: its two-pass
-    // instances run the lone kernels if one launch holds them
-    if (opt.schedule == 0 && !batched && !order.empty()) {
+    // a handle of few instances, too small to fill the chip, on the automatic schedule:
+    // the lone kernels, or the team kernels where they serve every shape
+    if (few) {
         const bool f64 = opt.precision == OPO_F64;
-        bool ok = static_cast<int>(order.size()) <= (f64 ? kLoneMax<double> : kLoneMax<float>);
-        h->lone_nf = h->inst[order[0]].nf;
+        h->lone = order;
+        h->lone_nf = h->inst[0].nf;
+        h->team = prop.multiProcessorCount == 256;
         for (int i : order) {
             const InstDesc &d = h->inst[i];
-            ok = ok && d.nf == h->lone_nf && d.log2nt >= kLoneMinLog2 && d.log2n2 >= kLoneMinLog2N2 && d.log2n2 <= kLoneMaxLog2N2 &&
-                 d.log2n1 >= kLoneMinLog2N1;
+            if (d.log2n2 < kLoneMinLog2N2 || d.log2n2 > kLoneMaxLog2N2 || d.log2n1 < kLoneMinLog2N1)
+                return bail(fail(OPO_EINVAL, "internal: no lone kernel for this split"));
             h->lone_tiles_a = std::max<unsigned>(h->lone_tiles_a, d.n1 / lone_cols(d.log2n2));
             h->lone_threads_b = std::max(h->lone_threads_b, lone_row_threads(d.log2n1));
             h->lone_ln1 = std::max(h->lone_ln1, d.log2n1);
+            h->team = h->team && team_shape(d.log2n2, d.log2n1, d.nf);
         }
-        if (ok) h->lone = order;
-        for (int i : h->lone) {
+        for (int i : order) {
             const InstDesc &d = h->inst[i];
             const unsigned rows = h->lone_threads_b / lone_row_threads(d.log2n1);
             const int pts = h->lone_threads_b * lone_row_pf(d.log2n1);
@@ -1346,11 +1377,18 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
         hipMalloc(reinterpret_cast<void **>(&h->d_partial), h->tiles_a * 3 * sizeof(double)) != hipSuccess ||
         hipMalloc(reinterpret_cast<void **>(&h->d_hist),
                   static_cast<size_t>(kHistChunk) * n * 3 * sizeof(double)) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void **>(&h->d_counter), 4 * sizeof(int)) != hipSuccess ||
+        hipMalloc(reinterpret_cast<void **>(&h->d_counter), 8 * sizeof(int)) != hipSuccess ||
         (h->mixed && (hipMalloc(reinterpret_cast<void **>(&h->d_map[0]), maps[0].size() * sizeof(int)) != hipSuccess ||
                       hipMalloc(reinterpret_cast<void **>(&h->d_map[1]), maps[1].size() * sizeof(int)) != hipSuccess)))
         return bail(fail(OPO_ENOMEM, "hipMalloc of the tables failed"));
 
+    if (!h->lone.empty()) {
+        const size_t cb = opt.precision == OPO_F64 ? sizeof(Coupling<double>) : sizeof(Coupling<float>);
+        if ((h->team &&
+             hipMalloc(reinterpret_cast<void **>(&h->d_team), sizeof(TeamSync) * h->lone.size()) != hipSuccess) ||
+            hipMalloc(&h->d_coef, (kCoefChunk + 1) * cb * n) != hipSuccess)
+            return bail(fail(OPO_ENOMEM, "hipMalloc of the lone instances' tables failed"));
+    }
     std::vector<MidInst> mid_inst;
     if (h->mid) {
         for (const InstDesc &d : h->inst)
@@ -1358,7 +1396,7 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
                                 d.kerr ? 2 : d.dk_rev == 0.0 ? 0 : 1});
         const size_t cb = opt.precision == OPO_F64 ? sizeof(Coupling<double>) : sizeof(Coupling<float>);
         bool ok = hipMalloc(reinterpret_cast<void **>(&h->d_mid_inst), mid_inst.size() * sizeof(MidInst)) == hipSuccess &&
-                  hipMalloc(&h->d_coef, kCoefChunk * cb * n) == hipSuccess;
+                  hipMalloc(&h->d_coef, (kCoefChunk + 1) * cb * n) == hipSuccess;
         for (int q = 0; q < 4; ++q) {
             h->mid_len[q] = static_cast<int>(mid_maps[q].size());
             ok = ok && hipMalloc(reinterpret_cast<void **>(&h->d_mid_map[q]), mid_maps[q].size() * sizeof(MidTile)) == hipSuccess;
@@ -1709,7 +1747,7 @@ template <typename R> static int roundtrip_impl(opo_t *h, int n_rt)
     }
     int done = 0;
     std::vector<double> chunk;
-    int ctr[4] = {0, 0, 0, 0};
+    int ctr[5] = {0, 0, 0, 0, 0};
     while (done < n_rt) {
         const int m = std::min(kHistChunk, n_rt - done);
         set_counter<<<1, 1, 0, h->stream>>>(h->d_counter, 0, -1, 0);
@@ -1730,6 +1768,7 @@ template <typename R> static int roundtrip_impl(opo_t *h, int n_rt)
                                hipMemcpyDeviceToHost, h->stream));
         HIP_TRY(hipMemcpyAsync(ctr, h->d_counter, sizeof(ctr), hipMemcpyDeviceToHost, h->stream));
         HIP_TRY(hipStreamSynchronize(h->stream));
+        if (ctr[4] != 0) return fail(OPO_EDEVICE, "a wait of the pass kernel gave up");
         const int rows = std::min(ctr[0], m);   // finite round trips of this chunk
         h->hist.insert(h->hist.end(), chunk.begin(), chunk.begin() + static_cast<size_t>(rows) * h->n_inst * 3);
         h->hist_rows += rows;

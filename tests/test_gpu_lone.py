@@ -1,5 +1,5 @@
 """Handles too small to fill the chip, on the automatic schedule: their z-steps run the
-wave-level column kernels and the preloaded row kernels. Every split those serve, both
+wave-level column kernels and the preloaded row kernels, or the one-launch pass. Every split those serve, both
 precisions, two and three waves and the three kinds of nonlinear step against the FP64
 oracle; uneven instances of one launch, at the most instances a launch holds."""
 import sys
@@ -51,7 +51,10 @@ def _instance(nt, nf, seed, dk=0.0, n2=0.0):
 @pytest.mark.parametrize("l, col, nf, dk, n2", [
     (10, 0, 3, 0.0, 0.0), (11, 4, 2, 0.0, 0.0), (11, 5, 3, 0.6, 0.0), (12, 4, 3, 0.0, 1e-17), (12, 6, 2, 0.6, 0.0),
     (13, 5, 3, 0.0, 0.0), (14, 7, 2, 0.0, 1e-17), (14, 4, 3, 0.0, 0.0), (15, 5, 2, 0.0, 0.0), (16, 5, 3, 0.6, 0.0),
-    (17, 6, 3, 0.0, 0.0), (18, 7, 2, 0.0, 0.0), (18, 0, 3, 0.0, 0.0)])
+    (17, 6, 3, 0.0, 0.0), (18, 7, 2, 0.0, 0.0), (18, 0, 3, 0.0, 0.0),
+    # shapes of the one-launch pass: columns of 2^5 with rows of 2^5..2^9, 2^6 with 2^9 (two waves)
+    (10, 5, 2, 0.6, 0.0), (11, 5, 2, 0.0, 1e-17), (12, 5, 3, 0.6, 0.0), (13, 5, 2, 0.6, 1e-17), (14, 5, 3, 0.0, 0.0),
+    (14, 5, 2, 0.6, 0.0), (15, 6, 2, 0.0, 1e-17), (15, 6, 3, 0.6, 0.0)])
 def test_lone_pass_parity(l, col, nf, dk, n2, precision):
     print("lone 2^%d col %d nf %d dk %g n2 %g %s" % (l, col, nf, dk, n2, precision), file=sys.stderr, flush=True)
     ins = _instance(1 << l, nf, l + col, dk, n2)
@@ -66,10 +69,10 @@ def test_lone_pass_parity(l, col, nf, dk, n2, precision):
         assert rel_l2(got[x], ref[x]) <= tol, (x, rel_l2(got[x], ref[x]), tol)
 
 
-@pytest.mark.parametrize("precision, count", [("f32", 14), ("f32", 15), ("f64", 8), ("f64", 9)])
+@pytest.mark.parametrize("precision, count", [("f32", 14), ("f32", 48), ("f32", 49), ("f64", 48), ("f64", 49)])
 def test_lone_uneven_handle(precision, count):
-    """As many uneven instances as one launch holds, and one more (which runs the mixed
-    launches): round trips match the oracle."""
+    """Uneven instances, up to as many as one launch holds, and one more (which runs the
+    mixed launches and resident passes): round trips match the oracle."""
     print("lone uneven %s x%d" % (precision, count), file=sys.stderr, flush=True)
     insts = [_instance(1 << (10 + b % 4), 3, 50 + b, dk=0.3 * (b % 3), n2=1e-17 * (b % 2)) for b in range(count)]
     nz, nrt = 6, 2
@@ -82,3 +85,31 @@ def test_lone_uneven_handle(precision, count):
             assert rel_l2(f[x], ref[x]) <= TOL[precision], (x, rel_l2(f[x], ref[x]))
         # |E - E0|/E0 <= 2 eps + eps^2 for a field within eps
         assert np.max(np.abs(e - en) / en) <= 3 * TOL[precision]
+
+
+@pytest.mark.parametrize("precision, nf, order, dk", [("f32", 3, 2, 0.4), ("f64", 3, 4, 0.0), ("f64", 2, 2, 0.4),
+                                                      ("f32", 2, 4, 0.4)])
+def test_lone_long_pass(precision, nf, order, dk):
+    """More step boundaries than the coupling table holds (128), alone and as crystals of a
+    round trip: against the oracle, two calls equal to one bit for bit, and graph replay
+    (three times) equal to plain launches."""
+    print("lone long %s nf %d order %d" % (precision, nf, order), file=sys.stderr, flush=True)
+    ins = _instance(1 << 11, nf, 7, dk=dk)
+    nz, dz = 140, 2.0 ** -5          # dyadic: z of every step is exact in both splits
+    ref = oracle.ssfm_pass(dict(ins["crystal"], order=order), ins["fields"], nz, dz)
+    out = []
+    for calls in ((nz,), (130, 10)):
+        with B.Opo([ins], nz, precision=precision, split_order=order) as h:
+            for n in calls:
+                h.ssfm_propagate(n, dz)
+            out.append(h.get_fields())
+    assert np.array_equal(*out)
+    for x in range(nf):
+        assert rel_l2(out[0][x], ref[x]) <= TOL[precision], (x, rel_l2(out[0][x], ref[x]))
+    runs = []
+    for graph in (True, False):
+        with B.Opo([ins], 131, precision=precision, split_order=order, use_graph=graph) as h:
+            for _ in range(3):
+                h.cavity_roundtrip(1)
+            runs.append((h.get_fields(), h.energy_history()))
+    assert np.array_equal(runs[0][0], runs[1][0]) and np.array_equal(runs[0][1], runs[1][1])
