@@ -1062,16 +1062,21 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
     long long total_points = 0;
     for (int i = 0; i < n; ++i) total_points += static_cast<long long>(nfields(f[i])) * f[i].nt;
     const bool batched = total_points >= kBatchPoints;
-    bool few = opt.schedule == 0 && !batched && n <= kLoneMax && opt.col_log2 <= kLoneMaxLog2N2;
-    for (int i = 0; i < n; ++i) few = few && nfields(f[i]) == nfields(f[0]) && ilog2(f[i].nt) >= kLoneMinLog2;
+    bool few = opt.schedule == 0 && !batched && n <= kLoneMax && opt.col_log2 <= kLoneMaxLog2N2, one_nf = true;
+    for (int i = 0; i < n; ++i) {
+        one_nf = one_nf && nfields(f[i]) == nfields(f[0]);
+        few = few && one_nf && ilog2(f[i].nt) >= kLoneMinLog2;
+    }
     for (int i = 0; i < n; ++i) {
         InstDesc &d = h->inst[i];
         // schedule: the table's entry for this shape (schedule 0), or two-pass
         // (1) / resident where served (2); an explicit col_log2 sets the split
         const int l2 = ilog2(f[i].nt);
-        const Schedule sc = few ? Schedule{lone_split(opt.precision == OPO_F64, nfields(f[i]), l2), 0}
-                            : opt.schedule == 0 ? schedule_lookup(opt.precision == OPO_F64, nfields(f[i]), l2, batched)
-                                              : Schedule{0, opt.schedule == 2 ? 1 : 0};
+        const bool f64 = opt.precision == OPO_F64;
+        Schedule sc{0, opt.schedule == 2 ? 1 : 0};
+        if (few) sc = Schedule{lone_split(f64, nfields(f[i]), l2), 0};
+        else if (opt.schedule == 0) sc = schedule_lookup(f64, nfields(f[i]), l2, batched);
+        if (opt.schedule == 0 && batched && one_nf) sc.col_log2 = batch_split(f64, nfields(f[i]), l2, sc.col_log2);
         const Plan p = make_plan(f[i].nt, opt.precision, opt.col_log2 != 0 ? opt.col_log2 : sc.col_log2);
         fill_desc(d, f[i], c[i * K], k[i], p);
         // resident passes: shapes resident_pass serves, second-order steps, one crystal
