@@ -40,6 +40,7 @@ template <typename R> struct LoneColumnArgs {
     const int *counter;   // [2] stop flag, see StepArgs
     const Coupling<R> *coef;   // couplings of this launch, per instance
     int flags;            // A_INV | A_RK_PREV, A_RK_THIS | A_FWD, or both
+    int spread;           // see lone_col_pf
     LoneColumnInst inst[kLoneMax];
 };
 
@@ -142,8 +143,15 @@ template <int N, int PF, int P = 1> __host__ __device__ constexpr int fft_exchan
 
 // ---- column tile: one wave, 64/T columns with T = N/PF lanes each
 constexpr int kLoneMinLog2N2 = 4, kLoneMaxLog2N2 = 7;
-constexpr int lone_col_pf(int ln2) { return ln2 <= 5 ? 2 : ln2 == 6 ? 4 : 8; }
-constexpr int lone_cols(int ln2) { return 64 * lone_col_pf(ln2) >> ln2; }
+// Samples per thread: 2 (radix 2) up to columns of 2^5, and for columns of 2^6 while
+// the launch then has at most one wave per SIMD of the chip (`spread`): the RK4 of two
+// points instead of four is 1700 cycles less to wait for than the three more radix-2
+// stages (one 2^16 instance 12.1 -> 11.5 us a z-step, FP64 14.6 -> 13.8); with more waves
+// the extra stages cost more (rows of 2^12, 2048 waves, 22.5 -> 23.0; five 2^16 instances
+// in FP64 31.7 -> 35.4).
+constexpr int kLoneSpreadWaves = 1024;
+constexpr int lone_col_pf(int ln2, bool spread) { return ln2 <= 5 ? 2 : ln2 == 6 ? (spread ? 2 : 4) : 8; }
+constexpr int lone_cols(int ln2, bool spread) { return 64 * lone_col_pf(ln2, spread) >> ln2; }
 
 // What a column tile computes, from its samples and four-step and stage twiddles.
 // (flags stay a run-time value in every kernel, so that all of them run, and round in,
@@ -173,11 +181,11 @@ __device__ __forceinline__ void lone_column_math(cplx<R> (&v)[NF][PF], const Pha
     }
 }
 
-template <typename R, int LN2, int NF>
+template <typename R, int LN2, int NF, int PF>
 __device__ __forceinline__ void lone_column_tile(const LoneColumnArgs<R> &a, const LoneColumnInst &d)
 {
     using V = cplx<R>;
-    constexpr int N = 1 << LN2, PF = lone_col_pf(LN2), T = N / PF, COLS = 64 / T;
+    constexpr int N = 1 << LN2, T = N / PF, COLS = 64 / T;
     constexpr int TW = wave_tw_regs<N, PF>();
     const int flags = a.flags;
     const int c = threadIdx.x % COLS, t = threadIdx.x / COLS;
@@ -222,10 +230,10 @@ template <typename R, int NF> __global__ __launch_bounds__(64) void lone_column(
 {
     const LoneColumnInst &d = a.inst[blockIdx.y];
     switch (d.log2n2) {
-    case 4: return lone_column_tile<R, 4, NF>(a, d);
-    case 5: return lone_column_tile<R, 5, NF>(a, d);
-    case 6: return lone_column_tile<R, 6, NF>(a, d);
-    default: return lone_column_tile<R, 7, NF>(a, d);
+    case 4: return lone_column_tile<R, 4, NF, 2>(a, d);
+    case 5: return lone_column_tile<R, 5, NF, 2>(a, d);
+    case 6: return a.spread ? lone_column_tile<R, 6, NF, 2>(a, d) : lone_column_tile<R, 6, NF, 4>(a, d);
+    default: return lone_column_tile<R, 7, NF, 8>(a, d);
     }
 }
 
@@ -234,7 +242,10 @@ template <typename R, int NF> __global__ __launch_bounds__(64) void lone_column(
 // propagator and twiddles, 26 KB at 512 points) are bound by the CU's L1, so fewer
 // rows per CU are faster as long as CUs are idle.
 constexpr int kLoneMinLog2N1 = 5;
-constexpr int lone_row_pf(int ln1) { return ln1 <= 7 ? 4 : ln1 == 12 ? 16 : 8; }
+// 1024 points take 4 samples and 256 threads (five radix-4 stages) instead of 8 and 128:
+// one 2^16 instance 12.4 -> 12.1 us a z-step; 4096 points 8 and 512 threads instead of 16
+// (radix 16) and 256: one 2^18 instance 23.7 -> 22.5. 2048 points with 4 were no faster.
+constexpr int lone_row_pf(int ln1) { return ln1 <= 7 || ln1 == 10 ? 4 : 8; }
 constexpr int lone_row_threads(int ln1) { return (1 << ln1) / lone_row_pf(ln1); }
 
 template <typename R, int LN1>
@@ -272,7 +283,7 @@ __device__ __forceinline__ void lone_row_tile(const LoneRowArgs<R> &a, const Lon
 
 // Rows of 2^5..2^HI points: HI = 9, or 12 (the longer rows hold more samples and
 // twiddles per thread, one wave per SIMD).
-template <typename R, int HI> __global__ __launch_bounds__(kThreads) void lone_row(LoneRowArgs<R> a)
+template <typename R, int HI> __global__ __launch_bounds__(HI > 9 ? 512 : 256) void lone_row(LoneRowArgs<R> a)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     cplx<R> *s = reinterpret_cast<cplx<R> *>(lds_raw);

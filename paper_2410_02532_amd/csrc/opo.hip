@@ -260,6 +260,7 @@ struct opo_s {
     // and their launches' grids, LDS and longest row
     std::vector<int> lone;
     unsigned lone_tiles_a = 0, lone_tiles_b = 0;
+    bool lone_spread = false;        // see lone_col_pf
     bool team = false;               // ... or team_pass (team_kernels.h)
     TeamSync *d_team = nullptr;
     size_t lone_lds_b = 0;
@@ -781,6 +782,7 @@ static hipError_t launch_lone_a(opo_t *h, const StepArgs<R> &a, int flags, int r
     la.counter = a.counter;
     la.coef = static_cast<const Coupling<R> *>(h->d_coef) + static_cast<size_t>(row) * h->n_inst;
     la.flags = flags;
+    la.spread = h->lone_spread;
     const InstDesc *inst = h->inst.data() + static_cast<size_t>(stage) * h->n_inst;
     for (size_t q = 0; q < h->lone.size(); ++q) {
         const InstDesc &d = inst[h->lone[q]];
@@ -846,7 +848,7 @@ static hipError_t launch_team(opo_t *h, const StepArgs<R> &a, int s0, int begin,
         const int rows = d.nf * d.n2, per = team_rows(d.log2n1);
         t.inst[q] = {d.off, d.w4_off, d.disp_off, d.nt, d.n1, d.log2n1, d.log2n2, rows,
                      d.kerr ? 2 : d.dk_rev == 0.0 ? 0 : 1, h->lone[q],
-                     std::min(kTeamMax, std::max(d.n1 / lone_cols(d.log2n2), (rows + per - 1) / per))};
+                     std::min(kTeamMax, std::max(d.n1 / kTeamCols, (rows + per - 1) / per))};
     }
     team_init<<<1, kThreads, 0, h->stream>>>(h->d_team, t.count);
     HIP_RET(hipGetLastError());
@@ -1074,7 +1076,7 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
         const int l2 = ilog2(f[i].nt);
         const bool f64 = opt.precision == OPO_F64;
         Schedule sc{0, opt.schedule == 2 ? 1 : 0};
-        if (few) sc = Schedule{lone_split(f64, nfields(f[i]), l2), 0};
+        if (few) sc = Schedule{lone_split(l2), 0};
         else if (opt.schedule == 0) sc = schedule_lookup(f64, nfields(f[i]), l2, batched);
         if (opt.schedule == 0 && batched && one_nf) sc.col_log2 = batch_split(f64, nfields(f[i]), l2, sc.col_log2);
         const Plan p = make_plan(f[i].nt, opt.precision, opt.col_log2 != 0 ? opt.col_log2 : sc.col_log2);
@@ -1129,11 +1131,14 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
         h->lone = order;
         h->lone_nf = h->inst[0].nf;
         h->team = prop.multiProcessorCount == 256;
+        long long waves = 0;
+        for (int i : order) waves += h->inst[i].n1 / lone_cols(h->inst[i].log2n2, true);
+        h->lone_spread = waves <= kLoneSpreadWaves;
         for (int i : order) {
             const InstDesc &d = h->inst[i];
             if (d.log2n2 < kLoneMinLog2N2 || d.log2n2 > kLoneMaxLog2N2 || d.log2n1 < kLoneMinLog2N1)
                 return bail(fail(OPO_EINVAL, "internal: no lone kernel for this split"));
-            h->lone_tiles_a = std::max<unsigned>(h->lone_tiles_a, d.n1 / lone_cols(d.log2n2));
+            h->lone_tiles_a = std::max<unsigned>(h->lone_tiles_a, d.n1 / lone_cols(d.log2n2, h->lone_spread));
             h->lone_threads_b = std::max(h->lone_threads_b, lone_row_threads(d.log2n1));
             h->lone_ln1 = std::max(h->lone_ln1, d.log2n1);
             h->team = h->team && team_shape(d.log2n2, d.log2n1, d.nf);

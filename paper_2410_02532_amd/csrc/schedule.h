@@ -46,19 +46,12 @@ inline Schedule schedule_lookup(bool f64, int nf, int log2nt, bool batched)
 // Handles that do not fill the chip, of at most kLoneMax instances of 2^10 points or more
 // and one field count, run the lone and team kernels: column splits (log2 n2, 0 = default)
 // by the time of one instance alone. Columns of 2^5 up to 2^14 points serve the team
-// kernels (us per z-step, FP32, three waves, lone kernels: 2^12 6.9 with 2^5, 7.5 with 2^4
-// and 2^6; 2^14 8.2 to 8.3 with 2^5 and 2^6, 9.0 with 2^4); at 2^15 two waves fit a team
-// with columns of 2^6; above, the longer columns of 2^6 (2^16: 11.9 against 12.5 with
-// 2^5, two waves 11.4 against 10.7), and of 2^7 for two waves of 2^18 (18.8 against 20.0).
+// kernels; above, the default's of 2^6 are the fastest (2^16, us per z-step, FP32: 11.5
+// against 13.3 with 2^5 and 15.9 with 2^7; FP64 13.8, 14.6, 17.4).
 constexpr int kLoneMinLog2 = 10;
 constexpr int kLoneMax = 48;   // instances: their descriptors are kernel arguments
 
-inline int lone_split(bool f64, int nf, int log2nt)
-{
-    if (log2nt <= 15) return nf == 2 && log2nt == 15 ? 6 : 5;
-    if (log2nt == 16) return nf == 2 ? 5 : 6;
-    return log2nt == 18 && nf == 2 && !f64 ? 7 : 0;
-}
+inline int lone_split(int log2nt) { return log2nt <= 14 ? 5 : 0; }
 
 // Two-pass instances of a batch of one field count, FP64: the splits by mid_pass's times
 // (batches of 2^22 points, us per z-step; the table's entries are by mixed_pass's).

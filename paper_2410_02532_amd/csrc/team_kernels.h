@@ -45,6 +45,7 @@ constexpr bool team_shape(int log2n2, int log2n1, int nf)
 {
     return (log2n2 == 5 && log2n1 >= 5 && log2n1 <= 9) || (log2n2 == 6 && log2n1 == 9 && nf == 2);
 }
+constexpr int kTeamCols = 4;              // columns per wave: 2^5 points on 16 lanes of 2, 2^6 of 4
 constexpr int team_row_pf(int ln1) { return ln1 <= 8 ? 4 : 8; }
 constexpr int team_rows(int ln1) { return 64 * team_row_pf(ln1) >> ln1; }   // rows per wave
 
@@ -130,7 +131,7 @@ __device__ __forceinline__ void team_run(const TeamArgs<R> &a, const TeamInst &d
 {
     using V = cplx<R>;
     // columns: as lone_column_tile
-    constexpr int CN = 1 << LN2, CPF = lone_col_pf(LN2), CT = CN / CPF, COLS = 64 / CT;
+    constexpr int CN = 1 << LN2, CPF = LN2 == 6 ? 4 : 2, CT = CN / CPF, COLS = 64 / CT;
     // rows: whole rows, RT lanes each
     constexpr int RN = 1 << LN1, RPF = team_row_pf(LN1), RT = RN / RPF, ROWS = 64 / RT;
     constexpr int CTW = wave_tw_regs<CN, CPF>(), RTW = tw_regs<RN, RPF>(), X = fft_exchanges<RN, RPF>();

@@ -21,6 +21,13 @@ template <int D> __device__ __forceinline__ void lane_swap32(unsigned &a, unsign
                                : __builtin_amdgcn_permlane16_swap(a, b, false, false);
         a = r[0];
         b = r[1];
+    } else if constexpr (D == 2) {
+        // within quads: lanes 2, 3 take lanes 0, 1 of b, lanes 0, 1 take lanes 2, 3 of a
+        const bool hi = (threadIdx.x & 2) != 0;
+        const unsigned fb = __builtin_amdgcn_mov_dpp(b, 0x44, 0xf, 0xf, false);   // quad_perm 0 1 0 1
+        const unsigned fa = __builtin_amdgcn_mov_dpp(a, 0xee, 0xf, 0xf, false);   // quad_perm 2 3 2 3
+        a = hi ? fb : a;
+        b = hi ? b : fa;
     } else {
         static_assert(D == 8 || D == 4, "lane distance");
         constexpr int shr = 0x110 + D, shl = 0x100 + D;                 // row_shr:D, row_shl:D

@@ -51,7 +51,7 @@ def _instance(nt, nf, seed, dk=0.0, n2=0.0):
 @pytest.mark.parametrize("l, col, nf, dk, n2", [
     (10, 0, 3, 0.0, 0.0), (11, 4, 2, 0.0, 0.0), (11, 5, 3, 0.6, 0.0), (12, 4, 3, 0.0, 1e-17), (12, 6, 2, 0.6, 0.0),
     (13, 5, 3, 0.0, 0.0), (14, 7, 2, 0.0, 1e-17), (14, 4, 3, 0.0, 0.0), (15, 5, 2, 0.0, 0.0), (16, 5, 3, 0.6, 0.0),
-    (17, 6, 3, 0.0, 0.0), (18, 7, 2, 0.0, 0.0), (18, 0, 3, 0.0, 0.0),
+    (16, 6, 3, 0.6, 0.0), (16, 6, 2, 0.0, 0.0), (17, 6, 3, 0.0, 0.0), (18, 7, 2, 0.0, 0.0), (18, 0, 3, 0.0, 0.0),
     # shapes of the one-launch pass: columns of 2^5 with rows of 2^5..2^9, 2^6 with 2^9 (two waves)
     (10, 5, 2, 0.6, 0.0), (11, 5, 2, 0.0, 1e-17), (12, 5, 3, 0.6, 0.0), (13, 5, 2, 0.6, 1e-17), (14, 5, 3, 0.0, 0.0),
     (14, 5, 2, 0.6, 0.0), (15, 6, 2, 0.0, 1e-17), (15, 6, 3, 0.6, 0.0)])
