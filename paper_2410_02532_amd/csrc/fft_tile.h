@@ -275,8 +275,7 @@ __device__ __forceinline__ void reg_stage(cplx<R> (&v)[NTR][PF], cplx<R> *lds, c
     // is already padded by the caller (LIN). A thread's positions in a transform lie
     // in bit fields disjoint from its first position's (and LS is 1 without LIN), so
     // their offsets from it are compile-time constants either way (a batch of the
-    // uneven sweep 0.7 % faster; the resident passes' reg_stage_seq 1.3 % slower,
-    // which keeps the index per position).
+    // uneven sweep 0.7 % faster).
     static_assert(LIN || LS == 1, "padded positions are consecutive elements");
     auto at = [](int e) { return LIN ? e : lds_index<R>(e); };
     using V = cplx<R>;
@@ -359,86 +358,6 @@ __device__ __forceinline__ void reg_fft(cplx<R> (&v)[NTR][PF], cplx<R> *lds, con
                                         const Phasor<R> *__restrict__ tw)
 {
     reg_fft_from<R, N, PF, NTR, DIR, LS, 1, R16, LIN, WAVE>(v, lds, base, t, tw);
-}
-
-// The same transforms stage by stage through one transform's worth of LDS:
-// each stage loads its twiddles once and then writes, exchanges and reads
-// back the NTR transforms in turn (the arithmetic of each transform is that of
-// reg_fft). Used where NTR transforms would not fit LDS together.
-template <typename R, int N, int PF, int NTR, int DIR, int RS, int P>
-__device__ __forceinline__ void reg_stage_seq(cplx<R> (&v)[NTR][PF], cplx<R> *lds, int t,
-                                              const Phasor<R> *__restrict__ tw)
-{
-    using V = cplx<R>;
-    constexpr int NBT = PF / RS;
-    constexpr int STRIDE = N / PF;
-    constexpr bool LAST = P * RS == N;
-    Phasor<R> w[NBT][RS];
-    if constexpr (P > 1) {
-#pragma unroll
-        for (int u = 0; u < NBT; ++u) {
-            const int k = (t + u * STRIDE) & (P - 1);
-            const Phasor<R> *q = tw + tw_index(RS, P, k);
-#pragma unroll
-            for (int r = 1; r < RS; ++r)
-                w[u][r] = q[r - 1];
-        }
-    }
-#pragma unroll
-    for (int tr = 0; tr < NTR; ++tr) {
-#pragma unroll
-        for (int u = 0; u < NBT; ++u) {
-            V x[RS];
-#pragma unroll
-            for (int r = 0; r < RS; ++r)
-                x[r] = v[tr][u + r * NBT];
-            if constexpr (P > 1) {
-#pragma unroll
-                for (int r = 1; r < RS; ++r)
-                    x[r] = pmul<(DIR > 0)>(x[r], w[u][r]);
-            }
-            dft<RS, DIR>(x);
-            if constexpr (LAST) {
-#pragma unroll
-                for (int r = 0; r < RS; ++r)
-                    v[tr][u + r * NBT] = x[r];
-            } else {
-                const int i = t + u * STRIDE;
-                const int k = i & (P - 1);
-                const int j = (i - k) * RS + k;
-#pragma unroll
-                for (int r = 0; r < RS; ++r)
-                    lds[lds_index<R>(j + r * P)] = x[r];
-            }
-        }
-        if constexpr (!LAST) {
-            lds_sync();
-#pragma unroll
-            for (int m = 0; m < PF; ++m)
-                v[tr][m] = lds[lds_index<R>(t + m * STRIDE)];
-            lds_sync();
-        }
-    }
-}
-
-template <typename R, int N, int PF, int NTR, int DIR, int P, int R16>
-__device__ __forceinline__ void reg_fft_seq_from(cplx<R> (&v)[NTR][PF], cplx<R> *lds, int t,
-                                                 const Phasor<R> *__restrict__ tw)
-{
-    if constexpr (P < N) {
-        constexpr int RS = stage_radix<N, PF, P, R16>();
-        reg_stage_seq<R, N, PF, NTR, DIR, RS, P>(v, lds, t, tw);
-        reg_fft_seq_from<R, N, PF, NTR, DIR, P * RS, R16>(v, lds, t, tw);
-    }
-}
-
-// Unnormalized DFT of NTR transforms of length N, one at a time through LDS
-// positions 0..N-1 (stride 1), in the layout of reg_fft.
-template <typename R, int N, int PF, int NTR, int DIR, int R16 = 2048>
-__device__ __forceinline__ void reg_fft_seq(cplx<R> (&v)[NTR][PF], cplx<R> *lds, int t,
-                                            const Phasor<R> *__restrict__ tw)
-{
-    reg_fft_seq_from<R, N, PF, NTR, DIR, 1, R16>(v, lds, t, tw);
 }
 
 } // namespace opo

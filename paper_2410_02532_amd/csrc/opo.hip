@@ -687,7 +687,7 @@ template <typename R> static hipError_t launch_resident(opo_t *h, StepArgs<R> a,
         a.tile0 = g.tile0;
         a.tile_count = g.count;
         const int prec = sizeof(R) == 8 ? OPO_F64 : OPO_F32;
-        const size_t lds = static_cast<size_t>(lds_elems<R>(1 << g.ln)) * sizeof(cplx<R>);
+        const size_t lds = static_cast<size_t>(lds_elems<R>(g.nf << g.ln)) * sizeof(cplx<R>);
         void *args[] = {&a};
         HIP_RET(hipLaunchKernel(resident_fn<R>(g.ln, g.nf), dim3(g.count), dim3(resident_threads(g.ln, prec)), args,
                                 lds, st));
@@ -977,7 +977,7 @@ template <typename R> static int setup_kernels(opo_t *h)
     for (const Group &g : h->res_launch) {
         if (!resident_fn<R>(g.ln, g.nf)) return fail(OPO_EINVAL, "internal: no resident kernel for this size");
         HIP_TRY(hipFuncSetAttribute(resident_fn<R>(g.ln, g.nf), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    static_cast<int>(lds_elems<R>(1 << g.ln) * sizeof(cplx<R>))));
+                                    static_cast<int>(lds_elems<R>(g.nf << g.ln) * sizeof(cplx<R>))));
     }
     if (h->mid)
         HIP_TRY(hipFuncSetAttribute(mid_fn<R>(h->mid_rr, h->mid_nf), hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -853,9 +853,12 @@ __global__ __launch_bounds__(kThreads, (mixed_min_blocks<R, CR, RR>())) void mix
 // the fields cross HBM once per pass instead of twice per z-step. Thread t
 // keeps samples t + m*T (m < PF, T = nt/PF) of every field in registers: the
 // RK4 half-steps find the NF fields of a time point in one thread, and the
-// full-length transforms of one field at a time (Stockham stages with LDS
-// exchanges, fft_tile.h) return the bins in natural order to the same
-// positions, where the natural-order propagator table H_x(k)/nt applies.
+// full-length transforms of the fields together (Stockham stages with LDS
+// exchanges, fft_tile.h; every field in LDS of its own, 101 KB at 2^12, so that
+// a stage of all fields costs two barriers instead of two a field: 18.5 -> 16.8
+// us per z-step of a 2^12 instance, 17.1 -> 15.7 of a 2^11 one in FP64) return the
+// bins in natural order to the same positions, where the natural-order propagator
+// table H_x(k)/nt applies.
 // Shapes: FP32 nt 2^10..2^12 and FP64 2^10..2^11. Samples per thread and
 // field (res_pf): 8 (radix-8 stages; FP64 2^10: 4), so that an instance runs
 // on nt/8 threads, two waves per SIMD at 2^12, with the fields, a stage's
@@ -967,6 +970,9 @@ __global__ __launch_bounds__((res_threads<R, LN>())) void resident_pass(StepArgs
     const bool imag = d.dk_rev == 0.0;   // couplings without a phase: the same at every step
     const bool kerr = d.kerr != 0;
     const Phasor<R> *H = a.disp + d.disp_off + t;
+    int base[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) base[f] = f * N;
     for (int j = 0; j < a.nz; ++j) {
         // couplings of step j: [1] its first half from z_j, [0] its second half from z_j + dz/2
         if (j == 0 || !imag) {
@@ -978,13 +984,13 @@ __global__ __launch_bounds__((res_threads<R, LN>())) void resident_pass(StepArgs
 #pragma unroll
         for (int m = 0; m < PF; ++m)
             rk4_fields<R, NF>(cpl, 1, imag, kerr, v[0][m], v[1][m], v[NF - 1][m]);
-        reg_fft_seq<R, N, PF, NF, -1, N>(v, s, t, step_local(a.tw));
+        reg_fft<R, N, PF, NF, -1, 1, N>(v, s, base, t, step_local(a.tw));
         const Phasor<R> *Hj = step_local(H);
 #pragma unroll
         for (int f = 0; f < NF; ++f)
 #pragma unroll
             for (int m = 0; m < PF; ++m) v[f][m] = pmul(v[f][m], Hj[f * N + m * T]);
-        reg_fft_seq<R, N, PF, NF, +1, N>(v, s, t, step_local(a.tw));
+        reg_fft<R, N, PF, NF, +1, 1, N>(v, s, base, t, step_local(a.tw));
 #pragma unroll
         for (int m = 0; m < PF; ++m)
             rk4_fields<R, NF>(cpl, 0, imag, kerr, v[0][m], v[1][m], v[NF - 1][m]);
@@ -1014,13 +1020,14 @@ __global__ __launch_bounds__((res_threads<R, LN>())) void resident_pass(StepArgs
     }
     if ((flags & A_GDD) && d.gdd_mask) {
         const double inv_nt = 1.0 / N;
+        const int one[1] = {0};
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
             if (!((d.gdd_mask >> f) & 1)) continue;
             V w[1][PF];
 #pragma unroll
             for (int m = 0; m < PF; ++m) w[0][m] = v[f][m];
-            reg_fft_seq<R, N, PF, 1, -1, N>(w, s, t, a.tw);
+            reg_fft<R, N, PF, 1, -1, 1, N>(w, s, one, t, a.tw);
 #pragma unroll
             for (int m = 0; m < PF; ++m) {
                 const int k = t + m * T;
@@ -1028,7 +1035,7 @@ __global__ __launch_bounds__((res_threads<R, LN>())) void resident_pass(StepArgs
                 const double2 e = unit_rev(d.gdd_rev * ks * ks);
                 w[0][m] = pmul(w[0][m], make_phasor<R>(e.x * inv_nt, e.y * inv_nt));
             }
-            reg_fft_seq<R, N, PF, 1, +1, N>(w, s, t, a.tw);
+            reg_fft<R, N, PF, 1, +1, 1, N>(w, s, one, t, a.tw);
 #pragma unroll
             for (int m = 0; m < PF; ++m) v[f][m] = w[0][m];
         }
