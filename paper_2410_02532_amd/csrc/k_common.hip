@@ -10,7 +10,7 @@ namespace opo {
 // left as it is. Any other d that is not a number (a step that overflowed, or
 // non-finite fields) rejects the attempt like a too-large error and halves dz;
 // the attempt budget ends an instance that never recovers.
-__global__ __launch_bounds__(kThreads) void adapt_control(AdaptState *ctl, int n_inst, int chunks,
+__global__ __launch_bounds__(kThreads) void adapt_control(const InstDesc *inst, AdaptState *ctl, int n_inst,
                                                           const double *part, int mode, double z0, double length,
                                                           double dz0, double tol, int max_attempts)
 {
@@ -19,9 +19,9 @@ __global__ __launch_bounds__(kThreads) void adapt_control(AdaptState *ctl, int n
         // error sums of the attempt: lane-strided partials, then a fixed shuffle tree
         double num = 0.0, den = 0.0;
         if (mode == 1)
-            for (int c = lane; c < chunks; c += 64) {
-                num += part[2 * (static_cast<long long>(ii) * chunks + c)];
-                den += part[2 * (static_cast<long long>(ii) * chunks + c) + 1];
+            for (int c = lane; c < inst[ii].tiles_a; c += 64) {
+                num += part[3 * static_cast<long long>(inst[ii].tile_a0 + c)];
+                den += part[3 * static_cast<long long>(inst[ii].tile_a0 + c) + 1];
             }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {

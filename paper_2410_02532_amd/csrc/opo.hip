@@ -303,7 +303,6 @@ struct opo_s {
     // propagator tables (coarse and fine step), control state, error partials
     void *a_uc = nullptr, *a_uf = nullptr, *a_tab = nullptr;
     AdaptState *d_actl = nullptr;
-    double *d_apart = nullptr;
     int a_chunks = 0;
     hipGraphExec_t a_graph = nullptr;   // one attempt, replayed (reads everything from the device)
     std::vector<double> t_window;    // T of every instance [ps]
@@ -537,7 +536,7 @@ static void release(opo_t *h)
         if (st) (void)hipStreamDestroy(st);
     void *bufs[] = {h->d_res_inst, h->d_w4tab, h->pump, h->d_inst, h->d_tile_a, h->d_tile_b, h->d_tw, h->d_disp, h->d_map[0], h->d_map[1],
                     h->d_partial, h->d_hist, h->d_counter, h->spec_buf, h->d_record, h->d_snap,
-                    h->a_uc, h->a_uf, h->a_tab, h->d_actl, h->d_apart, h->d_team, h->d_mid_inst, h->d_coef,
+                    h->a_uc, h->a_uf, h->a_tab, h->d_actl, h->d_team, h->d_mid_inst, h->d_coef,
                     h->d_mid_map[0], h->d_mid_map[1], h->d_mid_map[2], h->d_mid_map[3]};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
@@ -629,11 +628,14 @@ template <typename R> static void set_half_steps(const opo_t *h, StepArgs<R> &a,
 // Column launches over the two-pass instances (of one half, or all), and with
 // all_tiles also over the tiles of the resident instances (the adaptive step
 // and the spectrum read-out).
+// With a.alt_state set the second layer runs alt_flags.
 template <typename R>
-static hipError_t launch_a(opo_t *h, StepArgs<R> a, int flags, int step, int half = -1, bool all_tiles = false)
+static hipError_t launch_a(opo_t *h, StepArgs<R> a, int flags, int step, int half = -1, bool all_tiles = false,
+                           int alt_flags = 0)
 {
     a.tile_inst = h->d_tile_a;
     a.flags = flags;
+    a.alt_flags = alt_flags;
     set_half_steps<R>(h, a, step);
     HIP_RET(prof_begin(h, OPO_K_COLUMN));
     for (int set = 0; set < (all_tiles ? 2 : 1); ++set)
@@ -643,7 +645,7 @@ static hipError_t launch_a(opo_t *h, StepArgs<R> a, int flags, int step, int hal
             a.tile_count = g.count;
             a.inst_only = g.only;
             void *args[] = {&a};
-            HIP_RET(hipLaunchKernel(column_fn<R>(g.ln, g.nf), dim3(g.count), dim3(kThreads), args, h->lds_a,
+            HIP_RET(hipLaunchKernel(column_fn<R>(g.ln, g.nf), dim3(g.count, a.alt_state ? 2 : 1), dim3(kThreads), args, h->lds_a,
                                     h->stream));
         }
     return prof_end(h);
@@ -653,7 +655,7 @@ template <typename R>
 static hipError_t launch_b(opo_t *h, StepArgs<R> a, int flags, int step = 0, int sel = -1, bool all_tiles = false)
 {
     a.tile_inst = h->d_tile_b;
-    a.flags = flags;
+    a.flags = a.alt_flags = flags;
     double z, tau;
     substep(h->order, step, z, tau, a.disp_sel);
     if (sel >= 0) a.disp_sel = sel;
@@ -664,7 +666,7 @@ static hipError_t launch_b(opo_t *h, StepArgs<R> a, int flags, int step = 0, int
             a.tile_count = g.count;
             a.inst_only = g.only;
             void *args[] = {&a};
-            HIP_RET(hipLaunchKernel(row_fn<R>(g.ln), dim3(g.count), dim3(kThreads), args, h->lds_b, h->stream));
+            HIP_RET(hipLaunchKernel(row_fn<R>(g.ln), dim3(g.count, a.alt_state ? 2 : 1), dim3(kThreads), args, h->lds_b, h->stream));
         }
     return prof_end(h);
 }
@@ -1607,26 +1609,24 @@ template <typename R> static hipError_t enqueue_attempt(opo_t *h)
     a.disp = tab;
     adapt_begin<R><<<blocks, kThreads, 0, h->stream>>>(h->d_inst, h->d_actl, h->a_chunks, u, uc, uf, tab);
     HIP_RET(hipGetLastError());
-    a.state = uc;                 // one step of dz, from u
+    // one step of dz on u_c and the first of two of dz/2 on u_f, both from u
+    a.state = uc;
     a.adapt_scale = 1.0;
+    a.alt_state = uf;
+    a.alt_scale = 0.5;
     a.src = u;
-    HIP_RET(launch_a<R>(h, a, A_RK_THIS | A_FWD, 0, -1, true));
+    HIP_RET(launch_a<R>(h, a, A_RK_THIS | A_FWD, 0, -1, true, A_RK_THIS | A_FWD));
     a.src = nullptr;
     HIP_RET(launch_b<R>(h, a, B_DISP, 0, 0, true));
-    HIP_RET(launch_a<R>(h, a, A_INV | A_RK_PREV, 1, -1, true));
-    a.state = uf;                 // two steps of dz/2, from u
+    HIP_RET(launch_a<R>(h, a, A_INV | A_RK_PREV, 1, -1, true, A_INV | A_RK_PREV | A_RK_THIS | A_FWD));
+    a.state = uf;                 // the second step of dz/2, and the error sums
     a.adapt_scale = 0.5;
-    a.src = u;
-    HIP_RET(launch_a<R>(h, a, A_RK_THIS | A_FWD, 0, -1, true));
-    a.src = nullptr;
-    HIP_RET(launch_b<R>(h, a, B_DISP, 0, 0, true));
-    HIP_RET(launch_a<R>(h, a, A_INV | A_RK_PREV | A_RK_THIS | A_FWD, 1, -1, true));
+    a.alt_state = nullptr;
     HIP_RET(launch_b<R>(h, a, B_DISP, 1, 0, true));
-    HIP_RET(launch_a<R>(h, a, A_INV | A_RK_PREV, 2, -1, true));
-    adapt_error<R><<<blocks, kThreads, 0, h->stream>>>(h->d_inst, h->d_actl, h->a_chunks, uc, uf, h->d_apart);
-    HIP_RET(hipGetLastError());
+    a.err = uc;
+    HIP_RET(launch_a<R>(h, a, A_INV | A_RK_PREV | A_ERROR, 2, -1, true));
     adapt_control<<<(h->n_inst + kThreads / 64 - 1) / (kThreads / 64), kThreads, 0, h->stream>>>(
-        h->d_actl, h->n_inst, h->a_chunks, h->d_apart, 1, 0.0, 0.0, 0.0, 0.0, 0);
+        h->d_inst, h->d_actl, h->n_inst, h->d_partial, 1, 0.0, 0.0, 0.0, 0.0, 0);
     return hipGetLastError();
 }
 
@@ -1649,11 +1649,9 @@ static int adaptive_impl(opo_t *h, double length, double tol, double dz0, int ma
             return fail(OPO_EINVAL, "too many instances for the adaptive step");
         if (hipMalloc(&h->a_uc, h->state_bytes) != hipSuccess || hipMalloc(&h->a_uf, h->state_bytes) != hipSuccess ||
             hipMalloc(&h->a_tab, n_elem * sizeof(Phasor<R>)) != hipSuccess ||
-            hipMalloc(&h->d_actl, h->n_inst * sizeof(AdaptState)) != hipSuccess ||
-            hipMalloc(&h->d_apart, 2 * sizeof(double) * h->a_chunks * h->n_inst) != hipSuccess) {
+            hipMalloc(&h->d_actl, h->n_inst * sizeof(AdaptState)) != hipSuccess) {
             // all or none: a later call allocates again
-            void **bufs[] = {&h->a_uc, &h->a_uf, &h->a_tab, reinterpret_cast<void **>(&h->d_actl),
-                             reinterpret_cast<void **>(&h->d_apart)};
+            void **bufs[] = {&h->a_uc, &h->a_uf, &h->a_tab, reinterpret_cast<void **>(&h->d_actl)};
             for (void **b : bufs) {
                 if (*b) (void)hipFree(*b);
                 *b = nullptr;
@@ -1680,7 +1678,7 @@ static int adaptive_impl(opo_t *h, double length, double tol, double dz0, int ma
         }
     }
     adapt_control<<<(h->n_inst + kThreads / 64 - 1) / (kThreads / 64), kThreads, 0, h->stream>>>(
-        h->d_actl, h->n_inst, h->a_chunks, h->d_apart, 0, h->z, length, dz0, tol, max_attempts);
+        h->d_inst, h->d_actl, h->n_inst, h->d_partial, 0, h->z, length, dz0, tol, max_attempts);
     HIP_TRY(hipGetLastError());
     std::vector<AdaptState> ctl(h->n_inst);
     HIP_TRY(hipMemcpyAsync(ctl.data(), h->d_actl, ctl.size() * sizeof(AdaptState), hipMemcpyDeviceToHost,

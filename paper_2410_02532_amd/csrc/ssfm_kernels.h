@@ -78,6 +78,7 @@ enum : int {
     A_RK_THIS = 64,   // first half-step of this z-step
     A_FWD = 128,      // end with the forward column FFT + twiddle (else store samples)
     A_GDD = 256,      // resident passes: GDD between the energies and the mirror
+    A_ERROR = 512,    // adaptive step: FP64 partial sums of |u_f - u_c|^2 and |u_f|^2
 };
 
 enum : int {
@@ -140,7 +141,21 @@ template <typename R> struct StepArgs {
     const AdaptState *adapt;
     double adapt_scale;
     const cplx<R> *src;
+    // the second layer of the launch's grid (blockIdx.y = 1): the same tiles on another
+    // copy of the fields with another step and flags
+    cplx<R> *alt_state;
+    double alt_scale;
+    int alt_flags;
+    const cplx<R> *err;       // A_ERROR: the coarse copy u_c
 };
+
+template <typename R> __device__ __forceinline__ void second_layer(StepArgs<R> &a)
+{
+    if (blockIdx.y == 0) return;
+    a.state = a.alt_state;
+    a.adapt_scale = a.alt_scale;
+    a.flags = a.alt_flags;
+}
 
 // Element q of the array at base, q formed in 32 bits (below 2^28 within one
 // instance's arrays): the address is a uniform 64-bit base plus a 32-bit
@@ -507,7 +522,8 @@ __device__ __forceinline__ void column_fft(cplx<R> (&v)[NF][PF], cplx<R> *s, con
 
 // Column pass of one tile: COLS columns j1 = c0 + c of the NF fields.
 // Thread (c, t) holds samples j2 (or k2) = t + m*T, m < PF, of column c.
-template <typename R, int LN2, int NF>
+// (ERR: with the error sums of the adaptive step.)
+template <typename R, int LN2, int NF, bool ERR>
 __device__ __forceinline__ void column_tile(const StepArgs<R> &a, const InstDesc &d, int tile,
                                             cplx<R> *s, Coupling<R> *cpl, double *red)
 {
@@ -641,7 +657,21 @@ __device__ __forceinline__ void column_tile(const StepArgs<R> &a, const InstDesc
         v[1][m] = y1;
         if constexpr (NF == 3) v[2][m] = y2;
     }
-    if (flags & A_ENERGY) {
+    if (ERR && (flags & A_ERROR)) {
+        const V *ec = a.err + d.off;
+#pragma unroll
+        for (int m = 0; m < PF; ++m)
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+                if (act) {
+                    const V c = el32(ec, q0 + m * cstep + f * nt);
+                    const double fx = v[f][m].x, fy = v[f][m].y;
+                    const double ex = fx - static_cast<double>(c.x), ey = fy - static_cast<double>(c.y);
+                    en[0] += ex * ex + ey * ey;
+                    en[1] += fx * fx + fy * fy;
+                }
+    }
+    if (flags & (ERR ? A_ENERGY | A_ERROR : A_ENERGY)) {
         block_sum3(en, red);
         if (threadIdx.x == 0 && !stopped)
             for (int x = 0; x < 3; ++x)
@@ -671,12 +701,12 @@ __device__ __forceinline__ void column_tile(const StepArgs<R> &a, const InstDesc
     }
 }
 
-template <typename R, int L, int HI, int NF>
+template <typename R, int L, int HI, int NF, bool ERR>
 __device__ __forceinline__ void column_dispatch(const StepArgs<R> &a, const InstDesc &d, int tile, cplx<R> *s,
                                                 Coupling<R> *cpl, double *red)
 {
-    if (d.log2n2 == L) column_tile<R, L, NF>(a, d, tile, s, cpl, red);
-    else if constexpr (L < HI) column_dispatch<R, L + 1, HI, NF>(a, d, tile, s, cpl, red);
+    if (d.log2n2 == L) column_tile<R, L, NF, ERR>(a, d, tile, s, cpl, red);
+    else if constexpr (L < HI) column_dispatch<R, L + 1, HI, NF, ERR>(a, d, tile, s, cpl, red);
 }
 
 // Column pass over the tiles of NF-wave instances whose log2 n2 lies in [LO, HI].
@@ -690,7 +720,8 @@ __global__ __launch_bounds__(kThreads) void column_pass(StepArgs<R> a)
     // a launch over one instance skips the dependent load of the tile's instance
     const int ii = a.inst_only > 0 ? a.inst_only - 1 : a.tile_inst[tile];
     if (a.adapt && a.adapt[ii].status != 0) return;
-    column_dispatch<R, LO, HI, NF>(a, a.inst[ii], tile, reinterpret_cast<cplx<R> *>(lds_raw), &cpl, red);
+    second_layer(a);
+    column_dispatch<R, LO, HI, NF, true>(a, a.inst[ii], tile, reinterpret_cast<cplx<R> *>(lds_raw), &cpl, red);
 }
 
 // ------------------------------------------------------------------------
@@ -796,6 +827,7 @@ __global__ __launch_bounds__(kThreads) void row_pass(StepArgs<R> a)
     const int tile = a.tile0 + blockIdx.x;
     const int ii = a.inst_only > 0 ? a.inst_only - 1 : a.tile_inst[tile];   // as in column_pass
     if (a.adapt && a.adapt[ii].status != 0) return;
+    second_layer(a);
     row_dispatch<R, LO, HI, true>(a, a.inst[ii], tile, reinterpret_cast<cplx<R> *>(lds_raw));
 }
 
@@ -839,7 +871,7 @@ __global__ __launch_bounds__(kThreads, (mixed_min_blocks<R, CR, RR>())) void mix
     const int code = ac.block_map[blockIdx.x];
     if (code == kNoTile) return;
     if (code >= 0) {
-        column_dispatch<R, kColRanges[CR][0], kColRanges[CR][1], NF>(ac, ac.inst[ac.tile_inst[code]], code, s, &cpl,
+        column_dispatch<R, kColRanges[CR][0], kColRanges[CR][1], NF, false>(ac, ac.inst[ac.tile_inst[code]], code, s, &cpl,
                                                                  red);
     } else {
         const int tile = -1 - code;
@@ -1084,16 +1116,19 @@ __global__ __launch_bounds__((res_threads<R, LN>())) void resident_pass(StepArgs
 // formed in FP64 (phase reduced modulo one revolution) and stored in the
 // row-pass order (position k2*n1 + k1 holds bin k = k2 + n2*k1), or in natural
 // bin order for the resident passes.
-template <typename R>
-__device__ __forceinline__ Phasor<R> propagator(const InstDesc &d, long long q, double dz, bool natural)
+// Modulus of H_x/nt (nt is a power of two, so the product is exact).
+__device__ __forceinline__ double propagator_amp(const InstDesc &d, int f, double dz)
 {
-    const int f = static_cast<int>(q / d.nt);
-    const int p = static_cast<int>(q - static_cast<long long>(f) * d.nt);
+    return exp(-d.alpha_half[f] * dz) * (1.0 / d.nt);
+}
+
+template <typename R>
+__device__ __forceinline__ Phasor<R> propagator(const InstDesc &d, int f, int p, double dz, double amp, bool natural)
+{
     const int k2 = p >> d.log2n1, k1 = p & (d.n1 - 1);
     const int k = natural ? p : k2 + d.n2 * k1;
     const double ks = static_cast<double>(k < (d.nt >> 1) ? k : k - d.nt);
     const double rho = dz * ks * (d.disp[f][0] + ks * (d.disp[f][1] + ks * d.disp[f][2]));
-    const double amp = exp(-d.alpha_half[f] * dz) / d.nt;
     const double2 e = unit_rev(rho);
     return make_phasor<R>(amp * e.x, amp * e.y);
 }
@@ -1105,9 +1140,12 @@ __global__ __launch_bounds__(kThreads) void disp_table(const InstDesc *inst, int
     const InstDesc &d = inst[owner];
     out += static_cast<long long>(sel) * d.nf * d.nt;     // table of the sel-th step size
     const long long n = static_cast<long long>(d.nf) * d.nt;
+    const double amp[3] = {propagator_amp(d, 0, dz), propagator_amp(d, 1, dz), propagator_amp(d, 2, dz)};
     for (long long q = blockIdx.x * static_cast<long long>(kThreads) + threadIdx.x; q < n;
-         q += static_cast<long long>(gridDim.x) * kThreads)
-        out[d.disp_off + q] = propagator<R>(d, q, dz, d.resident != 0);
+         q += static_cast<long long>(gridDim.x) * kThreads) {
+        const int f = static_cast<int>(q >> d.log2nt), p = static_cast<int>(q) & (d.nt - 1);
+        out[d.disp_off + q] = propagator<R>(d, f, p, dz, f == 0 ? amp[0] : f == 1 ? amp[1] : amp[2], d.resident != 0);
+    }
 }
 
 // ------------------------------------------------------------------------
@@ -1117,8 +1155,9 @@ __global__ __launch_bounds__(kThreads) void disp_table(const InstDesc *inst, int
 // rejects and halves dz; otherwise (4 u_f - u_c)/3 becomes the fields, z
 // advances, and dz shrinks by 2^(1/3) when d > tol, grows by 2^(1/3) when
 // d < tol/2. The kernels below run once per attempt around the step
-// launches: begin, [coarse, fine passes], error, control. Each of begin and
-// error covers instance b / chunks with `chunks` workgroups.
+// launches: begin, [coarse, fine passes], control. The launches that both copies need
+// run them as two layers of one grid, and the last fine column launch adds up the errors.
+// begin covers instance b / chunks with `chunks` workgroups.
 constexpr double kAdaptGrow = 1.25992104989487316477;   // 2^(1/3), the nearest double
 constexpr double kAdaptSlack = 1.0 + 1e-9;   // a step that stops within 1e-9 dz of the end goes to it
 
@@ -1138,6 +1177,11 @@ __global__ __launch_bounds__(kThreads) void adapt_begin(const InstDesc *inst, co
     if (!run && !st.pend) return;
     const InstDesc &d = inst[ii];
     const long long n = static_cast<long long>(d.nf) * d.nt;
+    // bound by memory (87 MB for 32 amplifiers of 2^12..2^16 points, 22 us; 25.8 us with
+    // the moduli and a 64-bit division per entry). Not refilling the table while the step
+    // stays the same gave 0.2 % of an attempt: it rarely does.
+    const double dz = 0.5 * st.dz;
+    const double amp[3] = {propagator_amp(d, 0, dz), propagator_amp(d, 1, dz), propagator_amp(d, 2, dz)};
     for (long long q = ch * static_cast<long long>(kThreads) + threadIdx.x; q < n;
          q += static_cast<long long>(chunks) * kThreads) {
         const long long j = d.off + q;
@@ -1145,32 +1189,10 @@ __global__ __launch_bounds__(kThreads) void adapt_begin(const InstDesc *inst, co
             const V f = uf[j], c = uc[j];
             u[j] = mk<V>((R(4) * f.x - c.x) / R(3), (R(4) * f.y - c.y) / R(3));
         }
-        if (run) tab[j] = propagator<R>(d, q, 0.5 * st.dz, false);   // the adaptive step runs column/row tiles
-    }
-}
-
-// FP64 partial sums of |u_f - u_c|^2 and |u_f|^2 of each running instance.
-template <typename R>
-__global__ __launch_bounds__(kThreads) void adapt_error(const InstDesc *inst, const AdaptState *ctl, int chunks,
-                                                        const cplx<R> *uc, const cplx<R> *uf, double *part)
-{
-    __shared__ double red[3 * kThreads / 64];
-    const int ii = blockIdx.x / chunks, ch = blockIdx.x - ii * chunks;
-    if (ctl[ii].status != 0) return;
-    const InstDesc &d = inst[ii];
-    const long long n = static_cast<long long>(d.nf) * d.nt;
-    double v[3] = {0.0, 0.0, 0.0};
-    for (long long q = ch * static_cast<long long>(kThreads) + threadIdx.x; q < n;
-         q += static_cast<long long>(chunks) * kThreads) {
-        const double fx = uf[d.off + q].x, fy = uf[d.off + q].y;
-        const double ex = fx - static_cast<double>(uc[d.off + q].x), ey = fy - static_cast<double>(uc[d.off + q].y);
-        v[0] += ex * ex + ey * ey;
-        v[1] += fx * fx + fy * fy;
-    }
-    block_sum3(v, red);
-    if (threadIdx.x == 0) {
-        part[2 * static_cast<long long>(blockIdx.x)] = v[0];
-        part[2 * static_cast<long long>(blockIdx.x) + 1] = v[1];
+        if (run) {   // the adaptive step runs column/row tiles
+            const int f = static_cast<int>(q >> d.log2nt), p = static_cast<int>(q) & (d.nt - 1);
+            tab[j] = propagator<R>(d, f, p, dz, f == 0 ? amp[0] : f == 1 ? amp[1] : amp[2], false);
+        }
     }
 }
 
@@ -1178,7 +1200,7 @@ __global__ __launch_bounds__(kThreads) void adapt_error(const InstDesc *inst, co
 // `length` with step dz0; mode 1 takes the decision of the attempt just made.
 // Both then prepare the next attempt: stop at the end or when the budget is
 // spent, else cut a step that would pass the end.
-__global__ __launch_bounds__(kThreads) void adapt_control(AdaptState *ctl, int n_inst, int chunks,
+__global__ __launch_bounds__(kThreads) void adapt_control(const InstDesc *inst, AdaptState *ctl, int n_inst,
                                                           const double *part, int mode, double z0, double length,
                                                           double dz0, double tol, int max_attempts);
 
