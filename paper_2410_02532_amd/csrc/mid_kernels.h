@@ -48,6 +48,16 @@ template <typename R> struct MidArgs {
 // ---- column tile: four waves of 64/T columns each (T = N/PF lanes a column)
 constexpr int kMidMinLog2N2 = 4, kMidMaxLog2N2 = 6;
 constexpr int mid_col_pf(int ln2) { return ln2 <= 5 ? 2 : 4; }
+// FP32 rows of 1024 and 2048 points take 16 samples a thread (radix-16 stages, one stage
+// and one exchange less): the batched sweep 16.7 -> 16.4 ms, two waves 12.0 -> 11.7. The
+// kernel then holds 128 registers (four workgroups per CU) instead of 92, which costs
+// nothing here (mixed_pass lost 2.5 % with it). Rows of 256 with 16 lost 0.6 %, columns of
+// 2^6 with 8 samples (168 registers, spills) 8 %.
+template <typename R> constexpr int mid_row_pf(int ln1)
+{
+    return sizeof(R) == 4 && (ln1 == 10 || ln1 == 11) ? 16 : row_pf<R>(ln1);
+}
+template <typename R> constexpr int mid_rows(int ln1) { return kThreads * mid_row_pf<R>(ln1) >> ln1; }
 constexpr int mid_cols(int ln2) { return kThreads * mid_col_pf(ln2) >> ln2; }
 
 template <typename R, int LN2, int NF>
@@ -124,7 +134,7 @@ template <typename R, int LN1>
 __device__ __forceinline__ void mid_row_tile(const MidArgs<R> &a, const MidInst &d, int tile, cplx<R> *s)
 {
     using V = cplx<R>;
-    constexpr int N = 1 << LN1, PF = row_pf<R>(LN1), ROWS = row_rows<R>(LN1), T = N / PF;
+    constexpr int N = 1 << LN1, PF = mid_row_pf<R>(LN1), ROWS = mid_rows<R>(LN1), T = N / PF;
     constexpr bool WAVE = T <= OPO_ROW_WAVE_MAX;
     const int r = threadIdx.x / T, t = threadIdx.x % T;
     const int row = tile * ROWS + r;
@@ -154,10 +164,7 @@ __device__ __forceinline__ void mid_row_dispatch(const MidArgs<R> &a, const MidI
 }
 
 // Rows of 2^LO..2^HI points: 5..11, or 12 (FP32).
-#ifndef OPO_MID_MIN_BLOCKS
-#define OPO_MID_MIN_BLOCKS 4
-#endif
-template <typename R, int HI> constexpr int mid_min_blocks() { return sizeof(R) == 4 && HI <= 11 ? OPO_MID_MIN_BLOCKS : 1; }
+template <typename R, int HI> constexpr int mid_min_blocks() { return sizeof(R) == 4 && HI <= 11 ? 4 : 1; }
 
 template <typename R, int LO, int HI, int NF>
 __global__ __launch_bounds__(kThreads, (mid_min_blocks<R, HI>())) void mid_pass(MidArgs<R> a)

@@ -1310,7 +1310,7 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
             int nc = 0;
             for (int i : order) {
                 const InstDesc &d = h->inst[i];
-                const int rows = f64 ? row_rows<double>(d.log2n1) : row_rows<float>(d.log2n1);
+                const int rows = f64 ? mid_rows<double>(d.log2n1) : mid_rows<float>(d.log2n1);
                 h->mid_lds = std::max(h->mid_lds, (f64 ? lds_elems<double>(rows << d.log2n1)
                                                        : lds_elems<float>(rows << d.log2n1)) * h->elem);
                 if (half[i] == ch) {
