@@ -2,5 +2,5 @@
 #include "kernel_list.h"
 
 namespace opo {
-OPO_MID_KERNELS(template, double)
+OPO_MID_KERNELS_F64(template)
 } // namespace opo

@@ -72,17 +72,29 @@
     DECL __global__ void team_pass<R, 2>(TeamArgs<R>);                                             \
     DECL __global__ void team_pass<R, 3>(TeamArgs<R>);
 
-// Interior launches of batches: columns of 2^4..2^6 points, rows of 2^5..2^11, or 2^12 (FP32).
+// Launches inside a pass of batches: columns of 2^4..2^6, 2^7 or 2^8 points (0, 1, 2), rows
+// of 2^5..2^11, or 2^12 (FP32). The longer columns come with the longest rows.
 #define OPO_MID_KERNELS(DECL, R)                                                                   \
-    DECL __global__ void mid_pass<R, 5, 11, 2>(MidArgs<R>);                                        \
-    DECL __global__ void mid_pass<R, 5, 11, 3>(MidArgs<R>);                                        \
+    DECL __global__ void mid_pass<R, 5, 11, 2, 0>(MidArgs<R>);                                     \
+    DECL __global__ void mid_pass<R, 5, 11, 3, 0>(MidArgs<R>);                                     \
     DECL __global__ void coupling_table<R>(const InstDesc *, int, int, double, double, int, int,   \
                                            int, Coupling<R> *);
 
 #define OPO_MID_KERNELS_F32(DECL)                                                                  \
     OPO_MID_KERNELS(DECL, float)                                                                   \
-    DECL __global__ void mid_pass<float, 12, 12, 2>(MidArgs<float>);                               \
-    DECL __global__ void mid_pass<float, 12, 12, 3>(MidArgs<float>);
+    DECL __global__ void mid_pass<float, 12, 12, 2, 0>(MidArgs<float>);                            \
+    DECL __global__ void mid_pass<float, 12, 12, 3, 0>(MidArgs<float>);                            \
+    DECL __global__ void mid_pass<float, 12, 12, 2, 1>(MidArgs<float>);                            \
+    DECL __global__ void mid_pass<float, 12, 12, 3, 1>(MidArgs<float>);                            \
+    DECL __global__ void mid_pass<float, 12, 12, 2, 2>(MidArgs<float>);                            \
+    DECL __global__ void mid_pass<float, 12, 12, 3, 2>(MidArgs<float>);
+
+#define OPO_MID_KERNELS_F64(DECL)                                                                  \
+    OPO_MID_KERNELS(DECL, double)                                                                  \
+    DECL __global__ void mid_pass<double, 5, 11, 2, 1>(MidArgs<double>);                           \
+    DECL __global__ void mid_pass<double, 5, 11, 3, 1>(MidArgs<double>);                           \
+    DECL __global__ void mid_pass<double, 5, 11, 2, 2>(MidArgs<double>);                           \
+    DECL __global__ void mid_pass<double, 5, 11, 3, 2>(MidArgs<double>);
 
 #define OPO_ALL_KERNELS(DECL)                                                                      \
     OPO_PASS_KERNELS_F32(DECL)                                                                     \
@@ -98,5 +110,5 @@
     OPO_TEAM_KERNELS(DECL, float)                                                                  \
     OPO_TEAM_KERNELS(DECL, double)                                                                 \
     OPO_MID_KERNELS_F32(DECL)                                                                      \
-    OPO_MID_KERNELS(DECL, double)                                                                  \
+    OPO_MID_KERNELS_F64(DECL)                                                                      \
     OPO_RESIDENT_KERNELS(DECL)

@@ -46,7 +46,7 @@ template <typename R> struct MidArgs {
 };
 
 // ---- column tile: four waves of 64/T columns each (T = N/PF lanes a column)
-constexpr int kMidMinLog2N2 = 4, kMidMaxLog2N2 = 6;
+constexpr int kMidMinLog2N2 = 4;
 constexpr int mid_col_pf(int ln2) { return ln2 <= 5 ? 2 : 4; }
 // FP32 rows of 1024 and 2048 points take 16 samples a thread (radix-16 stages, one stage
 // and one exchange less): the batched sweep 16.7 -> 16.4 ms, two waves 12.0 -> 11.7. The
@@ -58,7 +58,10 @@ template <typename R> constexpr int mid_row_pf(int ln1)
     return sizeof(R) == 4 && (ln1 == 10 || ln1 == 11) ? 16 : row_pf<R>(ln1);
 }
 template <typename R> constexpr int mid_rows(int ln1) { return kThreads * mid_row_pf<R>(ln1) >> ln1; }
-constexpr int mid_cols(int ln2) { return kThreads * mid_col_pf(ln2) >> ln2; }
+template <typename R> constexpr int mid_cols(int ln2)
+{
+    return ln2 <= 6 ? kThreads * mid_col_pf(ln2) >> ln2 : col_cols<R>(ln2);
+}
 
 template <typename R, int LN2, int NF>
 __device__ __forceinline__ void mid_column_tile(const MidArgs<R> &a, const MidInst &d, const Coupling<R> &cp, int tile)
@@ -69,7 +72,7 @@ __device__ __forceinline__ void mid_column_tile(const MidArgs<R> &a, const MidIn
     const int flags = a.flags;
     const int lane = threadIdx.x & 63, c = lane % COLS, t = lane / COLS;
     const unsigned n1 = d.n1, nt = d.nt;
-    const unsigned j1 = tile * mid_cols(LN2) + (threadIdx.x >> 6) * COLS + c;
+    const unsigned j1 = tile * mid_cols<R>(LN2) + (threadIdx.x >> 6) * COLS + c;
     const int kind = d.kind;
     V *g = a.state + d.off;
     const Phasor<R> *w4t = a.w4tab + d.w4_off;
@@ -129,6 +132,62 @@ __device__ __forceinline__ void mid_column_tile(const MidArgs<R> &a, const MidIn
     }
 }
 
+// Longer columns (2^7 and 2^8 points, of grids whose rows are at their longest): the
+// tile of column_tile, exchanging through LDS, without its flags and checks (186 registers,
+// two workgroups per CU: 8 x 2^20 in FP32 31.7 -> 30.9 ms a round trip; held to 168 for
+// three it spills and took 31.6).
+template <typename R, int LN2, int NF>
+__device__ __forceinline__ void mid_long_column_tile(const MidArgs<R> &a, const MidInst &d, const Coupling<R> &cp,
+                                                     int tile, cplx<R> *s)
+{
+    using V = cplx<R>;
+    constexpr int N = 1 << LN2, PF = col_pf<R>(LN2), COLS = col_cols<R>(LN2), T = N / PF;
+    const int flags = a.flags, kind = d.kind;
+    const int c = threadIdx.x % COLS, t = threadIdx.x / COLS;
+    const unsigned n1 = d.n1, nt = d.nt, q0 = tile * COLS + c + n1 * t, step = n1 * T;
+    V *g = a.state + d.off;
+    const Phasor<R> *w4t = a.w4tab + d.w4_off;
+    const bool stopped = a.counter[2] != 0;   // see column_tile
+    V v[NF][PF];
+#pragma unroll
+    for (int m = 0; m < PF; ++m)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) v[f][m] = el32(g, q0 + m * step + f * nt);
+    int base[NF];
+#pragma unroll
+    for (int f = 0; f < NF; ++f) base[f] = f * col_lds_row<R>(LN2) * N + c;
+    if (flags & A_INV) {
+#pragma unroll
+        for (int m = 0; m < PF; ++m) {
+            const Phasor<R> w4 = el32(w4t, q0 + m * step);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) v[f][m] = pmul<true>(v[f][m], w4);
+        }
+        column_fft<R, LN2, PF, NF, +1, COLS>(v, s, base, t, a.tw);
+    }
+#pragma unroll
+    for (int which = 0; which < 2; ++which) {
+        if (!(flags & (which ? A_RK_THIS : A_RK_PREV))) continue;
+#pragma unroll
+        for (int m = 0; m < PF; ++m)
+            rk4_fields<R, NF>(cp, which, kind == 0, kind == 2, v[0][m], v[1][m], v[NF - 1][m]);
+    }
+    if (flags & A_FWD) {
+        column_fft<R, LN2, PF, NF, -1, COLS>(v, s, base, t, a.tw);
+#pragma unroll
+        for (int m = 0; m < PF; ++m) {
+            const Phasor<R> w4 = el32(w4t, q0 + m * step);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) v[f][m] = pmul(v[f][m], w4);
+        }
+    }
+    if (stopped) return;
+#pragma unroll
+    for (int m = 0; m < PF; ++m)
+#pragma unroll
+        for (int f = 0; f < NF; ++f) el32(g, q0 + m * step + f * nt) = v[f][m];
+}
+
 // ---- row tile: row_rows whole rows
 template <typename R, int LN1>
 __device__ __forceinline__ void mid_row_tile(const MidArgs<R> &a, const MidInst &d, int tile, cplx<R> *s)
@@ -164,10 +223,11 @@ __device__ __forceinline__ void mid_row_dispatch(const MidArgs<R> &a, const MidI
 }
 
 // Rows of 2^LO..2^HI points: 5..11, or 12 (FP32).
-template <typename R, int HI> constexpr int mid_min_blocks() { return sizeof(R) == 4 && HI <= 11 ? 4 : 1; }
+template <typename R, int HI, int CR> constexpr int mid_min_blocks() { return sizeof(R) == 4 && HI <= 11 && CR == 0 ? 4 : 1; }
 
-template <typename R, int LO, int HI, int NF>
-__global__ __launch_bounds__(kThreads, (mid_min_blocks<R, HI>())) void mid_pass(MidArgs<R> a)
+// CR: columns of 2^4..2^6 points (0), 2^7 (1) or 2^8 (2).
+template <typename R, int LO, int HI, int NF, int CR>
+__global__ __launch_bounds__(kThreads, (mid_min_blocks<R, HI, CR>())) void mid_pass(MidArgs<R> a)
 {
     extern __shared__ __align__(16) unsigned char lds_raw[];
     const MidTile mt = a.map[blockIdx.x];
@@ -175,7 +235,9 @@ __global__ __launch_bounds__(kThreads, (mid_min_blocks<R, HI>())) void mid_pass(
     const MidInst &d = a.inst[mt.inst];
     if (mt.code >= 0) {
         const Coupling<R> &cp = a.coef[mt.inst];
-        switch (d.log2n2) {
+        if constexpr (CR > 0)
+            return mid_long_column_tile<R, 6 + CR, NF>(a, d, cp, mt.code, reinterpret_cast<cplx<R> *>(lds_raw));
+        else switch (d.log2n2) {
         case 4: return mid_column_tile<R, 4, NF>(a, d, cp, mt.code);
         case 5: return mid_column_tile<R, 5, NF>(a, d, cp, mt.code);
         default: return mid_column_tile<R, 6, NF>(a, d, cp, mt.code);

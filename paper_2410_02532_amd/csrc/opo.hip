@@ -195,15 +195,25 @@ template <typename R> static const void *mixed_fn(int cr, int rr, int nf)
     return nf == 2 ? mixed_fn_nf<R, 2>(cr, rr) : mixed_fn_nf<R, 3>(cr, rr);
 }
 
-// Interior launches of batches (mid_kernels.h) with rows of range rr.
-template <typename R> static const void *mid_fn(int rr, int nf)
+// Launches inside a pass of batches (mid_kernels.h) with columns of range cr and rows of
+// range rr, or null.
+template <typename R, int NF> static const void *mid_fn_nf(int cr, int rr)
 {
-    if constexpr (kMaxLog2N1<R> >= 12)
+    if constexpr (sizeof(R) == 4) {
         if (rr == 2)
-            return nf == 2 ? reinterpret_cast<const void *>(&mid_pass<R, 12, 12, 2>)
-                           : reinterpret_cast<const void *>(&mid_pass<R, 12, 12, 3>);
-    return nf == 2 ? reinterpret_cast<const void *>(&mid_pass<R, 5, 11, 2>)
-                   : reinterpret_cast<const void *>(&mid_pass<R, 5, 11, 3>);
+            return cr == 0   ? reinterpret_cast<const void *>(&mid_pass<R, 12, 12, NF, 0>)
+                   : cr == 1 ? reinterpret_cast<const void *>(&mid_pass<R, 12, 12, NF, 1>)
+                             : reinterpret_cast<const void *>(&mid_pass<R, 12, 12, NF, 2>);
+        return cr == 0 ? reinterpret_cast<const void *>(&mid_pass<R, 5, 11, NF, 0>) : nullptr;
+    } else {
+        return cr == 0   ? reinterpret_cast<const void *>(&mid_pass<R, 5, 11, NF, 0>)
+               : cr == 1 ? reinterpret_cast<const void *>(&mid_pass<R, 5, 11, NF, 1>)
+                         : reinterpret_cast<const void *>(&mid_pass<R, 5, 11, NF, 2>);
+    }
+}
+template <typename R> static const void *mid_fn(int cr, int rr, int nf)
+{
+    return nf == 2 ? mid_fn_nf<R, 2>(cr, rr) : mid_fn_nf<R, 3>(cr, rr);
 }
 
 template <typename R> static const void *team_fn(int nf)
@@ -271,7 +281,7 @@ struct opo_s {
     // batches on the automatic schedule: launches inside a pass run mid_pass. Maps of the
     // mixed launches (column half 0, 1) and of the column tiles of a half alone (2, 3)
     bool mid = false;
-    int mid_rr = 0, mid_nf = 3;      // row range and coupled waves of its kernel
+    int mid_cr = 0, mid_rr = 0, mid_nf = 3;   // column and row range and coupled waves of its kernel
     MidInst *d_mid_inst = nullptr;   // per (crystal, instance)
     MidTile *d_mid_map[4] = {nullptr, nullptr, nullptr, nullptr};
     int mid_len[4] = {0, 0, 0, 0};
@@ -767,7 +777,7 @@ template <typename R> static hipError_t launch_mid(opo_t *h, const StepArgs<R> &
     substep(h->order, map == 0 ? step - 1 : step, z, tau, m.disp_sel);
     void *args[] = {&m};
     HIP_RET(prof_begin(h, map < 2 ? OPO_K_MIXED : OPO_K_COLUMN));
-    HIP_RET(hipLaunchKernel(mid_fn<R>(h->mid_rr, h->mid_nf), dim3(h->mid_len[map]), dim3(kThreads), args, h->mid_lds,
+    HIP_RET(hipLaunchKernel(mid_fn<R>(h->mid_cr, h->mid_rr, h->mid_nf), dim3(h->mid_len[map]), dim3(kThreads), args, h->mid_lds,
                             h->stream));
     return prof_end(h);
 }
@@ -982,7 +992,7 @@ template <typename R> static int setup_kernels(opo_t *h)
                                     static_cast<int>(lds_elems<R>(g.nf << g.ln) * sizeof(cplx<R>))));
     }
     if (h->mid)
-        HIP_TRY(hipFuncSetAttribute(mid_fn<R>(h->mid_rr, h->mid_nf), hipFuncAttributeMaxDynamicSharedMemorySize,
+        HIP_TRY(hipFuncSetAttribute(mid_fn<R>(h->mid_cr, h->mid_rr, h->mid_nf), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     static_cast<int>(h->mid_lds)));
     if (!h->lone.empty())
         HIP_TRY(hipFuncSetAttribute(lone_row_fn<R>(h->lone_ln1), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -1294,31 +1304,44 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
             h->map_len[ch] = static_cast<int>(maps[ch].size());
         }
     }
-    // mid_pass serves the launches inside a pass of a mixed batch on the automatic
-    // schedule whose columns fit a wave's registers (2^4..2^6 points)
+    // mid_pass serves the launches inside a pass of a mixed batch on the automatic schedule
     std::vector<MidTile> mid_maps[4];
-    if (h->mixed && opt.schedule == 0 && h->groups_a[0].ln == 0 && h->groups_a[1].ln == 0 &&
+    if (h->mixed && batched && opt.schedule == 0 && h->groups_a[0].ln == h->groups_a[1].ln &&
         h->groups_a[0].nf == h->groups_a[1].nf && (h->groups_b[0].ln == 2) == (h->groups_b[1].ln == 2)) {
         const bool f64 = opt.precision == OPO_F64;
-        h->mid = batched;
-        for (int i : order)
-            h->mid = h->mid && h->inst[i].log2n2 >= kMidMinLog2N2 && h->inst[i].log2n1 >= 5;
+        h->mid_cr = h->groups_a[0].ln;
         h->mid_rr = h->groups_b[0].ln;
         h->mid_nf = h->groups_a[0].nf;
+        h->mid = (f64 ? mid_fn<double>(h->mid_cr, h->mid_rr, h->mid_nf)
+                      : mid_fn<float>(h->mid_cr, h->mid_rr, h->mid_nf)) != nullptr;
+        for (int i : order)
+            h->mid = h->mid && h->inst[i].log2n2 >= kMidMinLog2N2 && h->inst[i].log2n1 >= 5;
         for (int ch = 0; h->mid && ch < 2; ++ch) {
-            std::vector<MidTile> qc[kXcd], qr[kXcd], none[kXcd];
-            int nc = 0;
+            std::vector<MidTile> cols, rows, qc[kXcd], qr[kXcd], none[kXcd];
             for (int i : order) {
                 const InstDesc &d = h->inst[i];
-                const int rows = f64 ? mid_rows<double>(d.log2n1) : mid_rows<float>(d.log2n1);
-                h->mid_lds = std::max(h->mid_lds, (f64 ? lds_elems<double>(rows << d.log2n1)
-                                                       : lds_elems<float>(rows << d.log2n1)) * h->elem);
-                if (half[i] == ch) {
-                    for (int t = 0; t < d.n1 / mid_cols(d.log2n2); ++t) qc[nc++ % kXcd].push_back({i, t});
-                } else {
-                    for (int t = 0; t < (d.nf * d.n2 + rows - 1) / rows; ++t) qr[t % kXcd].push_back({i, -1 - t});
+                const int per = f64 ? mid_rows<double>(d.log2n1) : mid_rows<float>(d.log2n1);
+                h->mid_lds = std::max(h->mid_lds, (f64 ? lds_elems<double>(per << d.log2n1)
+                                                       : lds_elems<float>(per << d.log2n1)) * h->elem);
+                const int nc = d.n1 / (f64 ? mid_cols<double>(d.log2n2) : mid_cols<float>(d.log2n2));
+                const int nr = (d.nf * d.n2 + per - 1) / per;
+                for (int t = 0; t < (half[i] == ch ? nc : nr); ++t) {
+                    if (half[i] == ch) cols.push_back({i, t});
+                    else rows.push_back({i, -1 - t});
                 }
             }
+            // Row tile t on XCD t mod 8, as in the mixed launches. FP64 and long columns:
+            // tile t of every instance together, columns on XCD t mod 8 too, so that the
+            // tables an XCD's L2 cannot hold are read once for all instances (256-instance
+            // FP64 sweep 30.6 -> 29.4 ms a round trip, 8 x 2^20 in FP32 30.9 -> 29.7; the
+            // FP32 sweep, whose tables stay in the L2, 16.8 -> 17.1: instance by instance)
+            const bool by_tile = f64 || h->mid_cr > 0;
+            if (by_tile) {
+                std::stable_sort(cols.begin(), cols.end(), [](const MidTile &p, const MidTile &q) { return p.code < q.code; });
+                std::stable_sort(rows.begin(), rows.end(), [](const MidTile &p, const MidTile &q) { return p.code > q.code; });
+            }
+            for (size_t q = 0; q < cols.size(); ++q) qc[by_tile ? cols[q].code % kXcd : q % kXcd].push_back(cols[q]);
+            for (const MidTile &m : rows) qr[(-1 - m.code) % kXcd].push_back(m);
             // FP32: the column tiles, which take longer, an eighth ahead, so that the launch
             // ends on row tiles (batched sweep 17.4 -> 17.1 ms, two waves 12.6 -> 12.2; a
             // twelfth or a fifth ahead the same, a tenth behind 17.4 and 12.3; in FP64 0.3 %
@@ -1436,6 +1459,7 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
     }
 
     h->lds_a = max_a * es;
+    if (h->mid_cr > 0) h->mid_lds = std::max(h->mid_lds, h->lds_a);   // columns through LDS
     h->lds_b = (opt.precision == OPO_F64 ? lds_elems<double>(static_cast<int>(max_b))
                                          : lds_elems<float>(static_cast<int>(max_b))) * es;
     if (h->lds_a > 160 * 1024 || h->lds_b > 160 * 1024)

@@ -1,6 +1,6 @@
 """Batches that fill the chip, on the automatic schedule: the launches inside a pass run
-mid_pass (wave-level columns of 2^4..2^6 points, rows of 2^5 up to the longest, couplings
-from a table refilled every 128 step boundaries). Members against the FP64 oracle."""
+mid_pass (wave-level columns of 2^4..2^6 points, columns of 2^7 and 2^8 through LDS, rows of
+2^5 up to the longest, couplings from a table refilled every 128 step boundaries). Members against the FP64 oracle."""
 import sys
 
 import numpy as np
@@ -10,7 +10,7 @@ import torch  # noqa: F401  (imported at collection: the first import can take m
 
 import oracle
 from paper_2410_02532_amd import opo as B
-from test_gpu_lone import TOL, _instance, rel_l2
+from test_gpu_lone import TOL, _instance, phase_rounding, rel_l2
 
 pytestmark = pytest.mark.gpu
 
@@ -24,6 +24,10 @@ CASES = [
     ("f32", 3, [16, 16, 15, 14, 14, 13], 0.4, 1e-17, 2),
     ("f32", 2, [16, 15, 14, 13] * 5, 0.0, 0.0, 4),
     ("f32", 3, [18, 18, 18], 0.4, 0.0, 2),
+    ("f32", 2, [19, 19], 0.4, 1e-17, 2),
+    ("f32", 3, [20, 20], 0.0, 0.0, 4),
+    ("f64", 3, [18, 18], 0.0, 0.0, 2),
+    ("f64", 2, [19, 19], 0.4, 0.0, 2),
     ("f64", 3, [16, 13, 14, 15, 12] * 3, 0.4, 1e-17, 2),
     ("f64", 2, [17, 16, 15, 13] * 3, 0.0, 0.0, 4),
 ]
@@ -42,8 +46,9 @@ def test_batch_round_trips(precision, nf, sizes, dk, n2, order):
         ins = insts[i]
         ref, _ = oracle.roundtrips(dict(ins["crystal"], order=order), ins["cavity"], ins["fields"], ins["pump_in"],
                                    nz, nrt)
+        tol = TOL[precision] + phase_rounding(ins["crystal"], nz * nrt * (3 if order == 4 else 1), 5.0 / nz)
         for x in range(nf):
-            assert rel_l2(got[i][x], ref[x]) <= TOL[precision], (i, x, rel_l2(got[i][x], ref[x]))
+            assert rel_l2(got[i][x], ref[x]) <= tol, (i, x, rel_l2(got[i][x], ref[x]), tol)
 
 
 @pytest.mark.parametrize("precision", ["f64", "f32"])
