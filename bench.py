@@ -233,8 +233,9 @@ def roofline(w, precision, n_rt, graph_rt_s=None):
     Each column, row or mixed launch carries out half of a z-step for the points of the
     two-pass instances it covers (a z-step is a column and a row pass of every such
     instance), so its algorithmic work is half a field-point-step per covered point: 48/2 B
-    (FP32) of HBM traffic and flops_per_unit/2. Instances that run resident are not covered
-    by those launches. The line is priced against HBM (the algorithmic minimum of one read
+    (FP32) of HBM traffic and flops_per_unit/2. A few small instances run a whole crystal
+    pass in one launch (counted as mixed). Instances that run resident are not covered by
+    those launches. The line is priced against HBM (the algorithmic minimum of one read
     and one write of every field per z-step); the VALU figures stand beside it."""
     with B.from_workload(w, precision=precision, profile=True) as h:
         two_pass = [i for i in range(len(instances_of(w))) if not h.plan(i)[2]]
@@ -248,8 +249,11 @@ def roofline(w, precision, n_rt, graph_rt_s=None):
         return resident_roofline(w, precision, per, two_pass, graph_rt_s)
     ms, launches = per[dom]
     insts = [instances_of(w)[i] for i in two_pass]
-    bytes_per_launch = sum(BYTES_PER_FIELD[precision] * nf_of(i) * i["crystal"]["nt"] for i in insts) / 2
-    flops_per_launch = sum(i["crystal"]["nt"] * flops_per_unit(i["crystal"]["nt"], nf_of(i)) for i in insts) / 2
+    # z-steps per launch: a half, or nearly a whole pass where a few small instances run it
+    # in one launch
+    steps = 0.5 if 2 * launches > w["nz"] * n_rt else w["nz"] * n_rt / launches
+    bytes_per_launch = steps * sum(BYTES_PER_FIELD[precision] * nf_of(i) * i["crystal"]["nt"] for i in insts)
+    flops_per_launch = steps * sum(i["crystal"]["nt"] * flops_per_unit(i["crystal"]["nt"], nf_of(i)) for i in insts)
     avg_s = ms / 1e3 / launches
     tflops = flops_per_launch / avg_s / 1e12
     gbs = bytes_per_launch / avg_s / 1e9

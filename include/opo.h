@@ -333,8 +333,9 @@ int opo_get_grid(opo_t *h, int32_t inst, double *t, double *omega);
 int opo_get_plan(opo_t *h, int32_t inst, int32_t *log2_n1, int32_t *log2_n2, int32_t *resident);
 
 /* Kernel classes timed by the profile option: column pass, row pass, energy
- * reduction, the mixed pass that runs the column tiles of one half of a batch
- * together with the row tiles of the other half, and the resident pass (under
+ * reduction, the mixed launches (the column tiles of one half of a batch
+ * together with the row tiles of the other half; for a handle of a few small
+ * instances, the launch that runs a whole crystal pass), and the resident pass (under
  * the profile option it runs before the two-pass launches instead of beside
  * them). */
 enum { OPO_K_COLUMN = 0, OPO_K_ROW = 1, OPO_K_ENERGY = 2, OPO_K_MIXED = 3, OPO_K_RESIDENT = 4, OPO_K_CLASSES = 5 };

@@ -15,8 +15,8 @@
 //
 // Measured per z-step (MI355X, us, two launches of which an empty one costs 1.55):
 // one 2^14 instance 12.7 -> 7.5 in FP32 and 13.6 -> 7.8 in FP64, three two-wave 2^12
-// instances 12.5 -> 6.1, one 2^16 15.9 -> 11.7, one 2^18 28.3 -> 22.3. With the
-// exchanges of the columns through LDS (256 threads, a barrier each) the 2^14 instance
+// instances 12.5 -> 6.1 (shapes that team_pass has taken over, team_kernels.h), one 2^16
+// 15.9 -> 10.8, one 2^18 28.3 -> 21.6. With the exchanges of the columns through LDS (256 threads, a barrier each) the 2^14 instance
 // took 9.5: a radix-2 stage then lasted about 590 cycles, four fifths of them waiting.
 #pragma once
 #include "coupling_table.h"

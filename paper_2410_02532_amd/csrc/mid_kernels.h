@@ -7,12 +7,14 @@
 // wave (no LDS, no barrier), the flags of the boundary, the bounds checks and the FP64
 // coupling phasors are gone (the couplings of every step come from a table), and one
 // map entry names a workgroup's instance and tile (two dependent loads before the
-// fields instead of three): 754 lane-instructions.
+// fields instead of three).
 //
-// Measured (MI355X, ms per round trip of the 256-instance sweeps of 2^12..2^16):
-// FP32 18.1 -> 17.8, two waves 14.0 -> 12.7, FP64 37.1 -> 31.9. The FP32 launch (87 us)
-// issues VALU 70 % of its cycles at 2.9 waves per SIMD; five workgroups per CU instead of
-// four changed nothing, about 9 us of it are its ramp and tail.
+// Measured (MI355X, ms per round trip of the 256-instance sweeps of 2^12..2^16, with the
+// launch order and the row shapes that followed): FP32 18.1 -> 16.5, two waves 14.0 ->
+// 11.8, FP64 37.1 -> 29.4. The FP32 launch takes 3.70e7 wave instructions (742
+// lane-instructions) and issues VALU 75 % of its cycles at four workgroups per CU (five
+// changed nothing); about 9 us of it are its ramp and tail. The FP64 launch issues VALU
+// 37 % of its cycles and moves its fields at 4.3 TB/s (a large copy: 4.85): memory bound.
 #pragma once
 #include "coupling_table.h"
 #include "wave_fft.h"

@@ -13,7 +13,9 @@ windows of about 30 ms. The timing is taken here, once, on the
 target device; the library only looks the result up, so the same shape always
 gets the same schedule (no timing-dependent rounding at run time). The fastest
 candidate of a key wins unless it is within 2 % of the default schedule, which
-then stays.
+then stays. Two-pass candidates run on the column, row and mixed kernels (the
+"two_pass" schedule); where the automatic schedule runs other kernels,
+csrc/schedule.h holds the splits that were timed with those.
 
 Usage (needs the GPU): python -m paper_2410_02532_amd.tune [--out FILE] [--summary FILE]
 """
