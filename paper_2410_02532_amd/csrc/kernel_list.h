@@ -10,14 +10,22 @@
 // Column and row passes, propagator tables and the adaptive-step kernels of
 // real type R (row range 2, rows of 4096 points, exists in FP32 only).
 #define OPO_PASS_KERNELS_COMMON(DECL, R)                                                           \
-    DECL __global__ void column_pass<R, kColRanges[0][0], kColRanges[0][1], 2>(StepArgs<R>);       \
-    DECL __global__ void column_pass<R, kColRanges[0][0], kColRanges[0][1], 3>(StepArgs<R>);       \
-    DECL __global__ void column_pass<R, kColRanges[1][0], kColRanges[1][1], 2>(StepArgs<R>);       \
-    DECL __global__ void column_pass<R, kColRanges[1][0], kColRanges[1][1], 3>(StepArgs<R>);       \
-    DECL __global__ void column_pass<R, kColRanges[2][0], kColRanges[2][1], 2>(StepArgs<R>);       \
-    DECL __global__ void column_pass<R, kColRanges[2][0], kColRanges[2][1], 3>(StepArgs<R>);       \
-    DECL __global__ void row_pass<R, kRowRanges[0][0], kRowRanges[0][1]>(StepArgs<R>);             \
-    DECL __global__ void row_pass<R, kRowRanges[1][0], kRowRanges[1][1]>(StepArgs<R>);             \
+    DECL __global__ void column_pass<R, kColRanges[0][0], kColRanges[0][1], 2, false>(StepArgs<R>);\
+    DECL __global__ void column_pass<R, kColRanges[0][0], kColRanges[0][1], 2, true>(StepArgs<R>); \
+    DECL __global__ void column_pass<R, kColRanges[0][0], kColRanges[0][1], 3, false>(StepArgs<R>);\
+    DECL __global__ void column_pass<R, kColRanges[0][0], kColRanges[0][1], 3, true>(StepArgs<R>); \
+    DECL __global__ void column_pass<R, kColRanges[1][0], kColRanges[1][1], 2, false>(StepArgs<R>);\
+    DECL __global__ void column_pass<R, kColRanges[1][0], kColRanges[1][1], 2, true>(StepArgs<R>); \
+    DECL __global__ void column_pass<R, kColRanges[1][0], kColRanges[1][1], 3, false>(StepArgs<R>);\
+    DECL __global__ void column_pass<R, kColRanges[1][0], kColRanges[1][1], 3, true>(StepArgs<R>); \
+    DECL __global__ void column_pass<R, kColRanges[2][0], kColRanges[2][1], 2, false>(StepArgs<R>);\
+    DECL __global__ void column_pass<R, kColRanges[2][0], kColRanges[2][1], 2, true>(StepArgs<R>); \
+    DECL __global__ void column_pass<R, kColRanges[2][0], kColRanges[2][1], 3, false>(StepArgs<R>);\
+    DECL __global__ void column_pass<R, kColRanges[2][0], kColRanges[2][1], 3, true>(StepArgs<R>); \
+    DECL __global__ void row_pass<R, kRowRanges[0][0], kRowRanges[0][1], false>(StepArgs<R>);      \
+    DECL __global__ void row_pass<R, kRowRanges[0][0], kRowRanges[0][1], true>(StepArgs<R>);       \
+    DECL __global__ void row_pass<R, kRowRanges[1][0], kRowRanges[1][1], false>(StepArgs<R>);      \
+    DECL __global__ void row_pass<R, kRowRanges[1][0], kRowRanges[1][1], true>(StepArgs<R>);       \
     DECL __global__ void disp_table<R>(const InstDesc *, int, Phasor<R> *, double, int);           \
     DECL __global__ void adapt_begin<R>(const InstDesc *, const AdaptState *, int, cplx<R> *,      \
                                         const cplx<R> *, const cplx<R> *, Phasor<R> *);            \
@@ -25,7 +33,8 @@
 
 #define OPO_PASS_KERNELS_F32(DECL)                                                                 \
     OPO_PASS_KERNELS_COMMON(DECL, float)                                                           \
-    DECL __global__ void row_pass<float, kRowRanges[2][0], kRowRanges[2][1]>(StepArgs<float>);
+    DECL __global__ void row_pass<float, kRowRanges[2][0], kRowRanges[2][1], false>(StepArgs<float>);  \
+    DECL __global__ void row_pass<float, kRowRanges[2][0], kRowRanges[2][1], true>(StepArgs<float>);
 
 #define OPO_PASS_KERNELS_F64(DECL) OPO_PASS_KERNELS_COMMON(DECL, double)
 

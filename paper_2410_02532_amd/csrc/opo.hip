@@ -109,29 +109,29 @@ template <size_t K> static int range_of(const int (&ranges)[K][2], int ln)
     return -1;
 }
 
-template <typename R, int NF> static const void *column_fn_nf(int range)
+template <typename R, int NF, bool ADAPT> static const void *column_fn_nf(int range)
 {
     switch (range) {
-    case 0: return reinterpret_cast<const void *>(&column_pass<R, kColRanges[0][0], kColRanges[0][1], NF>);
-    case 1: return reinterpret_cast<const void *>(&column_pass<R, kColRanges[1][0], kColRanges[1][1], NF>);
-    case 2: return reinterpret_cast<const void *>(&column_pass<R, kColRanges[2][0], kColRanges[2][1], NF>);
+    case 0: return reinterpret_cast<const void *>(&column_pass<R, kColRanges[0][0], kColRanges[0][1], NF, ADAPT>);
+    case 1: return reinterpret_cast<const void *>(&column_pass<R, kColRanges[1][0], kColRanges[1][1], NF, ADAPT>);
+    case 2: return reinterpret_cast<const void *>(&column_pass<R, kColRanges[2][0], kColRanges[2][1], NF, ADAPT>);
     default: return nullptr;
     }
 }
 
-template <typename R> static const void *column_fn(int range, int nf)
+template <typename R, bool ADAPT = false> static const void *column_fn(int range, int nf)
 {
-    return nf == 2 ? column_fn_nf<R, 2>(range) : column_fn_nf<R, 3>(range);
+    return nf == 2 ? column_fn_nf<R, 2, ADAPT>(range) : column_fn_nf<R, 3, ADAPT>(range);
 }
 
-template <typename R> static const void *row_fn(int range)
+template <typename R, bool ADAPT = false> static const void *row_fn(int range)
 {
     switch (range) {
-    case 0: return reinterpret_cast<const void *>(&row_pass<R, kRowRanges[0][0], kRowRanges[0][1]>);
-    case 1: return reinterpret_cast<const void *>(&row_pass<R, kRowRanges[1][0], kRowRanges[1][1]>);
+    case 0: return reinterpret_cast<const void *>(&row_pass<R, kRowRanges[0][0], kRowRanges[0][1], ADAPT>);
+    case 1: return reinterpret_cast<const void *>(&row_pass<R, kRowRanges[1][0], kRowRanges[1][1], ADAPT>);
     case 2:
         if constexpr (kMaxLog2N1<R> >= kRowRanges[2][0])
-            return reinterpret_cast<const void *>(&row_pass<R, kRowRanges[2][0], kRowRanges[2][1]>);
+            return reinterpret_cast<const void *>(&row_pass<R, kRowRanges[2][0], kRowRanges[2][1], ADAPT>);
         return nullptr;
     default: return nullptr;
     }
@@ -655,8 +655,8 @@ static hipError_t launch_a(opo_t *h, StepArgs<R> a, int flags, int step, int hal
             a.tile_count = g.count;
             a.inst_only = g.only;
             void *args[] = {&a};
-            HIP_RET(hipLaunchKernel(column_fn<R>(g.ln, g.nf), dim3(g.count, a.alt_state ? 2 : 1), dim3(kThreads), args, h->lds_a,
-                                    h->stream));
+            HIP_RET(hipLaunchKernel(a.adapt ? column_fn<R, true>(g.ln, g.nf) : column_fn<R>(g.ln, g.nf),
+                                    dim3(g.count, a.alt_state ? 2 : 1), dim3(kThreads), args, h->lds_a, h->stream));
         }
     return prof_end(h);
 }
@@ -676,7 +676,8 @@ static hipError_t launch_b(opo_t *h, StepArgs<R> a, int flags, int step = 0, int
             a.tile_count = g.count;
             a.inst_only = g.only;
             void *args[] = {&a};
-            HIP_RET(hipLaunchKernel(row_fn<R>(g.ln), dim3(g.count, a.alt_state ? 2 : 1), dim3(kThreads), args, h->lds_b, h->stream));
+            HIP_RET(hipLaunchKernel(a.adapt ? row_fn<R, true>(g.ln) : row_fn<R>(g.ln),
+                                    dim3(g.count, a.alt_state ? 2 : 1), dim3(kThreads), args, h->lds_b, h->stream));
         }
     return prof_end(h);
 }
@@ -970,22 +971,21 @@ template <typename R> static hipError_t enqueue_roundtrip(opo_t *h)
 
 template <typename R> static int setup_kernels(opo_t *h)
 {
-    for (const Group &g : h->groups_a) {
-        if (!column_fn<R>(g.ln, g.nf)) return fail(OPO_EINVAL, "internal: no column kernel for this size");
-        HIP_TRY(hipFuncSetAttribute(column_fn<R>(g.ln, g.nf), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    static_cast<int>(h->lds_a)));
-    }
-    for (const Group &g : h->groups_b) {
-        if (!row_fn<R>(g.ln)) return fail(OPO_EINVAL, "internal: no row kernel for this size");
-        HIP_TRY(hipFuncSetAttribute(row_fn<R>(g.ln), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    static_cast<int>(h->lds_b)));
-    }
-    for (const Group &g : h->res_groups_a)
-        HIP_TRY(hipFuncSetAttribute(column_fn<R>(g.ln, g.nf), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    static_cast<int>(h->lds_a)));
-    for (const Group &g : h->res_groups_b)
-        HIP_TRY(hipFuncSetAttribute(row_fn<R>(g.ln), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    static_cast<int>(h->lds_b)));
+    auto lds = [](const void *fn, size_t bytes) {
+        return hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, static_cast<int>(bytes));
+    };
+    for (const auto *groups : {&h->groups_a, &h->res_groups_a})
+        for (const Group &g : *groups) {
+            if (!column_fn<R>(g.ln, g.nf)) return fail(OPO_EINVAL, "internal: no column kernel for this size");
+            HIP_TRY(lds(column_fn<R>(g.ln, g.nf), h->lds_a));
+            HIP_TRY((lds(column_fn<R, true>(g.ln, g.nf), h->lds_a)));
+        }
+    for (const auto *groups : {&h->groups_b, &h->res_groups_b})
+        for (const Group &g : *groups) {
+            if (!row_fn<R>(g.ln)) return fail(OPO_EINVAL, "internal: no row kernel for this size");
+            HIP_TRY(lds(row_fn<R>(g.ln), h->lds_b));
+            HIP_TRY((lds(row_fn<R, true>(g.ln), h->lds_b)));
+        }
     for (const Group &g : h->res_launch) {
         if (!resident_fn<R>(g.ln, g.nf)) return fail(OPO_EINVAL, "internal: no resident kernel for this size");
         HIP_TRY(hipFuncSetAttribute(resident_fn<R>(g.ln, g.nf), hipFuncAttributeMaxDynamicSharedMemorySize,
