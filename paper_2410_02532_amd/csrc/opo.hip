@@ -1304,7 +1304,16 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
             h->map_len[ch] = static_cast<int>(maps[ch].size());
         }
     }
-    // mid_pass serves the launches inside a pass of a mixed batch on the automatic schedule
+    // mid_pass serves the launches inside a pass of a mixed batch on the automatic schedule.
+    // FP32 batches whose fields exceed the 256 MB of the last cache level are bound by
+    // memory, and only those of short columns and long rows gain there (us per z-step,
+    // mixed_pass / here: 2^16 x 256 547 / 509, 2^18 x 64 663 / 609, two waves 2^17 x 160
+    // 554 / 483, but 2^20 x 12 523 / 537, 2^15 x 400 398 / 408); FP64 gains everywhere
+    // (2^16 x 200 749 / 610)
+    constexpr long long kLastCache = 256LL << 20;
+    const long long state = total_points * (opt.precision == OPO_F64 ? 16 : 8);
+    bool long_rows = true;   // of 2^10 points or more
+    for (int i : order) long_rows = long_rows && h->inst[i].log2n1 >= 10;
     std::vector<MidTile> mid_maps[4];
     if (h->mixed && batched && opt.schedule == 0 && h->groups_a[0].ln == h->groups_a[1].ln &&
         h->groups_a[0].nf == h->groups_a[1].nf && (h->groups_b[0].ln == 2) == (h->groups_b[1].ln == 2)) {
@@ -1314,6 +1323,7 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
         h->mid_nf = h->groups_a[0].nf;
         h->mid = (f64 ? mid_fn<double>(h->mid_cr, h->mid_rr, h->mid_nf)
                       : mid_fn<float>(h->mid_cr, h->mid_rr, h->mid_nf)) != nullptr;
+        h->mid = h->mid && (f64 || state <= kLastCache || (long_rows && h->mid_cr == 0));
         for (int i : order)
             h->mid = h->mid && h->inst[i].log2n2 >= kMidMinLog2N2 && h->inst[i].log2n1 >= 5;
         for (int ch = 0; h->mid && ch < 2; ++ch) {
@@ -1330,12 +1340,15 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
                     else rows.push_back({i, -1 - t});
                 }
             }
-            // Row tile t on XCD t mod 8, as in the mixed launches. FP64 and long columns:
-            // tile t of every instance together, columns on XCD t mod 8 too, so that the
-            // tables an XCD's L2 cannot hold are read once for all instances (256-instance
-            // FP64 sweep 30.6 -> 29.4 ms a round trip, 8 x 2^20 in FP32 30.9 -> 29.7; the
-            // FP32 sweep, whose tables stay in the L2, 16.8 -> 17.1: instance by instance)
-            const bool by_tile = f64 || h->mid_cr > 0;
+            // Row tile t on XCD t mod 8, as in the mixed launches. Long columns, and FP64
+            // where the fields just exceed the last cache level: tile t of every instance
+            // together, columns on XCD t mod 8 too, so that the tables an XCD's L2 cannot
+            // hold are read once for all instances; else instance by instance. Measured, by
+            // instance / by tile: 8 x 2^20 in FP32 30.9 / 29.7 ms a round trip, the FP32 sweep
+            // 16.8 / 17.1; FP64, us a z-step: 2^12..2^15 x 256 (188 MB) 141 / 147, 2^12..2^16
+            // x 200 (244 MB) 189 / 193, x 256 (316 MB) 302 / 296, 2^13 x 700 (275 MB) 251 / 230,
+            // 2^13..2^16 x 256 (377 MB) 367 / 380, 2^16 x 200 (629 MB) 610 / 650
+            const bool by_tile = h->mid_cr > 0 || (f64 && state > kLastCache && state <= kLastCache * 5 / 4);
             if (by_tile) {
                 std::stable_sort(cols.begin(), cols.end(), [](const MidTile &p, const MidTile &q) { return p.code < q.code; });
                 std::stable_sort(rows.begin(), rows.end(), [](const MidTile &p, const MidTile &q) { return p.code > q.code; });
@@ -1345,8 +1358,10 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
             // FP32: the column tiles, which take longer, an eighth ahead, so that the launch
             // ends on row tiles (batched sweep 17.4 -> 17.1 ms, two waves 12.6 -> 12.2; a
             // twelfth or a fifth ahead the same, a tenth behind 17.4 and 12.3; in FP64 0.3 %
-            // slower)
-            mid_maps[ch] = interleave(qc, qr, f64 ? 8 : 9);
+            // slower). Not where all rows are long and take the longer themselves (us a z-step,
+            // in proportion / ahead: two waves 2^16 x 60 79 / 100, 2^17 x 30 86 / 117, 2^18 x
+            // 16 99 / 129; three waves the same; 2^15 and 2^16 together, two waves, 75 / 73)
+            mid_maps[ch] = interleave(qc, qr, f64 || long_rows ? 8 : 9);
             mid_maps[2 + ch] = interleave(qc, none);
         }
     }
