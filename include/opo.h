@@ -149,10 +149,12 @@ typedef struct {
                                the chip and has few instances (up to 48, of 2^10
                                points or more and one field count) runs two
                                passes through kernels of its own, made for
-                               latency. One shape in one kind of handle always
-                               gets the same schedule; an instance alone and the
-                               same instance in a larger handle may differ in
-                               rounding;
+                               latency. Equal instances of one handle always agree
+                               bit for bit. The kernels and splits of a handle
+                               also follow from what else is in it (its size, the
+                               shapes and field counts together), so an instance
+                               alone and the same instance in a larger or another
+                               handle may differ in rounding;
                                1 = two passes per z-step (column and row tiles of
                                a four-step FFT) for every instance;
                                2 = resident where served: one workgroup holds an

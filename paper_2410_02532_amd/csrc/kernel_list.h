@@ -91,6 +91,8 @@
 
 #define OPO_MID_KERNELS_F32(DECL)                                                                  \
     OPO_MID_KERNELS(DECL, float)                                                                   \
+    DECL __global__ void edge_pass<float, 2>(StepArgs<float>, MidArgs<float>);                     \
+    DECL __global__ void edge_pass<float, 3>(StepArgs<float>, MidArgs<float>);                     \
     DECL __global__ void mid_pass<float, 12, 12, 2, 0>(MidArgs<float>);                            \
     DECL __global__ void mid_pass<float, 12, 12, 3, 0>(MidArgs<float>);                            \
     DECL __global__ void mid_pass<float, 12, 12, 2, 1>(MidArgs<float>);                            \

@@ -248,4 +248,25 @@ __global__ __launch_bounds__(kThreads, (mid_min_blocks<R, HI, CR>())) void mid_p
     mid_row_dispatch<R, LO, HI>(a, d, -1 - mt.code, reinterpret_cast<cplx<R> *>(lds_raw));
 }
 
+// The mixed launches at the ends of a round trip where mid_pass's rows differ from
+// mixed_pass's (FP32 rows of 1024 and 2048 points, mid_row_pf): column tiles with the
+// flags of the boundary (column_tile, global tile numbers) and row tiles of mid_pass. The
+// halves of a batch are a launch apart, so only one half's rows of a step fall into such a
+// launch: with the same transform in both, equal members agree bit for bit whichever half
+// they were dealt to.
+template <typename R, int NF>
+__global__ __launch_bounds__(kThreads, OPO_MIXED_MIN_BLOCKS) void edge_pass(StepArgs<R> ac, MidArgs<R> ar)
+{
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    __shared__ Coupling<R> cpl;
+    __shared__ double red[3 * kThreads / 64];
+    cplx<R> *s = reinterpret_cast<cplx<R> *>(lds_raw);
+    const MidTile mt = ar.map[blockIdx.x];
+    if (mt.inst < 0) return;
+    if (mt.code >= 0)
+        column_dispatch<R, kColRanges[0][0], kColRanges[0][1], NF, false>(ac, ac.inst[mt.inst], mt.code, s, &cpl, red);
+    else
+        mid_row_dispatch<R, 5, 11>(ar, ar.inst[mt.inst], -1 - mt.code, s);
+}
+
 } // namespace opo

@@ -45,6 +45,7 @@ static int fail(int code, const std::string &msg)
 
 static constexpr int kHistChunk = 1024;   // round trips buffered on the device per read-back
 static constexpr int kCoefChunk = 128;    // step boundaries whose couplings are held (mid launches)
+static constexpr int kMidMaps = 6;        // maps of mid_pass and edge_pass, see opo_s::mid
 static constexpr double kTwoPi = 6.283185307179586476925286766559;
 static constexpr double kPi = 3.1415926535897932384626433832795;
 
@@ -216,6 +217,13 @@ template <typename R> static const void *mid_fn(int cr, int rr, int nf)
     return nf == 2 ? mid_fn_nf<R, 2>(cr, rr) : mid_fn_nf<R, 3>(cr, rr);
 }
 
+// Mixed launches at the ends of a round trip of such batches, FP32.
+static const void *edge_fn(int nf)
+{
+    return nf == 2 ? reinterpret_cast<const void *>(&edge_pass<float, 2>)
+                   : reinterpret_cast<const void *>(&edge_pass<float, 3>);
+}
+
 template <typename R> static const void *team_fn(int nf)
 {
     return nf == 2 ? reinterpret_cast<const void *>(&team_pass<R, 2>) : reinterpret_cast<const void *>(&team_pass<R, 3>);
@@ -278,13 +286,15 @@ struct opo_s {
     bool mixed = false;              // two halves a launch apart, mixed launches
     int *d_map[2] = {nullptr, nullptr};  // workgroup -> tile maps of the two mixed launches
     int map_len[2] = {0, 0};
-    // batches on the automatic schedule: launches inside a pass run mid_pass. Maps of the
-    // mixed launches (column half 0, 1) and of the column tiles of a half alone (2, 3)
-    bool mid = false;
+    // batches on the automatic schedule: launches inside a pass run mid_pass, and with
+    // `edge` the mixed launches at the ends of a round trip run edge_pass. Maps of mid_pass's
+    // mixed launches (column half 0, 1), of the column tiles of a half alone (2, 3) and of
+    // edge_pass (4, 5)
+    bool mid = false, edge = false;
     int mid_cr = 0, mid_rr = 0, mid_nf = 3;   // column and row range and coupled waves of its kernel
     MidInst *d_mid_inst = nullptr;   // per (crystal, instance)
-    MidTile *d_mid_map[4] = {nullptr, nullptr, nullptr, nullptr};
-    int mid_len[4] = {0, 0, 0, 0};
+    MidTile *d_mid_map[kMidMaps] = {};
+    int mid_len[kMidMaps] = {};
     void *d_coef = nullptr;          // couplings of kCoefChunk step boundaries, per instance
     size_t mid_lds = 0;
     int *d_tile_a = nullptr, *d_tile_b = nullptr;
@@ -546,10 +556,11 @@ static void release(opo_t *h)
         if (st) (void)hipStreamDestroy(st);
     void *bufs[] = {h->d_res_inst, h->d_w4tab, h->pump, h->d_inst, h->d_tile_a, h->d_tile_b, h->d_tw, h->d_disp, h->d_map[0], h->d_map[1],
                     h->d_partial, h->d_hist, h->d_counter, h->spec_buf, h->d_record, h->d_snap,
-                    h->a_uc, h->a_uf, h->a_tab, h->d_actl, h->d_team, h->d_mid_inst, h->d_coef,
-                    h->d_mid_map[0], h->d_mid_map[1], h->d_mid_map[2], h->d_mid_map[3]};
+                    h->a_uc, h->a_uf, h->a_tab, h->d_actl, h->d_team, h->d_mid_inst, h->d_coef};
     for (void *b : bufs)
         if (b) (void)hipFree(b);
+    for (MidTile *m : h->d_mid_map)
+        if (m) (void)hipFree(m);
     for (hipEvent_t e : h->events)
         if (e) (void)hipEventDestroy(e);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
@@ -718,9 +729,30 @@ static hipError_t join_resident(opo_t *h)
     return hipSuccess;
 }
 
+// Arguments of a mid_pass or edge_pass launch over map `map`: the column tiles of a half
+// (flags, step boundary step) and, for the mixed launches, the row tiles of the other half,
+// which is a launch ahead (column half 0) or behind (1).
+template <typename R>
+static MidArgs<R> mid_args(const opo_t *h, const StepArgs<R> &a, int map, int flags, int step, int stage)
+{
+    MidArgs<R> m{};
+    m.state = a.state;
+    m.tw = a.tw;
+    m.w4tab = a.w4tab;
+    m.disp = a.disp;
+    m.counter = a.counter;
+    m.inst = h->d_mid_inst + static_cast<size_t>(stage) * h->n_inst;
+    m.coef = static_cast<const Coupling<R> *>(h->d_coef) + static_cast<size_t>(step % kCoefChunk) * h->n_inst;
+    m.map = h->d_mid_map[map];
+    m.flags = flags;
+    double z, tau;
+    substep(h->order, map % 2 == 0 ? step - 1 : step, z, tau, m.disp_sel);
+    return m;
+}
+
 // Column tiles of half `ch` (flags, step) with the row tiles (B_DISP) of the
 // other half, in one launch.
-template <typename R> static hipError_t launch_mixed(opo_t *h, StepArgs<R> a, int ch, int cflags, int step)
+template <typename R> static hipError_t launch_mixed(opo_t *h, StepArgs<R> a, int ch, int cflags, int step, int stage)
 {
     const Group &gc = h->groups_a[ch], &gr = h->groups_b[1 - ch];
     StepArgs<R> ac = a, ar = a;
@@ -729,6 +761,14 @@ template <typename R> static hipError_t launch_mixed(opo_t *h, StepArgs<R> a, in
     set_half_steps<R>(h, ac, step);
     ac.tile0 = gc.tile0;
     ac.tile_count = gc.count;
+    if (h->edge) {
+        MidArgs<R> m = mid_args<R>(h, a, 4 + ch, 0, step, stage);
+        void *args[] = {&ac, &m};
+        HIP_RET(prof_begin(h, OPO_K_MIXED));
+        HIP_RET(hipLaunchKernel(edge_fn(gc.nf), dim3(h->mid_len[4 + ch]), dim3(kThreads), args,
+                                std::max(h->lds_a, h->mid_lds), h->stream));
+        return prof_end(h);
+    }
     ac.block_map = h->d_map[ch];
     ar.tile_inst = h->d_tile_b;
     ar.flags = B_DISP;
@@ -759,23 +799,10 @@ template <typename R> static hipError_t fill_couplings(opo_t *h, const StepArgs<
     return hipGetLastError();
 }
 
-// Launch of map `map` inside a pass: the column tiles of a half (flags, step boundary
-// step) and, for maps 0 and 1, the row tiles of the other half, which is a launch ahead
-// (half 0) or behind (half 1).
+// Launch of map `map` inside a pass (see mid_args).
 template <typename R> static hipError_t launch_mid(opo_t *h, const StepArgs<R> &a, int map, int flags, int step, int stage)
 {
-    MidArgs<R> m{};
-    m.state = a.state;
-    m.tw = a.tw;
-    m.w4tab = a.w4tab;
-    m.disp = a.disp;
-    m.counter = a.counter;
-    m.inst = h->d_mid_inst + static_cast<size_t>(stage) * h->n_inst;
-    m.coef = static_cast<const Coupling<R> *>(h->d_coef) + static_cast<size_t>(step % kCoefChunk) * h->n_inst;
-    m.map = h->d_mid_map[map];
-    m.flags = flags;
-    double z, tau;
-    substep(h->order, map == 0 ? step - 1 : step, z, tau, m.disp_sel);
+    MidArgs<R> m = mid_args<R>(h, a, map, flags, step, stage);
     void *args[] = {&m};
     HIP_RET(prof_begin(h, map < 2 ? OPO_K_MIXED : OPO_K_COLUMN));
     HIP_RET(hipLaunchKernel(mid_fn<R>(h->mid_cr, h->mid_rr, h->mid_nf), dim3(h->mid_len[map]), dim3(kThreads), args, h->mid_lds,
@@ -890,7 +917,7 @@ static hipError_t enqueue_pass(opo_t *h, StepArgs<R> a, int nz_steps, int first,
                 }
                 return launch_mid<R>(h, a, rows ? half : 2 + half, flags, step, stage);
             }
-            return rows ? launch_mixed<R>(h, a, half, flags, step) : launch_a<R>(h, a, flags, step, half);
+            return rows ? launch_mixed<R>(h, a, half, flags, step, stage) : launch_a<R>(h, a, flags, step, half);
         };
         const int open = first | A_RK_THIS | A_FWD, close = A_INV | A_RK_PREV | last;
         HIP_RET(columns(0, false, open, 0));
@@ -997,7 +1024,9 @@ template <typename R> static int setup_kernels(opo_t *h)
     if (!h->lone.empty())
         HIP_TRY(hipFuncSetAttribute(lone_row_fn<R>(h->lone_ln1), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     static_cast<int>(h->lone_lds_b)));
-    if (h->mixed)
+    if (h->edge)
+        HIP_TRY(lds(edge_fn(h->mid_nf), std::max(h->lds_a, h->mid_lds)));
+    if (h->mixed && !h->edge)
         for (int hf = 0; hf < 2; ++hf) {
             const Group &gc = h->groups_a[1 - hf];
             HIP_TRY(hipFuncSetAttribute(mixed_fn<R>(gc.ln, h->groups_b[hf].ln, gc.nf),
@@ -1314,7 +1343,7 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
     const long long state = total_points * (opt.precision == OPO_F64 ? 16 : 8);
     bool long_rows = true;   // of 2^10 points or more
     for (int i : order) long_rows = long_rows && h->inst[i].log2n1 >= 10;
-    std::vector<MidTile> mid_maps[4];
+    std::vector<MidTile> mid_maps[kMidMaps];
     if (h->mixed && batched && opt.schedule == 0 && h->groups_a[0].ln == h->groups_a[1].ln &&
         h->groups_a[0].nf == h->groups_a[1].nf && (h->groups_b[0].ln == 2) == (h->groups_b[1].ln == 2)) {
         const bool f64 = opt.precision == OPO_F64;
@@ -1363,6 +1392,14 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
             // 16 99 / 129; three waves the same; 2^15 and 2^16 together, two waves, 75 / 73)
             mid_maps[ch] = interleave(qc, qr, f64 || long_rows ? 8 : 9);
             mid_maps[2 + ch] = interleave(qc, none);
+            // FP32 kernels of rows up to 2^11 points, where mid_row_pf differs from row_pf
+            h->edge = !f64 && h->mid_rr != 2;
+            if (h->edge) {
+                std::vector<MidTile> ec[kXcd];
+                const Group &gc = h->groups_a[ch];
+                for (int t = 0; t < gc.count; ++t) ec[t % kXcd].push_back({tile_a_inst[gc.tile0 + t], gc.tile0 + t});
+                mid_maps[4 + ch] = interleave(ec, qr);
+            }
         }
     }
 
@@ -1435,7 +1472,8 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
         hipMalloc(reinterpret_cast<void **>(&h->d_hist),
                   static_cast<size_t>(kHistChunk) * n * 3 * sizeof(double)) != hipSuccess ||
         hipMalloc(reinterpret_cast<void **>(&h->d_counter), 8 * sizeof(int)) != hipSuccess ||
-        (h->mixed && (hipMalloc(reinterpret_cast<void **>(&h->d_map[0]), maps[0].size() * sizeof(int)) != hipSuccess ||
+        (h->mixed && !h->edge &&
+                     (hipMalloc(reinterpret_cast<void **>(&h->d_map[0]), maps[0].size() * sizeof(int)) != hipSuccess ||
                       hipMalloc(reinterpret_cast<void **>(&h->d_map[1]), maps[1].size() * sizeof(int)) != hipSuccess)))
         return bail(fail(OPO_ENOMEM, "hipMalloc of the tables failed"));
 
@@ -1454,7 +1492,7 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
         const size_t cb = opt.precision == OPO_F64 ? sizeof(Coupling<double>) : sizeof(Coupling<float>);
         bool ok = hipMalloc(reinterpret_cast<void **>(&h->d_mid_inst), mid_inst.size() * sizeof(MidInst)) == hipSuccess &&
                   hipMalloc(&h->d_coef, (kCoefChunk + 1) * cb * n) == hipSuccess;
-        for (int q = 0; q < 4; ++q) {
+        for (int q = 0; q < (h->edge ? kMidMaps : 4); ++q) {
             h->mid_len[q] = static_cast<int>(mid_maps[q].size());
             ok = ok && hipMalloc(reinterpret_cast<void **>(&h->d_mid_map[q]), mid_maps[q].size() * sizeof(MidTile)) == hipSuccess;
         }
@@ -1495,8 +1533,8 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
             hipSuccess ||
         hipMemcpyAsync(h->d_tile_a, tile_a_inst.data(), tile_a_inst.size() * sizeof(int), hipMemcpyHostToDevice, st) != hipSuccess ||
         hipMemcpyAsync(h->d_tile_b, tile_b_inst.data(), tile_b_inst.size() * sizeof(int), hipMemcpyHostToDevice, st) != hipSuccess ||
-        (h->mixed && hipMemcpyAsync(h->d_map[0], maps[0].data(), maps[0].size() * sizeof(int), hipMemcpyHostToDevice, st) != hipSuccess) ||
-        (h->mixed && hipMemcpyAsync(h->d_map[1], maps[1].data(), maps[1].size() * sizeof(int), hipMemcpyHostToDevice, st) != hipSuccess) ||
+        (h->mixed && !h->edge && hipMemcpyAsync(h->d_map[0], maps[0].data(), maps[0].size() * sizeof(int), hipMemcpyHostToDevice, st) != hipSuccess) ||
+        (h->mixed && !h->edge && hipMemcpyAsync(h->d_map[1], maps[1].data(), maps[1].size() * sizeof(int), hipMemcpyHostToDevice, st) != hipSuccess) ||
         (!res_inst.empty() && hipMemcpyAsync(h->d_res_inst, res_inst.data(), res_inst.size() * sizeof(int),
                                              hipMemcpyHostToDevice, st) != hipSuccess) ||
         hipStreamSynchronize(st) != hipSuccess)
@@ -1504,7 +1542,7 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
     if (h->mid) {
         bool ok = hipMemcpyAsync(h->d_mid_inst, mid_inst.data(), mid_inst.size() * sizeof(MidInst), hipMemcpyHostToDevice,
                                  st) == hipSuccess;
-        for (int q = 0; q < 4; ++q)
+        for (int q = 0; q < (h->edge ? kMidMaps : 4); ++q)
             ok = ok && hipMemcpyAsync(h->d_mid_map[q], mid_maps[q].data(), mid_maps[q].size() * sizeof(MidTile),
                                       hipMemcpyHostToDevice, st) == hipSuccess;
         if (!ok || hipStreamSynchronize(st) != hipSuccess)

@@ -92,3 +92,19 @@ def test_batch_beyond_the_last_cache_level(precision, log2nt, count):
         for got in halves:
             for x in range(3):
                 assert rel_l2(got[x], ref[x]) <= tol, (x, rel_l2(got[x], ref[x]), tol)
+
+
+@pytest.mark.parametrize("precision, nf, log2nt, count, nz", [
+    ("f32", 3, 16, 6, 3), ("f32", 3, 17, 4, 2), ("f32", 2, 16, 8, 1), ("f32", 3, 15, 12, 3), ("f64", 3, 16, 6, 3)])
+def test_equal_members_of_both_halves_agree(precision, nf, log2nt, count, nz):
+    """Equal members agree bit for bit whichever half of the batch they were dealt to (the
+    halves' first and last row transforms fall into different launches)."""
+    print("batch members %s nf %d %d of 2^%d nz %d" % (precision, nf, count, log2nt, nz), file=sys.stderr, flush=True)
+    insts = _batch([log2nt], nf, 0.0, 0.0) * count
+    insts[0]["crystal"]["length_mm"] = float(nz)
+    with B.Opo(insts, nz, precision=precision) as h:
+        h.cavity_roundtrip(2)
+        first, energies = h.get_fields(0), h.energy_history(0)
+        for i in range(1, count):
+            assert np.array_equal(h.get_fields(i), first), i
+            assert np.array_equal(h.energy_history(i), energies), i
