@@ -212,7 +212,14 @@ int opo_init_batch(opo_t **h, int32_t n, const opo_fields_t *fields,
 /* One crystal pass of nz symmetrized SSFM steps of size dz [mm] (Eq. 11) for
  * every instance, continuing z from the end of the previous call (so two calls
  * of nz/2 equal one of nz). No cavity operation. Asynchronous on the handle's
- * stream; opo_sync waits. */
+ * stream; opo_sync waits.
+ * On a handle of few small instances (see opo_options_t.schedule) workgroups wait for
+ * one another inside the pass. Such a wait gives up after about ten seconds without
+ * progress (the device is stopped or shared far beyond its time): the fields are then
+ * undefined, and the next call that waits for the stream (opo_sync, opo_get_fields,
+ * ssfm_propagate_adaptive) returns OPO_EDEVICE once. The handle can be used again
+ * once every field is set; opo_set_progress also drops a report not yet made.
+ * cavity_roundtrip returns OPO_EDEVICE for it and stops as for a non-finite result. */
 int ssfm_propagate(opo_t *h, int32_t nz, double dz);
 
 /* Propagation of every instance over length_mm [mm] from the handle's z with

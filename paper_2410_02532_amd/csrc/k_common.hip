@@ -76,14 +76,16 @@ __global__ __launch_bounds__(kThreads) void adapt_control(const InstDesc *inst, 
 
 __global__ __launch_bounds__(kThreads) void energy_reduce(const InstDesc *inst, int n_inst,
                                                           const double *partial, double *hist,
-                                                          int *counter, int capacity)
+                                                          int *counter, int capacity, const int *failed)
 {
     __shared__ int bad;
     if (counter[2] != 0) return;     // stopped by an earlier round trip of this call
     const int slot = counter[0];
     if (threadIdx.x == 0) bad = counter[3];
     __syncthreads();
-    bool mine = false;
+    // (read across the host link, by a thread that has no instance to add up: such handles
+    // are small)
+    bool mine = failed && threadIdx.x == kThreads - 1 && *failed != 0;
     for (int ii = threadIdx.x; ii < n_inst; ii += kThreads) {
         const InstDesc &d = inst[ii];
         double e[3] = {0.0, 0.0, 0.0};
@@ -116,7 +118,6 @@ __global__ void set_counter(int *counter, int slot, int rt, int clear_flags)
         if (clear_flags) {
             counter[2] = 0;
             counter[3] = 0;
-            counter[4] = 0;
         }
     }
 }

@@ -306,8 +306,8 @@ struct opo_s {
     double *d_partial = nullptr;
     double *d_hist = nullptr;
     int *d_counter = nullptr;        // [0] history slot in the chunk, [1] round trips completed,
-                                     // [2] stop flag, [3] non-finite boundary value (ssfm_kernels.h),
-                                     // [4] a wait of team_pass gave up
+                                     // [2] stop flag, [3] non-finite boundary value (ssfm_kernels.h)
+    int *team_failed = nullptr;      // pinned host memory: a wait of team_pass gave up, see team_check
     void *d_snap = nullptr;          // state at the start of the current round trip
     void *d_record = nullptr;        // [record_cap][state] fields leaving the crystal per round trip
     int record_cap = 0;
@@ -561,6 +561,7 @@ static void release(opo_t *h)
         if (b) (void)hipFree(b);
     for (MidTile *m : h->d_mid_map)
         if (m) (void)hipFree(m);
+    if (h->team_failed) (void)hipHostFree(h->team_failed);
     for (hipEvent_t e : h->events)
         if (e) (void)hipEventDestroy(e);
     if (h->own_stream && h->stream) (void)hipStreamDestroy(h->stream);
@@ -873,7 +874,7 @@ static hipError_t launch_team(opo_t *h, const StepArgs<R> &a, int s0, int begin,
     t.counter = a.counter;
     t.coef = static_cast<const Coupling<R> *>(h->d_coef);
     t.sync = h->d_team;
-    t.failed = h->d_counter + 4;
+    t.failed = h->team_failed;
     t.n = h->n_inst;
     t.count = static_cast<int>(h->lone.size());
     t.begin = begin;
@@ -991,7 +992,7 @@ template <typename R> static hipError_t enqueue_roundtrip(opo_t *h)
     HIP_RET(join_resident(h));
     HIP_RET(prof_begin(h, OPO_K_ENERGY));
     energy_reduce<<<1, kThreads, 0, h->stream>>>(h->d_inst, h->n_inst, h->d_partial, h->d_hist,
-                                                 h->d_counter, kHistChunk);
+                                                 h->d_counter, kHistChunk, h->team_failed);
     HIP_RET(hipGetLastError());
     return prof_end(h);
 }
@@ -1471,7 +1472,7 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
         hipMalloc(reinterpret_cast<void **>(&h->d_partial), h->tiles_a * 3 * sizeof(double)) != hipSuccess ||
         hipMalloc(reinterpret_cast<void **>(&h->d_hist),
                   static_cast<size_t>(kHistChunk) * n * 3 * sizeof(double)) != hipSuccess ||
-        hipMalloc(reinterpret_cast<void **>(&h->d_counter), 8 * sizeof(int)) != hipSuccess ||
+        hipMalloc(reinterpret_cast<void **>(&h->d_counter), 4 * sizeof(int)) != hipSuccess ||
         (h->mixed && !h->edge &&
                      (hipMalloc(reinterpret_cast<void **>(&h->d_map[0]), maps[0].size() * sizeof(int)) != hipSuccess ||
                       hipMalloc(reinterpret_cast<void **>(&h->d_map[1]), maps[1].size() * sizeof(int)) != hipSuccess)))
@@ -1480,9 +1481,11 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
     if (!h->lone.empty()) {
         const size_t cb = opt.precision == OPO_F64 ? sizeof(Coupling<double>) : sizeof(Coupling<float>);
         if ((h->team &&
-             hipMalloc(reinterpret_cast<void **>(&h->d_team), sizeof(TeamSync) * h->lone.size()) != hipSuccess) ||
+             (hipMalloc(reinterpret_cast<void **>(&h->d_team), sizeof(TeamSync) * h->lone.size()) != hipSuccess ||
+              hipHostMalloc(reinterpret_cast<void **>(&h->team_failed), sizeof(int), hipHostMallocDefault) != hipSuccess)) ||
             hipMalloc(&h->d_coef, (kCoefChunk + 1) * cb * n) != hipSuccess)
             return bail(fail(OPO_ENOMEM, "hipMalloc of the lone instances' tables failed"));
+        if (h->team_failed) *h->team_failed = 0;
     }
     std::vector<MidInst> mid_inst;
     if (h->mid) {
@@ -1620,6 +1623,20 @@ static int check(opo_t *h)
     return OPO_OK;
 }
 
+// With the handle's stream idle: whether a wait of team_pass gave up since the last call
+// of this; clears the flag.
+static bool take_failed(opo_t *h)
+{
+    return h->team_failed && __atomic_exchange_n(h->team_failed, 0, __ATOMIC_RELAXED) != 0;
+}
+
+// For a call that has waited for the handle's stream: reports such a wait.
+static int team_check(opo_t *h)
+{
+    if (!take_failed(h)) return OPO_OK;
+    return fail(OPO_EDEVICE, "a wait inside ssfm_propagate gave up: the fields are undefined");
+}
+
 // Fill the linear-propagator tables for a step dz (mode > 0) or for each
 // instance's own L/nz (mode 0), unless they already hold that step.
 template <typename R> static int ensure_tables(opo_t *h, double mode)
@@ -1717,6 +1734,7 @@ static int adaptive_impl(opo_t *h, double length, double tol, double dz0, int ma
                          int32_t *rejected, double *z_end)
 {
     const size_t n_elem = h->state_bytes / h->elem;
+    int trc = OPO_OK;
     if (!h->a_uc) {
         long long max_n = 0;
         for (const InstDesc &d : h->inst)
@@ -1761,6 +1779,8 @@ static int adaptive_impl(opo_t *h, double length, double tol, double dz0, int ma
     HIP_TRY(hipMemcpyAsync(ctl.data(), h->d_actl, ctl.size() * sizeof(AdaptState), hipMemcpyDeviceToHost,
                            h->stream));
     HIP_TRY(hipStreamSynchronize(h->stream));
+    trc = team_check(h);
+    if (trc) return trc;
     for (;;) {
         // attempts the slowest running instance needs at least: its steps
         // growing by 2^(1/3) each time reach the end after n with
@@ -1812,10 +1832,10 @@ static int adaptive_impl(opo_t *h, double length, double tol, double dz0, int ma
 
 // Round trips in chunks of up to kHistChunk graph replays, the energy rows of
 // each chunk read back at its end. A round trip with non-finite energies (or
-// a non-finite value stored at its end) sets the device stop flag: every later
-// launch of the call stores nothing, the round trip's row is not counted, and
-// the state is restored from the snapshot its refresh launch took, i.e. to the
-// end of the last finite round trip.
+// a non-finite value stored at its end, or a wait of its pass that gave up) sets
+// the device stop flag: every later launch of the call stores nothing, the round
+// trip's row is not counted, and the state is restored from the snapshot its
+// refresh launch took, i.e. to the end of the last finite round trip.
 template <typename R> static int roundtrip_impl(opo_t *h, int n_rt)
 {
     int trc = ensure_tables<R>(h, 0.0);
@@ -1839,7 +1859,7 @@ template <typename R> static int roundtrip_impl(opo_t *h, int n_rt)
     }
     int done = 0;
     std::vector<double> chunk;
-    int ctr[5] = {0, 0, 0, 0, 0};
+    int ctr[4] = {0, 0, 0, 0};
     while (done < n_rt) {
         const int m = std::min(kHistChunk, n_rt - done);
         set_counter<<<1, 1, 0, h->stream>>>(h->d_counter, 0, -1, 0);
@@ -1860,7 +1880,6 @@ template <typename R> static int roundtrip_impl(opo_t *h, int n_rt)
                                hipMemcpyDeviceToHost, h->stream));
         HIP_TRY(hipMemcpyAsync(ctr, h->d_counter, sizeof(ctr), hipMemcpyDeviceToHost, h->stream));
         HIP_TRY(hipStreamSynchronize(h->stream));
-        if (ctr[4] != 0) return fail(OPO_EDEVICE, "a wait of the pass kernel gave up");
         const int rows = std::min(ctr[0], m);   // finite round trips of this chunk
         h->hist.insert(h->hist.end(), chunk.begin(), chunk.begin() + static_cast<size_t>(rows) * h->n_inst * 3);
         h->hist_rows += rows;
@@ -1871,6 +1890,10 @@ template <typename R> static int roundtrip_impl(opo_t *h, int n_rt)
             HIP_TRY(hipGetLastError());
             HIP_TRY(hipStreamSynchronize(h->stream));
             h->z = 0.0;
+            if (take_failed(h))
+                return fail(OPO_EDEVICE, "a wait inside the pass of round trip " + std::to_string(h->hist_rows) +
+                                             " (counted from opo_init) gave up; stopped with the state that round "
+                                             "trip started from");
             return fail(OPO_ENONFINITE, "non-finite energy or field at round trip " + std::to_string(h->hist_rows) +
                                             " (counted from opo_init); stopped with the state that round trip "
                                             "started from");
@@ -2083,7 +2106,7 @@ int opo_sync(opo_t *h)
     int rc = check(h);
     if (rc) return rc;
     HIP_TRY(hipStreamSynchronize(h->stream));
-    return OPO_OK;
+    return team_check(h);
 }
 
 int opo_get_fields(opo_t *h, int32_t inst, int32_t field, int32_t domain, double *out)
@@ -2094,14 +2117,16 @@ int opo_get_fields(opo_t *h, int32_t inst, int32_t field, int32_t domain, double
         domain > 1)
         return fail(OPO_EINVAL, "bad instance, field, domain or output pointer");
     try {
-        if (domain == 1)
-            return h->precision == OPO_F64 ? spectrum_impl<double>(h, inst, field, out)
-                                           : spectrum_impl<float>(h, inst, field, out);
+        if (domain == 1) {
+            rc = h->precision == OPO_F64 ? spectrum_impl<double>(h, inst, field, out)
+                                         : spectrum_impl<float>(h, inst, field, out);
+            return rc ? rc : team_check(h);
+        }
         const InstDesc &d = h->inst[inst];
         const char *src = static_cast<const char *>(h->state) + (d.off + static_cast<long long>(field) * d.nt) * h->elem;
         HIP_TRY(h->precision == OPO_F64 ? state_to_host<double>(out, src, d.nt, h->stream)
                                         : state_to_host<float>(out, src, d.nt, h->stream));
-        return OPO_OK;
+        return team_check(h);
     } catch (...) {
         return fail(OPO_ENOMEM, "host allocation failed");
     }
@@ -2162,6 +2187,7 @@ int opo_set_progress(opo_t *h, int32_t rt_done, double z_mm, const double *histo
         set_counter<<<1, 1, 0, h->stream>>>(h->d_counter, 0, rt_done, 1);
         HIP_TRY(hipGetLastError());
         HIP_TRY(hipStreamSynchronize(h->stream));
+        (void)take_failed(h);
         h->hist.swap(hist);
         h->hist_rows = rt_done;
         h->z = z_mm;
@@ -2270,6 +2296,18 @@ int opo_destroy(opo_t *h)
 {
     if (!is_live(h)) return fail(OPO_ESTATE, "invalid or destroyed handle");
     release(h);
+    return OPO_OK;
+}
+
+// Not part of the interface in opo.h: raises the flag of a wait that gave up, behind the
+// work queued so far, so that a test sees what follows from it.
+int opo_test_fail_wait(opo_t *h)
+{
+    int rc = check(h);
+    if (rc) return rc;
+    if (!h->team_failed) return fail(OPO_EINVAL, "the handle runs no pass that waits");
+    HIP_TRY(hipStreamSynchronize(h->stream));
+    __atomic_store_n(h->team_failed, 1, __ATOMIC_RELAXED);
     return OPO_OK;
 }
 

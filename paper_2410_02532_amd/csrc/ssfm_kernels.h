@@ -1214,14 +1214,15 @@ __global__ __launch_bounds__(kThreads) void adapt_control(const InstDesc *inst, 
 // ------------------------------------------------------------------------
 // Per-instance energies of one round trip from the column-tile partial sums,
 // summed in tile order (deterministic), into history row counter[0]. A
-// non-finite energy, or a non-finite value stored by the boundary launch
-// (counter[3]), sets the stop flag counter[2] instead: the row is not written,
+// non-finite energy, a non-finite value stored by the boundary launch
+// (counter[3]) or a wait that gave up in the pass (*failed, or null) sets the stop flag
+// counter[2] instead: the row is not written,
 // the counters do not advance, and every later launch of the call stores
 // nothing, so the state the round trip started from (kept by its refresh
 // launch) is the last finite one.
 __global__ __launch_bounds__(kThreads) void energy_reduce(const InstDesc *inst, int n_inst,
                                                           const double *partial, double *hist,
-                                                          int *counter, int capacity);
+                                                          int *counter, int capacity, const int *failed);
 
 // counter[0] = slot; counter[1] = rt unless rt < 0; clear_flags: counter[2] = counter[3] = 0.
 __global__ void set_counter(int *counter, int slot, int rt, int clear_flags);

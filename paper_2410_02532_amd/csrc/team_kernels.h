@@ -14,7 +14,9 @@
 // members then share the tiles out among fewer). The results do not depend on the
 // team's size. A list that another XCD has claimed is left to it; one that nobody has
 // claimed is taken by the first wave that finds it so, so every list is worked on, also
-// on a partition of the device with fewer XCDs.
+// on a partition of the device with fewer XCDs. A wait that makes kTeamSpin polls gives up:
+// it raises a flag, which the host reads when it has waited for the stream, and the launch
+// ends with fields that are not those of the pass.
 //
 // Coherent without fences: a team's waves share the L2 of the XCD they run on (XCC_ID)
 // and the L1 is write-through. Stores are waited for (vmcnt) before the flag is set;
@@ -95,7 +97,7 @@ template <typename R> struct TeamArgs {
     const int *counter;       // [2] stop flag, see StepArgs
     const Coupling<R> *coef;  // couplings of step boundary s0 + b at b n + index
     TeamSync *sync;           // per list
-    int *failed;              // set when a wait gave up
+    int *failed;              // set when a wait gave up (pinned host memory)
     int n;                    // instances of the handle
     int count;                // lists
     // phases begin .. end - 1: 2 j are the columns at step boundary s0 + j, 2 j + 1 the
@@ -121,7 +123,7 @@ __device__ __forceinline__ bool team_give_up(int &polls, int *failed)
 {
     if ((++polls & 1023) != 0) return false;
     if (polls < kTeamSpin && team_load(failed) == 0) return false;
-    __hip_atomic_store(failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(failed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     return true;
 }
 
