@@ -44,7 +44,7 @@ static int fail(int code, const std::string &msg)
     } while (0)
 
 static constexpr int kHistChunk = 1024;   // round trips buffered on the device per read-back
-static constexpr int kCoefChunk = 128;    // step boundaries whose couplings are held (mid launches)
+static constexpr int kCoefChunk = 128;    // steps whose couplings are held at most (lone and mid launches)
 static constexpr int kMidMaps = 6;        // maps of mid_pass and edge_pass, see opo_s::mid
 static constexpr double kTwoPi = 6.283185307179586476925286766559;
 static constexpr double kPi = 3.1415926535897932384626433832795;
@@ -295,7 +295,8 @@ struct opo_s {
     MidInst *d_mid_inst = nullptr;   // per (crystal, instance)
     MidTile *d_mid_map[kMidMaps] = {};
     int mid_len[kMidMaps] = {};
-    void *d_coef = nullptr;          // couplings of kCoefChunk step boundaries, per instance
+    int coef_chunk = kCoefChunk;     // steps whose couplings are held
+    void *d_coef = nullptr;          // couplings of coef_chunk + 1 step boundaries, per instance
     size_t mid_lds = 0;
     int *d_tile_a = nullptr, *d_tile_b = nullptr;
     void *d_tw = nullptr;
@@ -743,7 +744,7 @@ static MidArgs<R> mid_args(const opo_t *h, const StepArgs<R> &a, int map, int fl
     m.disp = a.disp;
     m.counter = a.counter;
     m.inst = h->d_mid_inst + static_cast<size_t>(stage) * h->n_inst;
-    m.coef = static_cast<const Coupling<R> *>(h->d_coef) + static_cast<size_t>(step % kCoefChunk) * h->n_inst;
+    m.coef = static_cast<const Coupling<R> *>(h->d_coef) + static_cast<size_t>(step % h->coef_chunk) * h->n_inst;
     m.map = h->d_mid_map[map];
     m.flags = flags;
     double z, tau;
@@ -793,7 +794,7 @@ static constexpr int kInterior = A_INV | A_RK_PREV | A_RK_THIS | A_FWD;
 // Couplings of the step boundaries from s0 on (of crystal `stage`) into d_coef.
 template <typename R> static hipError_t fill_couplings(opo_t *h, const StepArgs<R> &a, int s0, int boundaries)
 {
-    const int count = std::min(kCoefChunk + 1, boundaries - s0);
+    const int count = std::min(h->coef_chunk + 1, boundaries - s0);
     const unsigned blocks = (6u * count * h->n_inst + kThreads - 1) / kThreads;
     coupling_table<R><<<blocks, kThreads, 0, h->stream>>>(a.inst, h->n_inst, h->order, a.dz_arg, a.zbase, a.nz, s0, count,
                                                           static_cast<Coupling<R> *>(h->d_coef));
@@ -912,9 +913,9 @@ static hipError_t enqueue_pass(opo_t *h, StepArgs<R> a, int nz_steps, int first,
         int chunk = -1;
         auto columns = [&](int half, bool rows, int flags, int step) -> hipError_t {
             if (h->mid && !(flags & ~kInterior)) {
-                if (step / kCoefChunk != chunk) {
-                    chunk = step / kCoefChunk;
-                    HIP_RET(fill_couplings<R>(h, a, chunk * kCoefChunk, nz + 1));
+                if (step / h->coef_chunk != chunk) {
+                    chunk = step / h->coef_chunk;
+                    HIP_RET(fill_couplings<R>(h, a, chunk * h->coef_chunk, nz + 1));
                 }
                 return launch_mid<R>(h, a, rows ? half : 2 + half, flags, step, stage);
             }
@@ -933,8 +934,8 @@ static hipError_t enqueue_pass(opo_t *h, StepArgs<R> a, int nz_steps, int first,
     int held = -1;   // chunk of the coupling table
     auto column = [&](int flags, int step) -> hipError_t {
         if (!lone || (flags & ~kInterior)) return launch_a<R>(h, a, flags, step);
-        if (held < 0 || step < held || step > held + kCoefChunk) {
-            held = step - step % kCoefChunk;
+        if (held < 0 || step < held || step > held + h->coef_chunk) {
+            held = step - step % h->coef_chunk;
             HIP_RET(fill_couplings<R>(h, a, held, nz + 1));
         }
         return launch_lone_a<R>(h, a, flags, step - held, stage);
@@ -942,8 +943,8 @@ static hipError_t enqueue_pass(opo_t *h, StepArgs<R> a, int nz_steps, int first,
     if (h->team) {
         // the boundary's launches only where there is something of the boundary to do
         if (first) HIP_RET(launch_a<R>(h, a, first | A_RK_THIS | A_FWD, 0));
-        for (int s0 = 0; s0 < nz; s0 += kCoefChunk) {
-            const int s1 = std::min(nz, s0 + kCoefChunk), steps = s1 - s0;
+        for (int s0 = 0; s0 < nz; s0 += h->coef_chunk) {
+            const int s1 = std::min(nz, s0 + h->coef_chunk), steps = s1 - s0;
             HIP_RET(fill_couplings<R>(h, a, s0, nz + 1));
             const bool open = s0 == 0 && !first, close = s1 == nz && !last;
             HIP_RET(launch_team<R>(h, a, s0, open ? 0 : 1, s1 == nz && last ? 2 * steps : 2 * steps + 1, open ? 0 : -1,
@@ -1492,13 +1493,23 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
         for (const InstDesc &d : h->inst)
             mid_inst.push_back({d.off, d.w4_off, d.disp_off, d.nt, d.n1, d.log2n1, d.log2n2, d.nf * d.n2,
                                 d.kerr ? 2 : d.dk_rev == 0.0 ? 0 : 1});
-        const size_t cb = opt.precision == OPO_F64 ? sizeof(Coupling<double>) : sizeof(Coupling<float>);
-        bool ok = hipMalloc(reinterpret_cast<void **>(&h->d_mid_inst), mid_inst.size() * sizeof(MidInst)) == hipSuccess &&
-                  hipMalloc(&h->d_coef, (kCoefChunk + 1) * cb * n) == hipSuccess;
+        bool ok = hipMalloc(reinterpret_cast<void **>(&h->d_mid_inst), mid_inst.size() * sizeof(MidInst)) == hipSuccess;
         for (int q = 0; q < (h->edge ? kMidMaps : 4); ++q) {
             h->mid_len[q] = static_cast<int>(mid_maps[q].size());
             ok = ok && hipMalloc(reinterpret_cast<void **>(&h->d_mid_map[q]), mid_maps[q].size() * sizeof(MidTile)) == hipSuccess;
         }
+        // The couplings take an eighth of the fields at most, and 64 MiB (at 128 steps they
+        // would be 1.8 times the fields of FP64 instances of 2^9 points), and fewer steps
+        // still where that does not fit: a refill is one launch of microseconds.
+        const size_t row = (opt.precision == OPO_F64 ? sizeof(Coupling<double>) : sizeof(Coupling<float>)) * n;
+        const size_t rows = std::min<size_t>(need / 8, 64 << 20) / row;
+        h->coef_chunk = static_cast<int>(std::min<size_t>(kCoefChunk, std::max<size_t>(rows, 2) - 1));
+        while (ok && hipMalloc(&h->d_coef, (h->coef_chunk + 1) * row) != hipSuccess) {
+            h->d_coef = nullptr;
+            ok = h->coef_chunk > 1;
+            h->coef_chunk /= 2;
+        }
+        (void)hipGetLastError();   // of an attempt above
         if (!ok) return bail(fail(OPO_ENOMEM, "hipMalloc of the batch tables failed"));
     }
     if (!res_inst.empty()) {

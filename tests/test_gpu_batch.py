@@ -108,3 +108,42 @@ def test_equal_members_of_both_halves_agree(precision, nf, log2nt, count, nz):
         for i in range(1, count):
             assert np.array_equal(h.get_fields(i), first), i
             assert np.array_equal(h.energy_history(i), energies), i
+
+
+@pytest.mark.parametrize("precision, nf, log2nt, count, order", [("f64", 3, 9, 684, 2), ("f64", 2, 9, 1024, 4),
+                                                                 ("f32", 3, 10, 342, 4)])
+def test_batch_of_small_grids_refills_its_couplings(precision, nf, log2nt, count, order):
+    """Small grids hold the couplings of a few steps only (an eighth of their fields): passes
+    over many refills against the oracle, and two calls equal to one bit for bit."""
+    print("batch refills %s nf %d 2^%d order %d" % (precision, nf, log2nt, order), file=sys.stderr, flush=True)
+    members = _batch([log2nt] * 3, nf, 0.4, 0.0)
+    insts = [members[b % 3] for b in range(count)]
+    nz, dz = 40, 2.0 ** -5
+    out = []
+    for calls in ((nz,), (29, 11)):
+        with B.Opo(insts, nz, precision=precision, split_order=order) as h:
+            for n in calls:
+                h.ssfm_propagate(n, dz)
+            out.append([h.get_fields(i) for i in (0, 1, 2, count - 1)])
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
+    for ins, a in zip(members, out[0]):
+        ref = oracle.ssfm_pass(dict(ins["crystal"], order=order), ins["fields"], nz, dz)
+        for x in range(nf):
+            assert rel_l2(a[x], ref[x]) <= TOL[precision], (x, rel_l2(a[x], ref[x]))
+
+
+def test_batch_of_small_grids_holds_few_tables():
+    """Device memory of a handle per instance beyond its fields, from two handles (what both
+    hold cancels): a second copy of the fields, 1024 rows of energies, and tables that stay
+    below a quarter of the fields, each of some 20 allocations rounded up to 2 MiB."""
+    ins = _batch([9], 3, 0.4, 0.0)[0]
+    fields, counts, used = 3 * 512 * 16, (1000, 6000), []
+    print("batch memory %s of 2^9" % (counts,), file=sys.stderr, flush=True)
+    hold = torch.empty(fields * counts[1], dtype=torch.uint8, device="cuda")   # torch keeps room for the state
+    del hold
+    for n in counts:
+        before = torch.cuda.mem_get_info()[0]
+        with B.Opo([ins] * n, 4, precision="f64"):
+            used.append(before - torch.cuda.mem_get_info()[0])
+    assert used[1] - used[0] <= (counts[1] - counts[0]) * (fields + 1024 * 24 + fields // 4) + 20 * (2 << 20), used
