@@ -48,7 +48,7 @@ template <typename R> struct MidArgs {
 };
 
 // ---- column tile: four waves of 64/T columns each (T = N/PF lanes a column)
-constexpr int kMidMinLog2N2 = 4;
+constexpr int kMidMinLog2N2 = 4, kMidMinLog2N1 = 5;
 constexpr int mid_col_pf(int ln2) { return ln2 <= 5 ? 2 : 4; }
 // FP32 rows of 1024 and 2048 points take 16 samples a thread (radix-16 stages, one stage
 // and one exchange less): the batched sweep 16.7 -> 16.4 ms, two waves 12.0 -> 11.7. The

@@ -1112,20 +1112,39 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
         one_nf = one_nf && nfields(f[i]) == nfields(f[0]);
         few = few && one_nf && ilog2(f[i].nt) >= kLoneMinLog2;
     }
+    // schedule: the table's entry for each shape (schedule 0), or two-pass (1) / resident
+    // where served (2); an explicit col_log2 sets the split
+    const bool f64 = opt.precision == OPO_F64;
+    std::vector<Schedule> sched(n, Schedule{0, opt.schedule == 2 ? 1 : 0});
+    for (int i = 0; i < n; ++i) {
+        const int l2 = ilog2(f[i].nt);
+        if (few) sched[i] = Schedule{lone_split(l2), 0};
+        else if (opt.schedule == 0) sched[i] = schedule_lookup(f64, nfields(f[i]), l2, batched);
+        // resident passes: shapes resident_pass serves, second-order steps, one crystal
+        sched[i].resident = sched[i].resident && resident_shape(l2, opt.precision) && h->order == 2 && K == 1;
+        if (opt.col_log2 != 0) sched[i].col_log2 = opt.col_log2;
+    }
+    if (opt.schedule == 0 && batched && one_nf && f64 && opt.col_log2 == 0) {
+        // mid_pass's splits, where with them the two-pass instances share one kernel and so
+        // run mid_pass (below)
+        std::vector<Schedule> mid = sched;
+        int cr = -1, rr = -1, two_pass = 0;
+        bool one = true;
+        for (int i = 0; i < n; ++i) {
+            if (mid[i].resident) continue;
+            mid[i].col_log2 = batch_split(nfields(f[i]), ilog2(f[i].nt), mid[i].col_log2);
+            const Plan p = make_plan(f[i].nt, opt.precision, mid[i].col_log2);
+            const int c1 = range_of(kColRanges, p.log2n2), r1 = range_of(kRowRanges, p.log2n1);
+            if (two_pass++ == 0) cr = c1, rr = r1;
+            one = one && c1 == cr && r1 == rr && p.log2n2 >= kMidMinLog2N2 && p.log2n1 >= kMidMinLog2N1;
+        }
+        if (one && two_pass >= 2) sched.swap(mid);
+    }
     for (int i = 0; i < n; ++i) {
         InstDesc &d = h->inst[i];
-        // schedule: the table's entry for this shape (schedule 0), or two-pass
-        // (1) / resident where served (2); an explicit col_log2 sets the split
-        const int l2 = ilog2(f[i].nt);
-        const bool f64 = opt.precision == OPO_F64;
-        Schedule sc{0, opt.schedule == 2 ? 1 : 0};
-        if (few) sc = Schedule{lone_split(l2), 0};
-        else if (opt.schedule == 0) sc = schedule_lookup(f64, nfields(f[i]), l2, batched);
-        if (opt.schedule == 0 && batched && one_nf) sc.col_log2 = batch_split(f64, nfields(f[i]), l2, sc.col_log2);
-        const Plan p = make_plan(f[i].nt, opt.precision, opt.col_log2 != 0 ? opt.col_log2 : sc.col_log2);
+        const Plan p = make_plan(f[i].nt, opt.precision, sched[i].col_log2);
         fill_desc(d, f[i], c[i * K], k[i], p);
-        // resident passes: shapes resident_pass serves, second-order steps, one crystal
-        d.resident = sc.resident && resident_shape(l2, opt.precision) && h->order == 2 && K == 1 ? 1 : 0;
+        d.resident = sched[i].resident;
         d.off = off;
         off += static_cast<long long>(d.nf) * d.nt;
         if (f[i].pump_in) {
@@ -1170,7 +1189,6 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
     // a handle of few instances, too small to fill the chip, on the automatic schedule:
     // the lone kernels, or the team kernels where they serve every shape
     if (few) {
-        const bool f64 = opt.precision == OPO_F64;
         h->lone = order;
         h->lone_nf = h->inst[0].nf;
         h->team = prop.multiProcessorCount == 256;
@@ -1275,7 +1293,6 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
     if (n >= 2 && h->groups_a.size() == 2 && h->groups_b.size() == 2 &&
         h->groups_a[0].half == 0 && h->groups_a[1].half == 1 && h->groups_b[0].half == 0 &&
         h->groups_b[1].half == 1) {
-        const bool f64 = opt.precision == OPO_F64;
         h->mixed = true;
         for (int hf = 0; hf < 2; ++hf) {
             const Group &gc = h->groups_a[1 - hf];
@@ -1348,7 +1365,6 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
     std::vector<MidTile> mid_maps[kMidMaps];
     if (h->mixed && batched && opt.schedule == 0 && h->groups_a[0].ln == h->groups_a[1].ln &&
         h->groups_a[0].nf == h->groups_a[1].nf && (h->groups_b[0].ln == 2) == (h->groups_b[1].ln == 2)) {
-        const bool f64 = opt.precision == OPO_F64;
         h->mid_cr = h->groups_a[0].ln;
         h->mid_rr = h->groups_b[0].ln;
         h->mid_nf = h->groups_a[0].nf;
@@ -1356,7 +1372,7 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
                       : mid_fn<float>(h->mid_cr, h->mid_rr, h->mid_nf)) != nullptr;
         h->mid = h->mid && (f64 || state <= kLastCache || (long_rows && h->mid_cr == 0));
         for (int i : order)
-            h->mid = h->mid && h->inst[i].log2n2 >= kMidMinLog2N2 && h->inst[i].log2n1 >= 5;
+            h->mid = h->mid && h->inst[i].log2n2 >= kMidMinLog2N2 && h->inst[i].log2n1 >= kMidMinLog2N1;
         for (int ch = 0; h->mid && ch < 2; ++ch) {
             std::vector<MidTile> cols, rows, qc[kXcd], qr[kXcd], none[kXcd];
             for (int i : order) {

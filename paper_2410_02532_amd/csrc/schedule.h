@@ -56,14 +56,15 @@ constexpr int kLoneMax = 48;   // instances: their descriptors are kernel argume
 
 inline int lone_split(int log2nt) { return log2nt <= 14 ? 5 : 0; }
 
-// Two-pass instances of a batch of one field count, FP64: the splits by mid_pass's times
-// (batches of 2^22 points, us per z-step; the table's entries are by mixed_pass's).
-// Columns of 2^6 instead of 2^4: three waves 2^13 172 -> 169, 2^15 176 -> 166, 2^16 184
-// (columns of 2^5, the rows' limit) -> 180; two waves 2^12 147 -> 111, 2^16 124 -> 121.
-// Returns the table's split where that stays the better one.
-inline int batch_split(bool f64, int nf, int log2nt, int table)
+// Two-pass instances of an FP64 batch whose launches inside a pass run mid_pass: the splits
+// by its times (batches of 2^22 points, us per z-step; the table's entries are by
+// mixed_pass's). Columns of 2^6 instead of 2^4: three waves 2^13 172 -> 169, 2^15 176 -> 166,
+// 2^16 184 (columns of 2^5, the rows' limit) -> 180; two waves 2^12 147 -> 111, 2^16 124 ->
+// 121. Returns the table's split where that stays the better one. Not for batches that run
+// other kernels (two 2^13 with two 2^18, which do not share one: 84 with the table's splits,
+// 90 with these).
+inline int batch_split(int nf, int log2nt, int table)
 {
-    if (!f64) return table;
     if (nf == 3) return log2nt == 13 || log2nt == 15 || log2nt == 16 ? 6 : table;
     return log2nt == 12 || log2nt == 16 ? 6 : table;
 }

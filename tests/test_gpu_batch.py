@@ -147,3 +147,15 @@ def test_batch_of_small_grids_holds_few_tables():
         with B.Opo([ins] * n, 4, precision="f64"):
             used.append(before - torch.cuda.mem_get_info()[0])
     assert used[1] - used[0] <= (counts[1] - counts[0]) * (fields + 1024 * 24 + fields // 4) + 20 * (2 << 20), used
+
+
+@pytest.mark.parametrize("sizes, l, mid", [([13, 13, 18, 18], 13, False), ([13] * 44, 13, True), ([13] * 40 + [19], 13, False),
+                                           ([13, 16] * 6, 16, True), ([15, 19, 15, 19], 15, False)])
+def test_fp64_batch_splits_follow_its_kernels(sizes, l, mid):
+    """The splits timed with mid_pass are taken only by batches that run it (one column and
+    one row size range); the others take the table's, as a forced split or kernel would."""
+    print("fp64 batch splits %s" % sizes[:4], file=sys.stderr, flush=True)
+    with B.Opo(_batch(sizes, 3, 0.0, 0.0), 5, precision="f64") as h:
+        log2n1, log2n2, resident = h.plan(sizes.index(l))
+    assert not resident
+    assert log2n1 + log2n2 == l and log2n2 == (6 if mid else {13: 4, 15: 4, 16: 5}[l])
