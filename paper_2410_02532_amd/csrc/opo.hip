@@ -1371,8 +1371,11 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
         h->mid = (f64 ? mid_fn<double>(h->mid_cr, h->mid_rr, h->mid_nf)
                       : mid_fn<float>(h->mid_cr, h->mid_rr, h->mid_nf)) != nullptr;
         h->mid = h->mid && (f64 || state <= kLastCache || (long_rows && h->mid_cr == 0));
-        for (int i : order)
-            h->mid = h->mid && h->inst[i].log2n2 >= kMidMinLog2N2 && h->inst[i].log2n1 >= kMidMinLog2N1;
+        for (int i : order) {
+            const InstDesc &d = h->inst[i];
+            h->mid = h->mid && d.log2n2 >= kMidMinLog2N2 && d.log2n1 >= kMidMinLog2N1 &&
+                     (f64 || mid_faster_f32(d.nf, d.log2n2, d.log2n1));
+        }
         for (int ch = 0; h->mid && ch < 2; ++ch) {
             std::vector<MidTile> cols, rows, qc[kXcd], qr[kXcd], none[kXcd];
             for (int i : order) {

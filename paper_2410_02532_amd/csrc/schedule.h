@@ -69,4 +69,18 @@ inline int batch_split(int nf, int log2nt, int table)
     return log2nt == 12 || log2nt == 16 ? 6 : table;
 }
 
+// FP32 shapes that mid_pass runs faster than mixed_pass (us a z-step, mixed_pass / mid_pass,
+// batches of 2^20 .. 2^23 points): columns of 2^6 and more, or rows of 2^10 and more, always
+// (0.80 to 1.01 of the time). Shorter ones are stages of radix 2 over 64-byte pieces of
+// rows: three waves gain but for 2^9 points (columns of 2^4, rows of 2^5: 139 / 159, 259 /
+// 306; columns and rows of 2^5 287 / 257), two waves only at 2^11 and 2^12 points (columns
+// of 2^5, rows of 2^6 221 / 181; but 2^4 x 2^5 121 / 141, 2^5 x 2^5 812 / 858, 2^5 x 2^8 182
+// / 193, 2^4 x 2^9 97 / 113, 2^5 x 2^9 102 / 113).
+inline bool mid_faster_f32(int nf, int log2n2, int log2n1)
+{
+    if (log2n2 >= 6 || log2n1 >= 10) return true;
+    const int log2nt = log2n2 + log2n1;
+    return nf == 3 ? log2nt > 9 : log2nt == 11 || log2nt == 12;
+}
+
 } // namespace opo
