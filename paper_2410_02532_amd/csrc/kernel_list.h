@@ -73,8 +73,12 @@
 #define OPO_LONE_KERNELS(DECL, R)                                                                  \
     DECL __global__ void lone_column<R, 2>(LoneColumnArgs<R>);                                     \
     DECL __global__ void lone_column<R, 3>(LoneColumnArgs<R>);                                     \
+    DECL __global__ void lone_column_uneven<R, 2>(LoneColumnArgs<R>, LoneTiles);                   \
+    DECL __global__ void lone_column_uneven<R, 3>(LoneColumnArgs<R>, LoneTiles);                   \
     DECL __global__ void lone_row<R, 9>(LoneRowArgs<R>);                                           \
-    DECL __global__ void lone_row<R, 12>(LoneRowArgs<R>);
+    DECL __global__ void lone_row<R, 12>(LoneRowArgs<R>);                                          \
+    DECL __global__ void lone_row_uneven<R, 9>(LoneRowArgs<R>, LoneTiles);                         \
+    DECL __global__ void lone_row_uneven<R, 12>(LoneRowArgs<R>, LoneTiles);
 
 // All interior steps of small instances in one launch.
 #define OPO_TEAM_KERNELS(DECL, R)                                                                  \

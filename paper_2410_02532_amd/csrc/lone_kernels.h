@@ -34,6 +34,35 @@ struct LoneColumnInst {
     int index;            // instance (couplings)
 };
 
+// Tiles of a launch over instances of uneven size, one after another along the grid:
+// first[q] is the first tile of instance q, the largest value past the last. (Otherwise
+// each instance takes a layer of the grid, as long as the largest one's. About 0.35 ns for
+// each idle workgroup of those layers, against 0.3 us for the search here: with more than
+// kLoneMaxIdle of them, in the column and row launch together, the search is the cheaper.
+// FP32, a 2^18 and 40 2^10 instances 40.6 us a z-step in layers, 23.0 with the search.)
+constexpr unsigned kLoneMaxIdle = 4096;
+struct LoneTiles {
+    static_assert(kLoneMax % 8 == 0, "searched eight at a time");
+    unsigned first[kLoneMax];
+
+    // the instance of workgroup `tile`, which becomes its tile in the instance
+    __device__ __forceinline__ int find(unsigned &tile) const
+    {
+        int q = -1;
+        unsigned start = 0;
+        for (int c = 0; c < kLoneMax && tile >= first[c]; c += 8) {   // the larger instances come first
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+                const bool past = tile >= first[c + k];
+                q += past;
+                start = past ? first[c + k] : start;
+            }
+        }
+        tile -= start;
+        return q;
+    }
+};
+
 template <typename R> struct LoneColumnArgs {
     cplx<R> *state;
     const Phasor<R> *tw, *w4tab;
@@ -182,7 +211,7 @@ __device__ __forceinline__ void lone_column_math(cplx<R> (&v)[NF][PF], const Pha
 }
 
 template <typename R, int LN2, int NF, int PF>
-__device__ __forceinline__ void lone_column_tile(const LoneColumnArgs<R> &a, const LoneColumnInst &d)
+__device__ __forceinline__ void lone_column_tile(const LoneColumnArgs<R> &a, const LoneColumnInst &d, unsigned b)
 {
     using V = cplx<R>;
     constexpr int N = 1 << LN2, T = N / PF, COLS = 64 / T;
@@ -190,10 +219,10 @@ __device__ __forceinline__ void lone_column_tile(const LoneColumnArgs<R> &a, con
     const int flags = a.flags;
     const int c = threadIdx.x % COLS, t = threadIdx.x / COLS;
     const unsigned n1 = d.n1, nt = d.nt, tiles = n1 / COLS;
-    if (blockIdx.x >= tiles) return;          // a launch over instances of uneven size
+    if (b >= tiles) return;          // a layer longer than this instance
     // workgroups are dealt to the eight XCDs in turn: neighbouring tiles, which share
     // the cache lines of their columns, go to the same one
-    const unsigned tile = tiles >= 8 ? (blockIdx.x & 7) * (tiles >> 3) + (blockIdx.x >> 3) : blockIdx.x;
+    const unsigned tile = tiles >= 8 ? (b & 7) * (tiles >> 3) + (b >> 3) : b;
     const int kind = d.kind;
     const Coupling<R> *coef = a.coef + d.index;
     V *g = a.state + d.off;
@@ -226,15 +255,26 @@ __device__ __forceinline__ void lone_column_tile(const LoneColumnArgs<R> &a, con
         for (int m = 0; m < PF; ++m) el32(g, qo[m] + f * nt) = v[f][m];
 }
 
+template <typename R, int NF>
+__device__ __forceinline__ void lone_column_dispatch(const LoneColumnArgs<R> &a, const LoneColumnInst &d, unsigned b)
+{
+    switch (d.log2n2) {
+    case 4: return lone_column_tile<R, 4, NF, 2>(a, d, b);
+    case 5: return lone_column_tile<R, 5, NF, 2>(a, d, b);
+    case 6: return a.spread ? lone_column_tile<R, 6, NF, 2>(a, d, b) : lone_column_tile<R, 6, NF, 4>(a, d, b);
+    default: return lone_column_tile<R, 7, NF, 8>(a, d, b);
+    }
+}
+
 template <typename R, int NF> __global__ __launch_bounds__(64) void lone_column(LoneColumnArgs<R> a)
 {
-    const LoneColumnInst &d = a.inst[blockIdx.y];
-    switch (d.log2n2) {
-    case 4: return lone_column_tile<R, 4, NF, 2>(a, d);
-    case 5: return lone_column_tile<R, 5, NF, 2>(a, d);
-    case 6: return a.spread ? lone_column_tile<R, 6, NF, 2>(a, d) : lone_column_tile<R, 6, NF, 4>(a, d);
-    default: return lone_column_tile<R, 7, NF, 8>(a, d);
-    }
+    lone_column_dispatch<R, NF>(a, a.inst[blockIdx.y], blockIdx.x);
+}
+template <typename R, int NF> __global__ __launch_bounds__(64) void lone_column_uneven(LoneColumnArgs<R> a, LoneTiles t)
+{
+    unsigned b = blockIdx.x;
+    const int q = t.find(b);
+    lone_column_dispatch<R, NF>(a, a.inst[q], b);
 }
 
 // ---- row tile: whole rows, PF samples per thread. A workgroup holds one row where it
@@ -249,15 +289,15 @@ constexpr int lone_row_pf(int ln1) { return ln1 <= 7 || ln1 == 10 ? 4 : 8; }
 constexpr int lone_row_threads(int ln1) { return (1 << ln1) / lone_row_pf(ln1); }
 
 template <typename R, int LN1>
-__device__ __forceinline__ void lone_row_tile(const LoneRowArgs<R> &a, const LoneRowInst &d, cplx<R> *s)
+__device__ __forceinline__ void lone_row_tile(const LoneRowArgs<R> &a, const LoneRowInst &d, unsigned b, cplx<R> *s)
 {
     using V = cplx<R>;
     constexpr int N = 1 << LN1, PF = lone_row_pf(LN1), T = N / PF;
     constexpr int TW = tw_regs<N, PF>(), X = fft_exchanges<N, PF>();
     constexpr bool WAVE = T <= 64;   // a row's threads lie within one wavefront
     const int rows = blockDim.x / T, r = threadIdx.x / T, t = threadIdx.x % T;
-    if (static_cast<int>(blockIdx.x) * rows >= d.rows) return;   // a launch over instances of uneven size
-    const int row = blockIdx.x * rows + r;
+    if (static_cast<int>(b) * rows >= d.rows) return;   // a layer longer than this instance
+    const int row = b * rows + r;
     const bool act = row < d.rows;
     const unsigned q0 = static_cast<unsigned>(act ? row : 0) * N + t;
     V *g = a.state + d.off;
@@ -283,26 +323,38 @@ __device__ __forceinline__ void lone_row_tile(const LoneRowArgs<R> &a, const Lon
 
 // Rows of 2^5..2^HI points: HI = 9, or 12 (the longer rows hold more samples and
 // twiddles per thread, one wave per SIMD).
-template <typename R, int HI> __global__ __launch_bounds__(HI > 9 ? 512 : 256) void lone_row(LoneRowArgs<R> a)
+template <typename R, int HI>
+__device__ __forceinline__ void lone_row_dispatch(const LoneRowArgs<R> &a, const LoneRowInst &d, unsigned b, cplx<R> *s)
 {
-    extern __shared__ __align__(16) unsigned char lds_raw[];
-    cplx<R> *s = reinterpret_cast<cplx<R> *>(lds_raw);
-    const LoneRowInst &d = a.inst[blockIdx.y];
     switch (d.log2n1) {
-    case 5: return lone_row_tile<R, 5>(a, d, s);
-    case 6: return lone_row_tile<R, 6>(a, d, s);
-    case 7: return lone_row_tile<R, 7>(a, d, s);
-    case 8: return lone_row_tile<R, 8>(a, d, s);
-    case 9: return lone_row_tile<R, 9>(a, d, s);
+    case 5: return lone_row_tile<R, 5>(a, d, b, s);
+    case 6: return lone_row_tile<R, 6>(a, d, b, s);
+    case 7: return lone_row_tile<R, 7>(a, d, b, s);
+    case 8: return lone_row_tile<R, 8>(a, d, b, s);
+    case 9: return lone_row_tile<R, 9>(a, d, b, s);
     }
     if constexpr (HI > 9) {
         switch (d.log2n1) {
-        case 10: return lone_row_tile<R, 10>(a, d, s);
-        case 11: return lone_row_tile<R, 11>(a, d, s);
+        case 10: return lone_row_tile<R, 10>(a, d, b, s);
+        case 11: return lone_row_tile<R, 11>(a, d, b, s);
         case 12:
-            if constexpr (kMaxLog2N1<R> >= 12) return lone_row_tile<R, 12>(a, d, s);
+            if constexpr (kMaxLog2N1<R> >= 12) return lone_row_tile<R, 12>(a, d, b, s);
         }
     }
+}
+
+template <typename R, int HI> __global__ __launch_bounds__(HI > 9 ? 512 : 256) void lone_row(LoneRowArgs<R> a)
+{
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    lone_row_dispatch<R, HI>(a, a.inst[blockIdx.y], blockIdx.x, reinterpret_cast<cplx<R> *>(lds_raw));
+}
+template <typename R, int HI>
+__global__ __launch_bounds__(HI > 9 ? 512 : 256) void lone_row_uneven(LoneRowArgs<R> a, LoneTiles t)
+{
+    extern __shared__ __align__(16) unsigned char lds_raw[];
+    unsigned b = blockIdx.x;
+    const int q = t.find(b);
+    lone_row_dispatch<R, HI>(a, a.inst[q], b, reinterpret_cast<cplx<R> *>(lds_raw));
 }
 
 } // namespace opo

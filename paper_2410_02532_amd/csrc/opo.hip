@@ -230,13 +230,19 @@ template <typename R> static const void *team_fn(int nf)
 }
 
 // Lone kernels (lone_kernels.h): columns of nf-wave instances, rows of up to 2^ln points.
-template <typename R> static const void *lone_column_fn(int nf)
+template <typename R> static const void *lone_column_fn(int nf, bool uneven)
 {
+    if (uneven)
+        return nf == 2 ? reinterpret_cast<const void *>(&lone_column_uneven<R, 2>)
+                       : reinterpret_cast<const void *>(&lone_column_uneven<R, 3>);
     return nf == 2 ? reinterpret_cast<const void *>(&lone_column<R, 2>)
                    : reinterpret_cast<const void *>(&lone_column<R, 3>);
 }
-template <typename R> static const void *lone_row_fn(int ln)
+template <typename R> static const void *lone_row_fn(int ln, bool uneven)
 {
+    if (uneven)
+        return ln <= 9 ? reinterpret_cast<const void *>(&lone_row_uneven<R, 9>)
+                       : reinterpret_cast<const void *>(&lone_row_uneven<R, 12>);
     return ln <= 9 ? reinterpret_cast<const void *>(&lone_row<R, 9>) : reinterpret_cast<const void *>(&lone_row<R, 12>);
 }
 
@@ -277,7 +283,9 @@ struct opo_s {
     // instances whose passes run the lone kernels (all two-pass instances, or none),
     // and their launches' grids, LDS and longest row
     std::vector<int> lone;
-    unsigned lone_tiles_a = 0, lone_tiles_b = 0;
+    LoneTiles lone_tiles_a{}, lone_tiles_b{};   // of uneven instances
+    dim3 lone_grid_a, lone_grid_b;
+    bool lone_uneven = false;
     bool lone_spread = false;        // see lone_col_pf
     bool team = false;               // ... or team_pass (team_kernels.h)
     TeamSync *d_team = nullptr;
@@ -830,10 +838,9 @@ static hipError_t launch_lone_a(opo_t *h, const StepArgs<R> &a, int flags, int r
         const InstDesc &d = inst[h->lone[q]];
         la.inst[q] = {d.off, d.w4_off, d.n1, d.nt, d.log2n2, d.kerr ? 2 : d.dk_rev == 0.0 ? 0 : 1, h->lone[q]};
     }
-    void *args[] = {&la};
+    void *args[] = {&la, &h->lone_tiles_a};
     HIP_RET(prof_begin(h, OPO_K_COLUMN));
-    HIP_RET(hipLaunchKernel(lone_column_fn<R>(h->lone_nf), dim3(h->lone_tiles_a, h->lone.size()), dim3(64), args, 0,
-                            h->stream));
+    HIP_RET(hipLaunchKernel(lone_column_fn<R>(h->lone_nf, h->lone_uneven), h->lone_grid_a, dim3(64), args, 0, h->stream));
     return prof_end(h);
 }
 
@@ -856,10 +863,9 @@ template <typename R> static hipError_t launch_lone_b(opo_t *h, const StepArgs<R
         la.inst[q].rows = d.nf * d.n2;
         la.inst[q].log2n1 = d.log2n1;
     }
-    void *args[] = {&la};
+    void *args[] = {&la, &h->lone_tiles_b};
     HIP_RET(prof_begin(h, OPO_K_ROW));
-    HIP_RET(hipLaunchKernel(lone_row_fn<R>(h->lone_ln1), dim3(h->lone_tiles_b, h->lone.size()),
-                            dim3(h->lone_threads_b), args, h->lone_lds_b, h->stream));
+    HIP_RET(hipLaunchKernel(lone_row_fn<R>(h->lone_ln1, h->lone_uneven), h->lone_grid_b, dim3(h->lone_threads_b), args, h->lone_lds_b, h->stream));
     return prof_end(h);
 }
 
@@ -1024,7 +1030,7 @@ template <typename R> static int setup_kernels(opo_t *h)
         HIP_TRY(hipFuncSetAttribute(mid_fn<R>(h->mid_cr, h->mid_rr, h->mid_nf), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     static_cast<int>(h->mid_lds)));
     if (!h->lone.empty())
-        HIP_TRY(hipFuncSetAttribute(lone_row_fn<R>(h->lone_ln1), hipFuncAttributeMaxDynamicSharedMemorySize,
+        HIP_TRY(hipFuncSetAttribute(lone_row_fn<R>(h->lone_ln1, h->lone_uneven), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     static_cast<int>(h->lone_lds_b)));
     if (h->edge)
         HIP_TRY(lds(edge_fn(h->mid_nf), std::max(h->lds_a, h->mid_lds)));
@@ -1199,19 +1205,40 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
             const InstDesc &d = h->inst[i];
             if (d.log2n2 < kLoneMinLog2N2 || d.log2n2 > kLoneMaxLog2N2 || d.log2n1 < kLoneMinLog2N1)
                 return bail(fail(OPO_EINVAL, "internal: no lone kernel for this split"));
-            h->lone_tiles_a = std::max<unsigned>(h->lone_tiles_a, d.n1 / lone_cols(d.log2n2, h->lone_spread));
             h->lone_threads_b = std::max(h->lone_threads_b, lone_row_threads(d.log2n1));
             h->lone_ln1 = std::max(h->lone_ln1, d.log2n1);
             h->team = h->team && team_shape(d.log2n2, d.log2n1, d.nf);
         }
-        for (int i : order) {
+        // the largest first: the tiles of an instance then start at a multiple of eight
+        if (!h->team)
+            std::stable_sort(h->lone.begin(), h->lone.end(), [&](int x, int y) { return h->inst[x].nt > h->inst[y].nt; });
+        std::vector<unsigned> tiles_a, tiles_b;
+        for (int i : h->lone) {
             const InstDesc &d = h->inst[i];
             const unsigned rows = h->lone_threads_b / lone_row_threads(d.log2n1);
             const int pts = h->lone_threads_b * lone_row_pf(d.log2n1);
-            h->lone_tiles_b = std::max(h->lone_tiles_b, (d.nf * d.n2 + rows - 1) / rows);
+            tiles_a.push_back(d.n1 / lone_cols(d.log2n2, h->lone_spread));
+            tiles_b.push_back((d.nf * d.n2 + rows - 1) / rows);
             h->lone_lds_b = std::max(h->lone_lds_b,
                                      2 * h->elem * (f64 ? lds_elems<double>(pts) : lds_elems<float>(pts)));
         }
+        // workgroups without work, were every instance given as many as the largest
+        size_t idle = 0;
+        for (const auto *t : {&tiles_a, &tiles_b})
+            for (unsigned c : *t) idle += *std::max_element(t->begin(), t->end()) - c;
+        h->lone_uneven = idle > kLoneMaxIdle;
+        auto place = [&](const std::vector<unsigned> &tiles, LoneTiles &t, dim3 &grid) {
+            std::fill(std::begin(t.first), std::end(t.first), ~0u);
+            unsigned sum = 0;
+            for (size_t q = 0; q < tiles.size(); ++q) {
+                t.first[q] = sum;
+                sum += tiles[q];
+            }
+            grid = h->lone_uneven ? dim3(sum) : dim3(*std::max_element(tiles.begin(), tiles.end()),
+                                                     static_cast<unsigned>(tiles.size()));
+        };
+        place(tiles_a, h->lone_tiles_a, h->lone_grid_a);
+        place(tiles_b, h->lone_tiles_b, h->lone_grid_b);
     }
     if (order.size() >= 2 && h->lone.empty()) {
         std::stable_sort(order.begin(), order.end(),

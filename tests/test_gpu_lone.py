@@ -113,3 +113,26 @@ def test_lone_long_pass(precision, nf, order, dk):
                 h.cavity_roundtrip(1)
             runs.append((h.get_fields(), h.energy_history()))
     assert np.array_equal(runs[0][0], runs[1][0]) and np.array_equal(runs[0][1], runs[1][1])
+
+
+@pytest.mark.parametrize("precision, nf, sizes", [
+    ("f32", 3, [10] * 20 + [18] + [11] * 20), ("f64", 2, [17, 12, 17] + [10] * 40), ("f64", 3, [15] + [10] * 47),
+    ("f32", 2, [18, 10]), ("f64", 3, [16, 10, 11])])
+def test_lone_uneven_launches(precision, nf, sizes):
+    """Uneven instances with a shape that the one-launch pass does not serve: a layer of the
+    grid each, or one after another where many layers would idle. Against the oracle; members
+    of one shape and one set of fields agree bit for bit."""
+    print("lone uneven launches %s nf %d %s x%d" % (precision, nf, sizes[:3], len(sizes)), file=sys.stderr, flush=True)
+    member = {l: _instance(1 << l, nf, 90 + l, dk=0.3) for l in set(sizes)}
+    nz, dz = 5, 0.125
+    with B.Opo([member[l] for l in sizes], nz, precision=precision) as h:
+        h.ssfm_propagate(nz, dz)
+        got = [h.get_fields(i) for i in range(len(sizes))]
+    for l, ins in member.items():
+        ref = oracle.ssfm_pass(ins["crystal"], ins["fields"], nz, dz)
+        mine = [g for g, s in zip(got, sizes) if s == l]
+        tol = TOL[precision] + phase_rounding(ins["crystal"], nz, dz)
+        for x in range(nf):
+            assert rel_l2(mine[0][x], ref[x]) <= tol, (l, x, rel_l2(mine[0][x], ref[x]), tol)
+        for g in mine[1:]:
+            assert np.array_equal(g, mine[0]), l
