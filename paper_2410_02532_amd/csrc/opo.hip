@@ -1209,9 +1209,11 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
             h->lone_ln1 = std::max(h->lone_ln1, d.log2n1);
             h->team = h->team && team_shape(d.log2n2, d.log2n1, d.nf);
         }
-        // the largest first: the tiles of an instance then start at a multiple of eight
-        if (!h->team)
-            std::stable_sort(h->lone.begin(), h->lone.end(), [&](int x, int y) { return h->inst[x].nt > h->inst[y].nt; });
+        // the largest first: in a grid of tiles one after another an instance then starts at a
+        // multiple of eight, and the waves that a team has no place for take up lists that are
+        // no larger (two waves, 2^15 and 2^10 in turn, nine of each: a 2^15 taken up by the few
+        // waves of a finished 2^10 held the launch up: 47.5 -> 12.9 us a z-step in FP32)
+        std::stable_sort(h->lone.begin(), h->lone.end(), [&](int x, int y) { return h->inst[x].nt > h->inst[y].nt; });
         std::vector<unsigned> tiles_a, tiles_b;
         for (int i : h->lone) {
             const InstDesc &d = h->inst[i];
