@@ -491,10 +491,6 @@ __device__ __forceinline__ void block_sum3(double v[3], double *scratch /* [3*kT
         }
 }
 
-struct ColumnShared {
-    double red[3 * kThreads / 64];
-};
-
 // ------------------------------------------------------------------------
 // The column FFTs of the NF fields of a tile: all fields through LDS
 // together, or one after another for the large columns (col_seq_lds).
@@ -522,8 +518,8 @@ __device__ __forceinline__ void column_fft(cplx<R> (&v)[NF][PF], cplx<R> *s, con
 
 // Column pass of one tile: COLS columns j1 = c0 + c of the NF fields.
 // Thread (c, t) holds samples j2 (or k2) = t + m*T, m < PF, of column c.
-// (ERR: with the error sums of the adaptive step.)
-template <typename R, int LN2, int NF, bool ERR>
+// (ADAPT: launches of the adaptive step, with its steps and error sums.)
+template <typename R, int LN2, int NF, bool ADAPT>
 __device__ __forceinline__ void column_tile(const StepArgs<R> &a, const InstDesc &d, int tile,
                                             cplx<R> *s, Coupling<R> *cpl, double *red)
 {
@@ -549,7 +545,7 @@ __device__ __forceinline__ void column_tile(const StepArgs<R> &a, const InstDesc
 
     double dz = a.dz_arg > 0.0 ? a.dz_arg : d.length_mm / a.nz;
     double zb = a.dz_arg > 0.0 ? a.zbase : 0.0;
-    if (a.adapt) {
+    if constexpr (ADAPT) {
         const AdaptState &st = a.adapt[a.inst_only > 0 ? a.inst_only - 1 : a.tile_inst[tile]];
         dz = st.dz * a.adapt_scale;
         zb = st.z;
@@ -657,7 +653,7 @@ __device__ __forceinline__ void column_tile(const StepArgs<R> &a, const InstDesc
         v[1][m] = y1;
         if constexpr (NF == 3) v[2][m] = y2;
     }
-    if (ERR && (flags & A_ERROR)) {
+    if (ADAPT && (flags & A_ERROR)) {
         const V *ec = a.err + d.off;
 #pragma unroll
         for (int m = 0; m < PF; ++m)
@@ -671,7 +667,7 @@ __device__ __forceinline__ void column_tile(const StepArgs<R> &a, const InstDesc
                     en[1] += fx * fx + fy * fy;
                 }
     }
-    if (flags & (ERR ? A_ENERGY | A_ERROR : A_ENERGY)) {
+    if (flags & (ADAPT ? A_ENERGY | A_ERROR : A_ENERGY)) {
         block_sum3(en, red);
         if (threadIdx.x == 0 && !stopped)
             for (int x = 0; x < 3; ++x)
@@ -701,18 +697,20 @@ __device__ __forceinline__ void column_tile(const StepArgs<R> &a, const InstDesc
     }
 }
 
-template <typename R, int L, int HI, int NF, bool ERR>
+template <typename R, int L, int HI, int NF, bool ADAPT>
 __device__ __forceinline__ void column_dispatch(const StepArgs<R> &a, const InstDesc &d, int tile, cplx<R> *s,
                                                 Coupling<R> *cpl, double *red)
 {
-    if (d.log2n2 == L) column_tile<R, L, NF, ERR>(a, d, tile, s, cpl, red);
-    else if constexpr (L < HI) column_dispatch<R, L + 1, HI, NF, ERR>(a, d, tile, s, cpl, red);
+    if (d.log2n2 == L) column_tile<R, L, NF, ADAPT>(a, d, tile, s, cpl, red);
+    else if constexpr (L < HI) column_dispatch<R, L + 1, HI, NF, ADAPT>(a, d, tile, s, cpl, red);
 }
 
 // Column pass over the tiles of NF-wave instances whose log2 n2 lies in [LO, HI].
-// ADAPT: launches of the adaptive step. Its second layer and error sums in one kernel with
-// the rest made every other launch longer (one 2^14 instance in FP64 on the forced two-pass
-// schedule 14.1 -> 14.5 us a z-step; now 14.0, and the adaptive step 1.3 % faster too).
+// ADAPT: launches of the adaptive step. With its second layer, steps and error sums as
+// run-time branches of one kernel every other launch was longer (one 2^14 instance on the
+// forced two-pass schedule, us a z-step: 14.7 without the adaptive step's layers, 15.0 with
+// its steps still a branch, 14.6 with everything of it compiled out; FP64 14.35, 14.23,
+// 14.11; 2^18 27.1, 26.7, 26.0).
 template <typename R, int LO, int HI, int NF, bool ADAPT>
 __global__ __launch_bounds__(kThreads) void column_pass(StepArgs<R> a)
 {
@@ -737,7 +735,7 @@ __global__ __launch_bounds__(kThreads) void column_pass(StepArgs<R> a)
 // 4 PF registers, which the standalone row pass of a launch too small to hide
 // latency can spare (one 2^14 instance 5 % faster, a 2^18 one 10 %) and the mixed
 // kernel, bound by its occupancy, cannot (the batched sweep 4 % slower).
-template <typename R, int LN1, bool PRE>
+template <typename R, int LN1, bool PRE, bool ADAPT>
 __device__ __forceinline__ void row_tile(const StepArgs<R> &a, const InstDesc &d, int tile, cplx<R> *s)
 {
     using V = cplx<R>;
@@ -761,11 +759,11 @@ __device__ __forceinline__ void row_tile(const StepArgs<R> &a, const InstDesc &d
     for (int m = 0; m < PF; ++m)
         v[0][m] = act ? g[m * T] : mk<V>(R(0), R(0));
     // H_f(k)/nt from the instance's table, laid out like the rows
-    const long long toff = a.adapt ? d.off : d.disp_off;
+    const long long toff = ADAPT ? d.off : d.disp_off;
     const Phasor<R> *h = a.disp + toff + static_cast<long long>(a.disp_sel * d.nf + f) * nt +
                          static_cast<long long>(N) * k2 + t;
     Phasor<R> hr[PRE ? PF : 1];
-    const bool pre = PRE && (flags & B_DISP) && !(flags & B_FWD_ONLY) && !a.adapt;
+    const bool pre = PRE && (flags & B_DISP) && !(flags & B_FWD_ONLY) && !ADAPT;
     if constexpr (PRE) {
         if (pre) {
 #pragma unroll
@@ -787,7 +785,7 @@ __device__ __forceinline__ void row_tile(const StepArgs<R> &a, const InstDesc &d
 #pragma unroll
             for (int m = 0; m < PF; ++m)
                 if (act) v[0][m] = pmul(v[0][m], h[m * T]);
-            if (a.adapt && a.adapt_scale == 1.0) {   // adaptive coarse step: H(dz)/nt = (H(dz/2)/nt)^2 nt
+            if (ADAPT && a.adapt_scale == 1.0) {   // adaptive coarse step: H(dz)/nt = (H(dz/2)/nt)^2 nt
                 const R scale = static_cast<R>(nt);      // a power of two: exact
 #pragma unroll
                 for (int m = 0; m < PF; ++m)
@@ -817,11 +815,11 @@ __device__ __forceinline__ void row_tile(const StepArgs<R> &a, const InstDesc &d
             g[m * T] = v[0][m];
 }
 
-template <typename R, int L, int HI, bool PRE>
+template <typename R, int L, int HI, bool PRE, bool ADAPT>
 __device__ __forceinline__ void row_dispatch(const StepArgs<R> &a, const InstDesc &d, int tile, cplx<R> *s)
 {
-    if (d.log2n1 == L) row_tile<R, L, PRE>(a, d, tile, s);
-    else if constexpr (L < HI) row_dispatch<R, L + 1, HI, PRE>(a, d, tile, s);
+    if (d.log2n1 == L) row_tile<R, L, PRE, ADAPT>(a, d, tile, s);
+    else if constexpr (L < HI) row_dispatch<R, L + 1, HI, PRE, ADAPT>(a, d, tile, s);
 }
 
 // Row pass over the tiles of instances whose log2 n1 lies in [LO, HI].
@@ -835,7 +833,7 @@ __global__ __launch_bounds__(kThreads) void row_pass(StepArgs<R> a)
         if (a.adapt[ii].status != 0) return;
         second_layer(a);
     }
-    row_dispatch<R, LO, HI, true>(a, a.inst[ii], tile, reinterpret_cast<cplx<R> *>(lds_raw));
+    row_dispatch<R, LO, HI, true, ADAPT>(a, a.inst[ii], tile, reinterpret_cast<cplx<R> *>(lds_raw));
 }
 
 // Size ranges served by one launch: shapes of similar register use share a
@@ -882,7 +880,7 @@ __global__ __launch_bounds__(kThreads, (mixed_min_blocks<R, CR, RR>())) void mix
                                                                  red);
     } else {
         const int tile = -1 - code;
-        row_dispatch<R, kRowRanges[RR][0], kRowRanges[RR][1], false>(ar, ar.inst[ar.tile_inst[tile]], tile, s);
+        row_dispatch<R, kRowRanges[RR][0], kRowRanges[RR][1], false, false>(ar, ar.inst[ar.tile_inst[tile]], tile, s);
     }
 }
 
