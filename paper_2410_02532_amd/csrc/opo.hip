@@ -1390,7 +1390,17 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
     constexpr long long kLastCache = 256LL << 20;
     const long long state = total_points * (opt.precision == OPO_F64 ? 16 : 8);
     bool long_rows = true;   // of 2^10 points or more
-    for (int i : order) long_rows = long_rows && h->inst[i].log2n1 >= 10;
+    std::map<int, long long> of_size;
+    for (int i : order) {
+        long_rows = long_rows && h->inst[i].log2n1 >= 10;
+        of_size[h->inst[i].nt] += h->inst[i].nt;
+    }
+    long long two_pass_points = 0, largest_size = 0;
+    for (const auto &e : of_size) {
+        two_pass_points += e.second;
+        largest_size = std::max(largest_size, e.second);
+    }
+    const bool one_size = 4 * largest_size > 3 * two_pass_points;   // nearly
     std::vector<MidTile> mid_maps[kMidMaps];
     if (h->mixed && batched && opt.schedule == 0 && h->groups_a[0].ln == h->groups_a[1].ln &&
         h->groups_a[0].nf == h->groups_a[1].nf && (h->groups_b[0].ln == 2) == (h->groups_b[1].ln == 2)) {
@@ -1419,15 +1429,26 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
                     else rows.push_back({i, -1 - t});
                 }
             }
-            // Row tile t on XCD t mod 8, as in the mixed launches. Long columns, and FP64
-            // where the fields just exceed the last cache level: tile t of every instance
-            // together, columns on XCD t mod 8 too, so that the tables an XCD's L2 cannot
-            // hold are read once for all instances; else instance by instance. Measured, by
-            // instance / by tile: 8 x 2^20 in FP32 30.9 / 29.7 ms a round trip, the FP32 sweep
-            // 16.8 / 17.1; FP64, us a z-step: 2^12..2^15 x 256 (188 MB) 141 / 147, 2^12..2^16
-            // x 200 (244 MB) 189 / 193, x 256 (316 MB) 302 / 296, 2^13 x 700 (275 MB) 251 / 230,
-            // 2^13..2^16 x 256 (377 MB) 367 / 380, 2^16 x 200 (629 MB) 610 / 650
-            const bool by_tile = h->mid_cr > 0 || (f64 && state > kLastCache && state <= kLastCache * 5 / 4);
+            // Row tile t on XCD t mod 8, as in the mixed launches. Instance by instance, or tile
+            // t of every instance together and columns on XCD t mod 8 too.
+            // By tile where columns are long: the tables an XCD's L2 cannot hold are then read
+            // once for all instances (8 x 2^20 in FP32 30.9 -> 29.7 ms a round trip; FP64 and
+            // FP32, two to sixteen of 2^18 .. 2^20, 0 to 10 % faster).
+            // By tile, FP64 and three waves, where the fields just exceed the last cache level:
+            // in instance order each line comes again only after all the fields have passed and
+            // is gone, in tile order a column tile's lines are spread over the next launch's
+            // rows and part of them come sooner. That gain falls as the fields grow, and what
+            // tile order costs (pieces of every instance at once) remains: by tile / by instance
+            // at 264, 280, 290, 300, 310, 330 MiB: 2^12..2^16 0.94 0.95 0.97 0.98 0.98 1.01,
+            // 2^13..2^16 0.94 0.93 0.94 0.96 0.97 0.99; one size: 2^13 0.93 0.93 0.96 0.98 0.99
+            // 1.00, 2^15 0.98 0.97 1.01 1.03 1.04 1.06, 2^16 0.98 0.98 1.00 1.03 1.04 1.05;
+            // below 256 MiB 1.00 to 1.03. Hence up to 1.2 of the cache, 1.125 where one size holds
+            // more than three quarters of the points. Two waves never: instances then lie at
+            // powers of two and the same tile of each meets in few memory channels (one size,
+            // 264 .. 310 MiB: 2^12 1.6, 2^15 1.04 to 1.10, 2^16 1.15).
+            const bool by_tile = h->mid_cr > 0 ||
+                                 (f64 && h->mid_nf == 3 && state > kLastCache &&
+                                  state <= (one_size ? kLastCache * 9 / 8 : kLastCache * 6 / 5));
             if (by_tile) {
                 std::stable_sort(cols.begin(), cols.end(), [](const MidTile &p, const MidTile &q) { return p.code < q.code; });
                 std::stable_sort(rows.begin(), rows.end(), [](const MidTile &p, const MidTile &q) { return p.code > q.code; });
