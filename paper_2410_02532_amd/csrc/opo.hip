@@ -1415,6 +1415,19 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
             h->mid = h->mid && d.log2n2 >= kMidMinLog2N2 && d.log2n1 >= kMidMinLog2N1 &&
                      (f64 || mid_faster_f32(d.nf, d.log2n2, d.log2n1));
         }
+        // Three waves, FP32, long columns: a CU holds two workgroups of mid_pass (180 registers)
+        // and three of mixed_pass (129). Launches that fit the chip at once only at three stay
+        // with mixed_pass (two instances of 2^19, 640 workgroups: 64 us a z-step, 69 with
+        // mid_pass; three of them, 896 and 1024: 92 and 84)
+        for (int ch = 0; h->mid && !f64 && h->mid_cr > 0 && h->mid_nf == 3 && ch < 2; ++ch) {
+            long long groups = 0;
+            for (int i : order) {
+                const InstDesc &d = h->inst[i];
+                groups += half[i] == ch ? d.n1 / mid_cols<float>(d.log2n2)
+                                        : (d.nf * d.n2 + mid_rows<float>(d.log2n1) - 1) / mid_rows<float>(d.log2n1);
+            }
+            h->mid = groups <= 2LL * prop.multiProcessorCount || groups > 3LL * prop.multiProcessorCount;
+        }
         for (int ch = 0; h->mid && ch < 2; ++ch) {
             std::vector<MidTile> cols, rows, qc[kXcd], qr[kXcd], none[kXcd];
             for (int i : order) {
