@@ -46,13 +46,16 @@ __host__ __device__ inline void substep(int order, int i, double &z, double &tau
 
 // Couplings of the column launches at step boundaries s0 .. s0 + count - 1 of a pass:
 // entry (s - s0) n + i is boundary s of instance i, with the second half-step of step
-// s - 1 and the first of step s, formed as in coupling_tile. Six threads an entry.
+// s - 1 and the first of step s, formed as in coupling_tile. Six threads an entry. Clears
+// `cleared` ints at `clear` too (what a launch behind it starts from).
 template <typename R>
 __global__ __launch_bounds__(kThreads) void coupling_table(const InstDesc *inst, int n, int order, double dz_arg,
-                                                           double zbase, int nz, int s0, int count, Coupling<R> *out)
+                                                           double zbase, int nz, int s0, int count, Coupling<R> *out,
+                                                           int *clear, int cleared)
 {
     using V = cplx<R>;
     const int id = blockIdx.x * kThreads + threadIdx.x, e = id / 6, q = id - 6 * e;
+    for (int w = id; w < cleared; w += gridDim.x * kThreads) clear[w] = 0;
     if (e >= count * n) return;
     const int s = s0 + e / n, which = q / 3, st = q - 3 * which;
     const InstDesc &d = inst[e % n];

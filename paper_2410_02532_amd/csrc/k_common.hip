@@ -1,6 +1,6 @@
 // k_common.hip -- the kernels that are not templates: the adaptive step's
 // control decision, the per-round-trip energy reduction and the counter reset.
-#include "team_kernels.h"
+#include "ssfm_kernels.h"
 
 namespace opo {
 
@@ -134,12 +134,6 @@ __global__ __launch_bounds__(kThreads) void spectrum_prep(const InstDesc *inst, 
     }
     if (threadIdx.x < 4) counter[threadIdx.x] = 0;
     for (int q = threadIdx.x; q < map_len; q += kThreads) map[q] = 0;
-}
-
-__global__ __launch_bounds__(kThreads) void team_init(TeamSync *sync, int count)
-{
-    for (int q = threadIdx.x; q < count * static_cast<int>(sizeof(TeamSync) / sizeof(int)); q += kThreads)
-        reinterpret_cast<int *>(sync)[q] = 0;
 }
 
 } // namespace opo

@@ -2,5 +2,5 @@
 #include "kernel_list.h"
 
 namespace opo {
-OPO_TEAM_KERNELS(template, double)
+OPO_TEAM_KERNELS_F64(template)
 } // namespace opo

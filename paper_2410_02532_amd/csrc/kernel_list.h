@@ -80,10 +80,17 @@
     DECL __global__ void lone_row_uneven<R, 9>(LoneRowArgs<R>, LoneTiles);                         \
     DECL __global__ void lone_row_uneven<R, 12>(LoneRowArgs<R>, LoneTiles);
 
-// All interior steps of small instances in one launch.
+// All interior steps of small instances in one launch, or a phase of them.
 #define OPO_TEAM_KERNELS(DECL, R)                                                                  \
-    DECL __global__ void team_pass<R, 2>(TeamArgs<R>);                                             \
-    DECL __global__ void team_pass<R, 3>(TeamArgs<R>);
+    DECL __global__ void team_pass<R, 2, false>(TeamArgs<R>);                                      \
+    DECL __global__ void team_pass<R, 3, false>(TeamArgs<R>);                                      \
+    DECL __global__ void team_phase<R, 2>(TeamArgs<R>);                                            \
+    DECL __global__ void team_phase<R, 3>(TeamArgs<R>);
+
+#define OPO_TEAM_KERNELS_F64(DECL)                                                                 \
+    OPO_TEAM_KERNELS(DECL, double)                                                                 \
+    DECL __global__ void team_pass<double, 2, true>(TeamArgs<double>);                             \
+    DECL __global__ void team_pass<double, 3, true>(TeamArgs<double>);
 
 // Launches inside a pass of batches: columns of 2^4..2^6, 2^7 or 2^8 points (0, 1, 2), rows
 // of 2^5..2^11, or 2^12 (FP32). The longer columns come with the longest rows.
@@ -91,7 +98,7 @@
     DECL __global__ void mid_pass<R, 5, 11, 2, 0>(MidArgs<R>);                                     \
     DECL __global__ void mid_pass<R, 5, 11, 3, 0>(MidArgs<R>);                                     \
     DECL __global__ void coupling_table<R>(const InstDesc *, int, int, double, double, int, int,   \
-                                           int, Coupling<R> *);
+                                           int, Coupling<R> *, int *, int);
 
 #define OPO_MID_KERNELS_F32(DECL)                                                                  \
     OPO_MID_KERNELS(DECL, float)                                                                   \
@@ -123,7 +130,7 @@
     OPO_LONE_KERNELS(DECL, float)                                                                  \
     OPO_LONE_KERNELS(DECL, double)                                                                 \
     OPO_TEAM_KERNELS(DECL, float)                                                                  \
-    OPO_TEAM_KERNELS(DECL, double)                                                                 \
+    OPO_TEAM_KERNELS_F64(DECL)                                                                     \
     OPO_MID_KERNELS_F32(DECL)                                                                      \
     OPO_MID_KERNELS_F64(DECL)                                                                      \
     OPO_RESIDENT_KERNELS(DECL)

@@ -224,9 +224,17 @@ static const void *edge_fn(int nf)
                    : reinterpret_cast<const void *>(&edge_pass<float, 3>);
 }
 
-template <typename R> static const void *team_fn(int nf)
+// team_pass of nf-wave instances, or a single phase of it.
+template <typename R> static const void *team_fn(int nf, bool again, bool single)
 {
-    return nf == 2 ? reinterpret_cast<const void *>(&team_pass<R, 2>) : reinterpret_cast<const void *>(&team_pass<R, 3>);
+    if (single)
+        return nf == 2 ? reinterpret_cast<const void *>(&team_phase<R, 2>) : reinterpret_cast<const void *>(&team_phase<R, 3>);
+    if constexpr (sizeof(R) == 8)
+        if (again)
+            return nf == 2 ? reinterpret_cast<const void *>(&team_pass<R, 2, true>)
+                           : reinterpret_cast<const void *>(&team_pass<R, 3, true>);
+    return nf == 2 ? reinterpret_cast<const void *>(&team_pass<R, 2, false>)
+                   : reinterpret_cast<const void *>(&team_pass<R, 3, false>);
 }
 
 // Lone kernels (lone_kernels.h): columns of nf-wave instances, rows of up to 2^ln points.
@@ -289,6 +297,9 @@ struct opo_s {
     bool lone_spread = false;        // see lone_col_pf
     bool team = false;               // ... or team_pass (team_kernels.h)
     TeamSync *d_team = nullptr;
+    int team_first[9] = {};          // TeamArgs::first over `lone`
+    unsigned team_waves = 0;         // workgroups of a class
+    bool team_again = false;         // team_pass: AGAIN
     size_t lone_lds_b = 0;
     int lone_nf = 3, lone_ln1 = 0, lone_threads_b = 64;
     bool mixed = false;              // two halves a launch apart, mixed launches
@@ -799,13 +810,16 @@ template <typename R> static hipError_t launch_mixed(opo_t *h, StepArgs<R> a, in
 // Flags of a column launch inside a pass (no round-trip boundary).
 static constexpr int kInterior = A_INV | A_RK_PREV | A_RK_THIS | A_FWD;
 
-// Couplings of the step boundaries from s0 on (of crystal `stage`) into d_coef.
-template <typename R> static hipError_t fill_couplings(opo_t *h, const StepArgs<R> &a, int s0, int boundaries)
+// Couplings of the step boundaries from s0 on (of crystal `stage`) into d_coef; clears the
+// teams for a launch of team_pass.
+template <typename R>
+static hipError_t fill_couplings(opo_t *h, const StepArgs<R> &a, int s0, int boundaries, bool teams = false)
 {
     const int count = std::min(h->coef_chunk + 1, boundaries - s0);
     const unsigned blocks = (6u * count * h->n_inst + kThreads - 1) / kThreads;
     coupling_table<R><<<blocks, kThreads, 0, h->stream>>>(a.inst, h->n_inst, h->order, a.dz_arg, a.zbase, a.nz, s0, count,
-                                                          static_cast<Coupling<R> *>(h->d_coef));
+                                                          static_cast<Coupling<R> *>(h->d_coef), reinterpret_cast<int *>(h->d_team),
+                                                          teams ? static_cast<int>(h->lone.size() * sizeof(TeamSync) / 4) : 0);
     return hipGetLastError();
 }
 
@@ -869,7 +883,9 @@ template <typename R> static hipError_t launch_lone_b(opo_t *h, const StepArgs<R
     return prof_end(h);
 }
 
-// Phases begin .. end - 1 of the team instances (TeamArgs) from step s0 on, in one launch.
+// Phases begin .. end - 1 of the team instances (TeamArgs) from step s0 on, in one launch
+// behind the fill of its couplings. A single phase needs no teams: the grid holds every
+// instance's waves.
 template <typename R>
 static hipError_t launch_team(opo_t *h, const StepArgs<R> &a, int s0, int begin, int end, int open, int close, int stage)
 {
@@ -890,19 +906,21 @@ static hipError_t launch_team(opo_t *h, const StepArgs<R> &a, int s0, int begin,
     t.close = close;
     t.s0 = s0;
     t.order = h->order;
+    const bool single = end == begin + 1;
+    std::copy(std::begin(h->team_first), std::end(h->team_first), t.first);
+    unsigned want = 8;   // of the largest list
     const InstDesc *inst = h->inst.data() + static_cast<size_t>(stage) * h->n_inst;
     for (size_t q = 0; q < h->lone.size(); ++q) {
         const InstDesc &d = inst[h->lone[q]];
-        const int rows = d.nf * d.n2, per = team_rows(d.log2n1);
+        const int rows = d.nf * d.n2;
         t.inst[q] = {d.off, d.w4_off, d.disp_off, d.nt, d.n1, d.log2n1, d.log2n2, rows,
-                     d.kerr ? 2 : d.dk_rev == 0.0 ? 0 : 1, h->lone[q],
-                     std::min(kTeamMax, std::max(d.n1 / kTeamCols, (rows + per - 1) / per))};
+                     d.kerr ? 2 : d.dk_rev == 0.0 ? 0 : 1, h->lone[q], team_want(d.n1, d.log2n1, rows)};
+        want = std::max(want, (t.inst[q].want + 7u) & ~7u);
     }
-    team_init<<<1, kThreads, 0, h->stream>>>(h->d_team, t.count);
-    HIP_RET(hipGetLastError());
     void *args[] = {&t};
-    HIP_RET(prof_begin(h, OPO_K_MIXED));
-    HIP_RET(hipLaunchKernel(team_fn<R>(h->lone_nf), dim3(8 * kTeamMax), dim3(64), args, 0, h->stream));
+    HIP_RET(prof_begin(h, !single ? OPO_K_MIXED : begin & 1 ? OPO_K_ROW : OPO_K_COLUMN));
+    HIP_RET(hipLaunchKernel(team_fn<R>(h->lone_nf, h->team_again, single), single ? dim3(want, t.count) : dim3(8 * h->team_waves), dim3(64), args,
+                            0, h->stream));
     return prof_end(h);
 }
 
@@ -946,12 +964,20 @@ static hipError_t enqueue_pass(opo_t *h, StepArgs<R> a, int nz_steps, int first,
         }
         return launch_lone_a<R>(h, a, flags, step - held, stage);
     };
+    if (h->team && team_too_short(static_cast<int>(h->lone.size()), nz)) {   // a launch a phase
+        if (first) HIP_RET(launch_a<R>(h, a, first | A_RK_THIS | A_FWD, 0));
+        const int begin = first ? 1 : 0, end = last ? 2 * nz : 2 * nz + 1;
+        if (end > begin + 1) HIP_RET(fill_couplings<R>(h, a, 0, nz + 1));
+        for (int ph = begin; ph < end; ++ph)
+            HIP_RET(launch_team<R>(h, a, 0, ph, ph + 1, first ? -1 : 0, last ? -1 : 2 * nz, stage));
+        return last ? launch_a<R>(h, a, A_INV | A_RK_PREV | last, nz) : hipSuccess;
+    }
     if (h->team) {
         // the boundary's launches only where there is something of the boundary to do
         if (first) HIP_RET(launch_a<R>(h, a, first | A_RK_THIS | A_FWD, 0));
         for (int s0 = 0; s0 < nz; s0 += h->coef_chunk) {
             const int s1 = std::min(nz, s0 + h->coef_chunk), steps = s1 - s0;
-            HIP_RET(fill_couplings<R>(h, a, s0, nz + 1));
+            HIP_RET(fill_couplings<R>(h, a, s0, nz + 1, true));
             const bool open = s0 == 0 && !first, close = s1 == nz && !last;
             HIP_RET(launch_team<R>(h, a, s0, open ? 0 : 1, s1 == nz && last ? 2 * steps : 2 * steps + 1, open ? 0 : -1,
                                    close ? 2 * steps : -1, stage));
@@ -1118,6 +1144,18 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
         one_nf = one_nf && nfields(f[i]) == nfields(f[0]);
         few = few && one_nf && ilog2(f[i].nt) >= kLoneMinLog2;
     }
+    if (few) {
+        // handles whose passes the teams would run, but too short for them
+        bool team = true;
+        for (int i = 0; i < n && team; ++i) {
+            const int l2 = ilog2(f[i].nt);
+            const Plan p = make_plan(f[i].nt, opt.precision, opt.col_log2 != 0 ? opt.col_log2 : lone_split(l2));
+            team = team_shape(p.log2n2, p.log2n1, nfields(f[i]));
+        }
+        long long steps = 0;
+        for (int st = 0; st < K; ++st) steps += c[st].nz * (h->order == 4 ? 3LL : 1LL);
+        few = !team || steps >= static_cast<long long>(K) * team_min_steps(n);
+    }
     // schedule: the table's entry for each shape (schedule 0), or two-pass (1) / resident
     // where served (2); an explicit col_log2 sets the split
     const bool f64 = opt.precision == OPO_F64;
@@ -1241,6 +1279,27 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
         };
         place(tiles_a, h->lone_tiles_a, h->lone_grid_a);
         place(tiles_b, h->lone_tiles_b, h->lone_grid_b);
+        if (h->team) {
+            // lists dealt to the eight classes of workgroups, largest first, each to the class
+            // with the fewest waves so far; as many workgroups as its lists have places (a
+            // list needs them, and every other one is a claim that the rest wait behind)
+            std::vector<int> of_class[8];
+            unsigned waves[8] = {};
+            for (int i : h->lone) {
+                const InstDesc &d = h->inst[i];
+                const int c = static_cast<int>(std::min_element(waves, waves + 8) - waves);
+                of_class[c].push_back(i);
+                waves[c] += team_want(d.n1, d.log2n1, d.nf * d.n2);
+            }
+            h->lone.clear();
+            for (int c = 0; c < 8; ++c) {
+                h->lone.insert(h->lone.end(), of_class[c].begin(), of_class[c].end());
+                h->team_first[c + 1] = static_cast<int>(h->lone.size());
+                h->team_waves = std::max(h->team_waves, waves[c]);
+            }
+            h->team_again = f64 && h->team_waves > static_cast<unsigned>(kTeamMax);
+            if (h->team_again) h->team_waves = kTeamMax;
+        }
     }
     if (order.size() >= 2 && h->lone.empty()) {
         std::stable_sort(order.begin(), order.end(),

@@ -12,11 +12,13 @@
 // leader came. A member never waits for a wave that may not have started, so a team
 // makes progress whatever else the GPU runs; one that closes early is only slower (its
 // members then share the tiles out among fewer). The results do not depend on the
-// team's size. A list that another XCD has claimed is left to it; one that nobody has
-// claimed is taken by the first wave that finds it so, so every list is worked on, also
-// on a partition of the device with fewer XCDs. A wait that makes kTeamSpin polls gives up:
-// it raises a flag, which the host reads when it has waited for the stream, and the launch
-// ends with fields that are not those of the pass.
+// team's size. Workgroups are dealt to the XCDs in turn: those of one class (their number
+// modulo eight) share one, and the lists are dealt to the classes. A wave joins the first
+// list of its class that nobody has claimed, or that its XCD has and where a place is left.
+// A class has as many waves as its lists have places together, so every list gets some,
+// wherever its workgroups run. A wait that makes kTeamSpin polls gives up: it raises a flag,
+// which the host reads when it has waited for the stream, and the launch ends with fields
+// that are not those of the pass.
 //
 // Coherent without fences: a team's waves share the L2 of the XCD they run on (XCC_ID)
 // and the L1 is write-through. Stores are waited for (vmcnt) before the flag is set;
@@ -47,12 +49,30 @@ constexpr bool team_shape(int log2n2, int log2n1, int nf)
 {
     return (log2n2 == 5 && log2n1 >= 5 && log2n1 <= 9) || (log2n2 == 6 && log2n1 == 9 && nf == 2);
 }
+// A launch of teams has its price: claims, the members' arrival, and with more lists than
+// places at once the wait for members that do not come (about 8 us with one list, 16 with
+// 16, 40 to 60 with 32 to 48). A handle of n instances runs them if its round trips have at
+// least team_min_steps(n) symmetrized steps a crystal on average, else what it ran before
+// them (us a round trip of nz steps, before / teams: FP32 2^14, nz 2 42.5 / 48.5, 4 66.5 /
+// 54.9; 48 of 2^10, nz 2 51 / 68, 8 145 / 93; 32 of 2^13, nz 4 104 / 146, 8 185 / 178; FP64
+// 48 of 2^10, nz 8 93 / 96, 20 209 / 145).
+constexpr int team_min_steps(int n) { return 3 + n / 6; }
+// Calls of ssfm_propagate with fewer steps than the handle's round trips: many lists take a
+// launch a phase (us a call, teams / a launch a phase: one 2^10, 1 step 11.5 / 19.9; 16 of
+// them 19.4 / 20.9; 48 45 / 23, 2 steps 50 / 36, 4 58 / 61; 40 of 2^12, 4 steps 105 / 99).
+constexpr bool team_too_short(int n, int steps) { return 12 * steps <= n; }
 constexpr int kTeamCols = 4;              // columns per wave: 2^5 points on 16 lanes of 2, 2^6 of 4
 constexpr int team_row_pf(int ln1) { return ln1 <= 8 ? 4 : 8; }
 constexpr int team_rows(int ln1) { return 64 * team_row_pf(ln1) >> ln1; }   // rows per wave
+// Waves of a full team: one for every tile, up to an XCD's.
+constexpr int team_want(int n1, int log2n1, int rows)
+{
+    const int c = n1 / kTeamCols, r = (rows + team_rows(log2n1) - 1) / team_rows(log2n1), w = c > r ? c : r;
+    return w < kTeamMax ? w : kTeamMax;
+}
 
 // Device memory of a list's team, zeroed before the launch.
-struct TeamSync {
+struct alignas(128) TeamSync {
     int owner;            // 1 + XCC_ID of the XCD that works on the list
     int join;             // waves arrived, and kTeamSealed
     int size;             // members, once closed
@@ -105,6 +125,7 @@ template <typename R> struct TeamArgs {
     // only the half-step and the transform on their inner side
     int begin, end, open, close;
     int s0, order;
+    int first[9];         // lists first[c] .. first[c + 1] - 1 are dealt to class c
     TeamInst inst[kLoneMax];
 };
 
@@ -231,39 +252,62 @@ __device__ __forceinline__ void team_run(const TeamArgs<R> &a, const TeamInst &d
     }
 }
 
-template <typename R, int NF> __global__ __launch_bounds__(64) void team_pass(TeamArgs<R> a)
+template <typename R, int NF>
+__device__ __forceinline__ void team_dispatch(const TeamArgs<R> &a, int list, int rank, int size, cplx<R> *s)
+{
+    const TeamInst &d = a.inst[list];
+    TeamSync *sync = a.sync + list;
+    if (d.log2n2 == 6) team_run<R, 6, 9, NF>(a, d, sync, rank, size, s);
+    else if (d.log2n1 == 5) team_run<R, 5, 5, NF>(a, d, sync, rank, size, s);
+    else if (d.log2n1 == 6) team_run<R, 5, 6, NF>(a, d, sync, rank, size, s);
+    else if (d.log2n1 == 7) team_run<R, 5, 7, NF>(a, d, sync, rank, size, s);
+    else if (d.log2n1 == 8) team_run<R, 5, 8, NF>(a, d, sync, rank, size, s);
+    else team_run<R, 5, 9, NF>(a, d, sync, rank, size, s);
+}
+
+// AGAIN: a wave that has done with its list joins a further one. FP64 handles whose lists
+// have more places than an XCD has SIMDs run it: 40 of 2^12 points, round trips of 20 steps,
+// 358 us with a workgroup for every place, the later ones started as SIMDs come free, 240
+// so. FP32 without it holds two waves a SIMD (247 -> 180).
+template <typename R, int NF, bool AGAIN> __global__ __launch_bounds__(64) void team_pass(TeamArgs<R> a)
 {
     __shared__ __align__(16) cplx<R> s[lds_elems<R>(512)];
     if (a.counter[2] != 0) return;   // a round trip of this call was not finite: store nothing
-    // workgroups are dealt to the XCDs in turn: with fewer lists than XCDs only as many
-    // XCDs take part (a claim contended by all of them costs 80 ns a wave)
-    if (static_cast<int>(blockIdx.x & 7) >= a.count) return;
-    const int xcc = xcc_id();
+    // (a class without lists has no part: a claim contended by all waves costs 80 ns a wave)
+    const int xcc = xcc_id(), cls = blockIdx.x & 7;
     const bool first_lane = threadIdx.x == 0;
-    for (int l = 0; l < a.count; ++l) {
-        const int list = (xcc + l) % a.count;
-        const TeamInst &d = a.inst[list];
-        TeamSync *sync = a.sync + list;
+    int list = a.first[cls];
+    do {
         int rank = -1;
-        if (first_lane) {
-            int seen = team_load(&sync->owner);   // 0: this wave claims the list
-            if (seen == 0)
-                __hip_atomic_compare_exchange_strong(&sync->owner, &seen, xcc + 1, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
-                                                     __HIP_MEMORY_SCOPE_AGENT);
-            if (seen == 0 || seen == xcc + 1) {
-                const int j = __hip_atomic_fetch_add(&sync->join, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (j < d.want) rank = j;   // a closed list's count is past kTeamSealed
+        for (; list < a.first[cls + 1]; ++list) {
+            TeamSync *sync = a.sync + list;
+            if (first_lane) {
+                // owner and join in one load: a list that is full or closed costs no atomic
+                const unsigned long long both = __hip_atomic_load(
+                    reinterpret_cast<const unsigned long long *>(&sync->owner), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                int seen = static_cast<int>(both);   // 0: this wave claims the list
+                if (static_cast<int>(both >> 32) >= a.inst[list].want) seen = -1;
+                if (seen == 0)
+                    __hip_atomic_compare_exchange_strong(&sync->owner, &seen, xcc + 1, __ATOMIC_RELAXED,
+                                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (seen == 0 || seen == xcc + 1) {
+                    const int j = __hip_atomic_fetch_add(&sync->join, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (j < a.inst[list].want) rank = j;   // a closed list's count is past kTeamSealed
+                }
             }
+            rank = __builtin_amdgcn_readfirstlane(rank);
+            if (rank >= 0) break;
         }
-        rank = __builtin_amdgcn_readfirstlane(rank);
-        if (rank < 0) continue;
+        if (rank < 0) return;
+        TeamSync *sync = a.sync + list;
         int size = 0, polls = 0;
         if (rank == 0) {
+            const int want = a.inst[list].want;
             const long long t0 = wall_clock64();
-            while (team_load(&sync->join) < d.want && wall_clock64() - t0 < kTeamWait) __builtin_amdgcn_s_sleep(1);
+            while (team_load(&sync->join) < want && wall_clock64() - t0 < kTeamWait) __builtin_amdgcn_s_sleep(1);
             if (first_lane) {
                 size = __hip_atomic_fetch_or(&sync->join, kTeamSealed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                size = size < d.want ? size : d.want;
+                size = size < want ? size : want;
                 __hip_atomic_store(&sync->size, size, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
             size = __builtin_amdgcn_readfirstlane(size);
@@ -271,17 +315,22 @@ template <typename R, int NF> __global__ __launch_bounds__(64) void team_pass(Te
             while ((size = __builtin_amdgcn_readfirstlane(team_load(&sync->size))) == 0)
                 if (team_give_up(polls, a.failed)) return;
         }
-        if (d.log2n2 == 6) team_run<R, 6, 9, NF>(a, d, sync, rank, size, s);
-        else if (d.log2n1 == 5) team_run<R, 5, 5, NF>(a, d, sync, rank, size, s);
-        else if (d.log2n1 == 6) team_run<R, 5, 6, NF>(a, d, sync, rank, size, s);
-        else if (d.log2n1 == 7) team_run<R, 5, 7, NF>(a, d, sync, rank, size, s);
-        else if (d.log2n1 == 8) team_run<R, 5, 8, NF>(a, d, sync, rank, size, s);
-        else team_run<R, 5, 9, NF>(a, d, sync, rank, size, s);
-    }
+        team_dispatch<R, NF>(a, list, rank, size, s);
+        ++list;
+    } while (AGAIN);
+}
+
+// A single phase, without teams: workgroup (x, y) is a member of list y.
+template <typename R, int NF> __global__ __launch_bounds__(64) void team_phase(TeamArgs<R> a)
+{
+    __shared__ __align__(16) cplx<R> s[lds_elems<R>(512)];
+    if (a.counter[2] != 0) return;
+    const int list = blockIdx.y, size = a.inst[list].want, x = blockIdx.x;
+    if (x >= size) return;
+    // neighbouring tiles, which share cache lines, on one XCD
+    team_dispatch<R, NF>(a, list, size & 7 ? x : (x & 7) * (size >> 3) + (x >> 3), size, s);
 }
 
 static_assert(sizeof(TeamArgs<float>) <= 4096 && sizeof(LoneColumnArgs<float>) <= 4096, "kernel arguments");
-
-__global__ __launch_bounds__(kThreads) void team_init(TeamSync *sync, int count);
 
 } // namespace opo

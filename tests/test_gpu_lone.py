@@ -136,3 +136,30 @@ def test_lone_uneven_launches(precision, nf, sizes):
             assert rel_l2(mine[0][x], ref[x]) <= tol, (l, x, rel_l2(mine[0][x], ref[x]), tol)
         for g in mine[1:]:
             assert np.array_equal(g, mine[0]), l
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("sizes, nf, dk, n2, order", [
+    ([10], 3, 0.0, 0.0, 2), ([11], 2, 0.6, 0.0, 2), ([12], 3, 0.6, 1e-17, 2), ([13], 3, 0.0, 1e-17, 4),
+    ([13], 2, 0.6, 0.0, 2), ([14], 3, 0.0, 0.0, 2), ([15], 2, 0.6, 0.0, 2), ([10, 14, 13] * 4, 2, 0.3, 0.0, 2),
+    ([11, 12, 13] * 8 + [10] * 24, 2, 0.3, 0.0, 2)])
+def test_one_launch_pass_cut_short(sizes, nf, dk, n2, order, precision):
+    """A pass in one launch and the same steps in shorter calls, of which the shortest of many
+    instances take a launch a phase, agree bit for bit; and with the oracle."""
+    print("one-launch pass cut short %s nf %d %s" % (sizes[:3], nf, precision), file=sys.stderr, flush=True)
+    member = {l: _instance(1 << l, nf, 30 + l, dk=dk, n2=n2) for l in set(sizes)}
+    dz, out = 2.0 ** -5, []
+    for calls in ((24,), (1, 1, 2, 3, 1, 16), (2, 1) * 8):
+        with B.Opo([member[l] for l in sizes], 24, precision=precision, split_order=order) as h:
+            for n in calls:
+                h.ssfm_propagate(n, dz)
+            out.append([h.get_fields(i) for i in range(len(sizes))])
+    for other in out[1:]:
+        for a, b in zip(out[0], other):
+            assert np.array_equal(a, b)
+    for l, ins in member.items():
+        ref = oracle.ssfm_pass(dict(ins["crystal"], order=order), ins["fields"], 24, dz)
+        got = out[0][sizes.index(l)]
+        tol = TOL[precision] + phase_rounding(ins["crystal"], 24 * (3 if order == 4 else 1), 2 * dz)
+        for x in range(nf):
+            assert rel_l2(got[x], ref[x]) <= tol, (l, x, rel_l2(got[x], ref[x]), tol)
