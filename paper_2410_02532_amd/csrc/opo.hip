@@ -2070,14 +2070,18 @@ template <typename R> static int spectrum_impl(opo_t *h, int inst, int field, do
     std::vector<double> tmp(2 * static_cast<size_t>(d.nt));
     const char *src = static_cast<const char *>(h->spec_buf) + (d.off + static_cast<long long>(field) * d.nt) * h->elem;
     HIP_TRY(state_to_host<R>(tmp.data(), src, d.nt, h->stream));
-    // position k2*n1 + k1 holds bin k2 + n2*k1
-    for (int k2 = 0; k2 < d.n2; ++k2)
-        for (int k1 = 0; k1 < d.n1; ++k1) {
-            const long long pos = static_cast<long long>(k2) * d.n1 + k1;
-            const long long bin = k2 + static_cast<long long>(d.n2) * k1;
-            out[2 * bin] = tmp[2 * pos];
-            out[2 * bin + 1] = tmp[2 * pos + 1];
-        }
+    // position k2*n1 + k1 holds bin k2 + n2*k1. A cache line of positions at a time, in the
+    // order of the bins (one 2^15 instance, three fields: row by row 590 us with columns of
+    // 2^6 and 330 with 2^4, so 314)
+    const int line = std::min(4, d.n1);
+    for (int k0 = 0; k0 < d.n1; k0 += line)
+        for (int k2 = 0; k2 < d.n2; ++k2)
+            for (int k1 = k0; k1 < k0 + line; ++k1) {
+                const long long pos = static_cast<long long>(k2) * d.n1 + k1;
+                const long long bin = k2 + static_cast<long long>(d.n2) * k1;
+                out[2 * bin] = tmp[2 * pos];
+                out[2 * bin + 1] = tmp[2 * pos + 1];
+            }
     return OPO_OK;
 }
 
