@@ -176,3 +176,54 @@ def test_fp32_batches_that_keep_mixed_pass(nf, log2nt, count, order):
             out.append([h.get_fields(i) for i in sorted({0, 1, min(2, count - 1), count - 1})])
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+@pytest.mark.parametrize("precision, nf, log2nt, count, col, order", [
+    ("f32", 3, 10, 344, 0, 4), ("f32", 3, 11, 174, 0, 4), ("f32", 2, 11, 258, 0, 4), ("f32", 3, 12, 87, 4, 4),
+    ("f32", 3, 13, 44, 4, 2), ("f32", 3, 14, 24, 5, 2), ("f64", 3, 9, 690, 0, 2), ("f64", 3, 10, 344, 0, 4),
+    ("f64", 2, 11, 258, 0, 4), ("f64", 3, 12, 87, 6, 2)])
+def test_batch_short_rows_and_columns(precision, nf, log2nt, count, col, order):
+    """Rows of 2^5 and 2^6 points and columns of 2^4 and 2^5 (the shapes that batches of small
+    grids, forced splits, fourth-order steps and several crystals reach): with and without
+    mismatch and Kerr terms against the oracle; equal members agree bit for bit."""
+    print("batch short %s nf %d 2^%d col %d order %d" % (precision, nf, log2nt, col, order), file=sys.stderr, flush=True)
+    members = _batch([log2nt] * 3, nf, 0.4, 1e-17)
+    nz, nrt = 5, 2
+    with B.Opo([members[b % 3] for b in range(count)], nz, precision=precision, col_log2=col, split_order=order) as h:
+        h.cavity_roundtrip(nrt)
+        got = [h.get_fields(i) for i in range(6)]
+        for i in range(count - 3, count):
+            assert np.array_equal(h.get_fields(i), got[i % 3]), i
+    for a, b in zip(got, got[3:]):
+        assert np.array_equal(a, b)
+    for ins, a in zip(members, got):
+        ref, _ = oracle.roundtrips(dict(ins["crystal"], order=order), ins["cavity"], ins["fields"], ins["pump_in"],
+                                   nz, nrt)
+        tol = TOL[precision] + phase_rounding(ins["crystal"], nz * nrt * (3 if order == 4 else 1), 5.0 / nz)
+        for x in range(nf):
+            assert rel_l2(a[x], ref[x]) <= tol, (x, rel_l2(a[x], ref[x]), tol)
+
+
+@pytest.mark.parametrize("precision, sizes, col", [
+    ("f32", [14] * 20 + [13] * 6, 0), ("f64", [14] * 20 + [13] * 6, 0),      # a batch
+    ("f32", [11, 11], 4), ("f64", [11, 11], 4),                               # a pair of launches a step
+    ("f32", [11, 13, 12], 0), ("f64", [11, 13, 12], 0)])                      # one launch a pass
+def test_crystals_with_their_own_tables(precision, sizes, col):
+    """Two crystals of other mismatch, dispersion and step count, the first longer than the
+    coupling table (128 steps): their descriptors, propagators and refilled couplings."""
+    print("two crystals %s %s x%d" % (precision, sizes[:2], len(sizes)), file=sys.stderr, flush=True)
+    insts, nzs, nrt = [], [131, 6], 2
+    for b, l in enumerate(sizes):
+        ins = _instance(1 << l, 3, 40 + b, dk=0.4 * (b % 2))
+        second = dict(ins["crystal"], dk_per_mm=-0.3, length_mm=3.0, n2_m2_per_w=1e-17 * (b % 2))
+        second["b2_fs2_per_mm"] = (-150.0, 100.0, 250.0)
+        insts.append(dict(ins, crystals=[ins["crystal"], second]))
+    with B.Opo(insts, nzs, precision=precision, col_log2=col) as h:
+        h.cavity_roundtrip(nrt)
+        got = [h.get_fields(i) for i in range(len(insts))]
+    for i in sorted({0, 1, len(sizes) - 1}):
+        ins = insts[i]
+        ref, _, _ = oracle.roundtrips_multi(ins["crystals"], nzs, ins["cavity"], ins["fields"], ins["pump_in"], nrt)
+        tol = TOL[precision] + sum(phase_rounding(c, n * nrt, c["length_mm"] / n) for c, n in zip(ins["crystals"], nzs))
+        for x in range(3):
+            assert rel_l2(got[i][x], ref[x]) <= tol, (i, x, rel_l2(got[i][x], ref[x]), tol)

@@ -3,6 +3,7 @@ reported by the next call that waits for the stream, and leaves the handle usabl
 its fields set again it gives what a fresh handle gives."""
 import ctypes
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 import numpy as np
 import pytest
@@ -78,3 +79,24 @@ def test_roundtrip_stops_at_a_wait_that_gave_up(precision, graph):
         h.cavity_roundtrip(2)
         assert np.array_equal(h.get_fields(), four)
         assert np.array_equal(h.energy_history(), energies)
+
+
+def test_handles_of_teams_beside_each_other():
+    """Four handles whose passes run in one launch each, driven from four threads at once (their
+    teams share XCDs), give what they give one after another."""
+    say("teams beside each other")
+    runs = [("f32", [_instance(1 << 14, 3, 11)]), ("f64", [_instance(1 << 14, 3, 12)]),
+            ("f32", [_instance(1 << l, 2, 13) for l in (13, 10, 15, 10, 12)]), ("f64", [_instance(1 << 10, 3, 14)] * 16)]
+
+    def work(precision, insts):
+        with B.Opo(insts, NZ, precision=precision) as h:
+            for _ in range(5):
+                h.ssfm_propagate(7, DZ)
+                h.cavity_roundtrip(3)
+            return [h.get_fields(i) for i in range(len(insts))], h.energy_history()
+
+    alone = [work(*r) for r in runs]
+    with ThreadPoolExecutor(len(runs)) as ex:
+        beside = [f.result(timeout=100) for f in [ex.submit(work, *r) for r in runs]]
+    for (fa, ea), (fb, eb) in zip(alone, beside):
+        assert all(np.array_equal(x, y) for x, y in zip(fa, fb)) and np.array_equal(ea, eb)
