@@ -37,10 +37,12 @@ struct LoneColumnInst {
 // Tiles of a launch over instances of uneven size, one after another along the grid:
 // first[q] is the first tile of instance q, the largest value past the last. (Otherwise
 // each instance takes a layer of the grid, as long as the largest one's. About 0.35 ns for
-// each idle workgroup of those layers, against 0.3 us for the search here: with more than
-// kLoneMaxIdle of them, in the column and row launch together, the search is the cheaper.
-// FP32, a 2^18 and 40 2^10 instances 40.6 us a z-step in layers, 23.0 with the search.)
-constexpr unsigned kLoneMaxIdle = 4096;
+// each idle workgroup of those layers, against 0.3 to 0.8 us for the search here: with more
+// than kLoneMaxIdle of them, in the column and row launch together, the search is the cheaper.
+// Us a z-step, layers / search: FP32, a 2^18 and 40 2^10 instances 40.6 / 23.0, a 2^18 and
+// eight 2^12 (9424 idle) 24.9 / 22.4, a 2^17 and eight 2^12 (5280) 15.8 / 16.2; FP64 the same
+// two handles (6816, 5280) 31.3 / 32.2 and 19.6 / 20.4.)
+constexpr unsigned kLoneMaxIdle = 7168;
 struct LoneTiles {
     static_assert(kLoneMax % 8 == 0, "searched eight at a time");
     unsigned first[kLoneMax];
