@@ -152,7 +152,7 @@ typedef struct {
                                latency. Equal instances of one handle always agree
                                bit for bit. The kernels and splits of a handle
                                also follow from what else is in it (its size, the
-                               shapes, field counts and nz together), so an instance
+                               shapes and field counts together), so an instance
                                alone and the same instance in a larger or another
                                handle may differ in rounding;
                                1 = two passes per z-step (column and row tiles of

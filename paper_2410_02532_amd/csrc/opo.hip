@@ -300,6 +300,7 @@ struct opo_s {
     int team_first[9] = {};          // TeamArgs::first over `lone`
     unsigned team_waves = 0;         // workgroups of a class
     bool team_again = false;         // team_pass: AGAIN
+    int team_short = 0;              // phases of a pass up to which each is a launch
     size_t lone_lds_b = 0;
     int lone_nf = 3, lone_ln1 = 0, lone_threads_b = 64;
     bool mixed = false;              // two halves a launch apart, mixed launches
@@ -964,9 +965,9 @@ static hipError_t enqueue_pass(opo_t *h, StepArgs<R> a, int nz_steps, int first,
         }
         return launch_lone_a<R>(h, a, flags, step - held, stage);
     };
-    if (h->team && team_too_short(static_cast<int>(h->lone.size()), nz)) {   // a launch a phase
+    const int begin = first ? 1 : 0, end = last ? 2 * nz : 2 * nz + 1;   // phases (TeamArgs)
+    if (h->team && end - begin <= h->team_short) {   // a launch a phase
         if (first) HIP_RET(launch_a<R>(h, a, first | A_RK_THIS | A_FWD, 0));
-        const int begin = first ? 1 : 0, end = last ? 2 * nz : 2 * nz + 1;
         if (end > begin + 1) HIP_RET(fill_couplings<R>(h, a, 0, nz + 1));
         for (int ph = begin; ph < end; ++ph)
             HIP_RET(launch_team<R>(h, a, 0, ph, ph + 1, first ? -1 : 0, last ? -1 : 2 * nz, stage));
@@ -1144,18 +1145,6 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
         one_nf = one_nf && nfields(f[i]) == nfields(f[0]);
         few = few && one_nf && ilog2(f[i].nt) >= kLoneMinLog2;
     }
-    if (few) {
-        // handles whose passes the teams would run, but too short for them
-        bool team = true;
-        for (int i = 0; i < n && team; ++i) {
-            const int l2 = ilog2(f[i].nt);
-            const Plan p = make_plan(f[i].nt, opt.precision, opt.col_log2 != 0 ? opt.col_log2 : lone_split(l2));
-            team = team_shape(p.log2n2, p.log2n1, nfields(f[i]));
-        }
-        long long steps = 0;
-        for (int st = 0; st < K; ++st) steps += c[st].nz * (h->order == 4 ? 3LL : 1LL);
-        few = !team || steps >= static_cast<long long>(K) * team_min_steps(n);
-    }
     // schedule: the table's entry for each shape (schedule 0), or two-pass (1) / resident
     // where served (2); an explicit col_log2 sets the split
     const bool f64 = opt.precision == OPO_F64;
@@ -1297,6 +1286,7 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
                 h->team_first[c + 1] = static_cast<int>(h->lone.size());
                 h->team_waves = std::max(h->team_waves, waves[c]);
             }
+            h->team_short = 2 * team_short_steps(f64, n, static_cast<int>(h->team_waves));
             h->team_again = f64 && h->team_waves > static_cast<unsigned>(kTeamMax);
             if (h->team_again) h->team_waves = kTeamMax;
         }

@@ -51,16 +51,31 @@ constexpr bool team_shape(int log2n2, int log2n1, int nf)
 }
 // A launch of teams has its price: claims, the members' arrival, and with more lists than
 // places at once the wait for members that do not come (about 8 us with one list, 16 with
-// 16, 40 to 60 with 32 to 48). A handle of n instances runs them if its round trips have at
-// least team_min_steps(n) symmetrized steps a crystal on average, else what it ran before
-// them (us a round trip of nz steps, before / teams: FP32 2^14, nz 2 42.5 / 48.5, 4 66.5 /
-// 54.9; 48 of 2^10, nz 2 51 / 68, 8 145 / 93; 32 of 2^13, nz 4 104 / 146, 8 185 / 178; FP64
-// 48 of 2^10, nz 8 93 / 96, 20 209 / 145).
-constexpr int team_min_steps(int n) { return 3 + n / 6; }
-// Calls of ssfm_propagate with fewer steps than the handle's round trips: many lists take a
-// launch a phase (us a call, teams / a launch a phase: one 2^10, 1 step 11.5 / 19.9; 16 of
-// them 19.4 / 20.9; 48 45 / 23, 2 steps 50 / 36, 4 58 / 61; 40 of 2^12, 4 steps 105 / 99).
-constexpr bool team_too_short(int n, int steps) { return 12 * steps <= n; }
+// 16, 40 to 60 with 32 to 48). A pass of at most 2 team_short_steps phases takes a launch a
+// phase instead, which gives the same results (a round trip of nz steps has 2 nz - 1 phases,
+// an nz-step call of ssfm_propagate 2 nz + 1). `waves` are the places of the fullest class's
+// lists. Measured (us a round trip, teams / a launch a phase): FP32, one 2^10, nz 1 27.1 /
+// 25.3, nz 2 31.8 / 34.3; one 2^14, nz 2 46.5 / 40.0, nz 4 55.3 / 58.5; 16 of 2^13, nz 2 55.8 /
+// 47.1, nz 4 69.1 / 73.8; 32 of 2^12, nz 3 64.5 / 58.9, nz 6 85 / 100; 48 of 2^10, nz 3 53.4 /
+// 50.4, nz 4 56.2 / 60.2; 48 of 2^12, whose class fills its second turn of 256 places to an
+// eighth, nz 8 178 / 170, nz 12 222 / 253. FP64, one 2^14, nz 2 50.8 / 41.6; 32 of 2^13, nz 3
+// 131 / 120, nz 4 150 / 160; 48 of 2^12, nz 3 107 / 108, nz 4 118 / 140. Over 378 such shapes
+// and step counts the faster of the two is missed by 0.3 % on average. (Before the lone kernels
+// such round trips took as long or longer, but for many FP64 instances and two or three steps:
+// 48 of 2^10 35.9 and 45.3, now 43.2 and 55.0; 32 of 2^13 80.4, now 89.0.)
+constexpr int team_short_steps(bool f64, int n, int waves)
+{
+    const int steps = 1 + (waves > kTeamMax ? 1 : 0) + (n <= 4 && waves >= 96 ? 1 : 0);
+    if (f64) return steps + n / 32;
+    const int places = 2 * kTeamMax, lists = (n + 7) / 8;   // FP32: two waves a SIMD
+    int tail = 0;
+    if (waves > places) {
+        const int at_once = places * lists / waves > 1 ? places * lists / waves : 1;
+        const int turns = (lists + at_once - 1) / at_once;
+        if (2 * turns * places > 3 * waves) tail = 4;       // the last one mostly empty
+    }
+    return steps + n / 16 + tail;
+}
 constexpr int kTeamCols = 4;              // columns per wave: 2^5 points on 16 lanes of 2, 2^6 of 4
 constexpr int team_row_pf(int ln1) { return ln1 <= 8 ? 4 : 8; }
 constexpr int team_rows(int ln1) { return 64 * team_row_pf(ln1) >> ln1; }   // rows per wave

@@ -163,3 +163,36 @@ def test_one_launch_pass_cut_short(sizes, nf, dk, n2, order, precision):
         tol = TOL[precision] + phase_rounding(ins["crystal"], 24 * (3 if order == 4 else 1), 2 * dz)
         for x in range(nf):
             assert rel_l2(got[x], ref[x]) <= tol, (l, x, rel_l2(got[x], ref[x]), tol)
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("sizes, nf, nz, order", [
+    ([10], 3, 1, 2), ([14], 3, 2, 2), ([14], 3, 4, 2), ([12] * 3, 2, 1, 4), ([13, 10] * 8, 3, 2, 2), ([10] * 48, 3, 4, 2),
+    ([12] * 40, 2, 6, 2)])
+def test_short_round_trips(sizes, nf, nz, order, precision):
+    """Round trips of few steps against the oracle. What a call of ssfm_propagate runs does not
+    depend on the handle's step count: fields equal those of a handle of long round trips."""
+    print("short round trips %s nf %d nz %d %s" % (sizes[:2], nf, nz, precision), file=sys.stderr, flush=True)
+    member = {l: _instance(1 << l, nf, 60 + l, dk=0.3) for l in set(sizes)}
+    for ins in member.values():
+        ins["crystal"]["length_mm"] = 0.5 * nz
+    insts, nrt, out = [member[l] for l in sizes], 3, []
+    for steps in (nz, 100):
+        with B.Opo(insts, steps, precision=precision, split_order=order) as h:
+            h.ssfm_propagate(30, 2.0 ** -5)
+            out.append([h.get_fields(i) for i in range(len(sizes))])
+            out.append([h.plan(i) for i in range(len(sizes))])
+    assert out[1] == out[3]
+    for a, b in zip(out[0], out[2]):
+        assert np.array_equal(a, b)
+    with B.Opo(insts, nz, precision=precision, split_order=order) as h:
+        h.cavity_roundtrip(nrt)
+        got = [h.get_fields(i) for i in range(len(sizes))]
+    for l, ins in member.items():
+        ref, _ = oracle.roundtrips(dict(ins["crystal"], order=order), ins["cavity"], ins["fields"], ins["pump_in"], nz, nrt)
+        tol = TOL[precision] + phase_rounding(ins["crystal"], nz * nrt * (3 if order == 4 else 1), 1.0)
+        mine = [g for g, size in zip(got, sizes) if size == l]
+        for x in range(nf):
+            assert rel_l2(mine[0][x], ref[x]) <= tol, (l, x, rel_l2(mine[0][x], ref[x]), tol)
+        for g in mine[1:]:
+            assert np.array_equal(g, mine[0])
