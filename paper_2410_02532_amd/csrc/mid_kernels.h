@@ -10,8 +10,9 @@
 // fields instead of three).
 //
 // Measured (MI355X, ms per round trip of the 256-instance sweeps of 2^12..2^16, with the
-// launch order and the row shapes that followed): FP32 18.1 -> 16.5, two waves 14.0 ->
-// 11.8, FP64 37.1 -> 29.4. The FP32 launch takes 3.70e7 wave instructions (742
+// launch order and the row shapes that followed, both timed in turn on one card): FP32
+// 18.6 -> 17.2, two waves 13.9 -> 12.1, FP64 37.3 -> 29.9 (another card 17.0, 11.8, 29.7
+// after; cards differ by some percent in FP32). The FP32 launch takes 3.70e7 wave instructions (742
 // lane-instructions) and issues VALU 75 % of its cycles at four workgroups per CU (five
 // changed nothing); about 9 us of it are its ramp and tail. The FP64 launch issues VALU
 // 37 % of its cycles and moves its fields at 4.3 TB/s (a large copy: 4.85): memory bound.

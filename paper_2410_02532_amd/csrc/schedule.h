@@ -3,8 +3,8 @@
 // whether fixed-step passes run resident (one workgroup holds the instance).
 // The entries are chosen by timing the candidate schedules on the device
 // (paper_2410_02532_amd/tune.py, which writes schedule_table.inc); the lookup
-// itself is a plain table, so one shape always gets one schedule and results
-// do not depend on timings taken at run time. The batch entries apply to the
+// itself is a plain table, so results do not depend on timings taken at run
+// time. The batch entries apply to the
 // instances of a handle whose fields fill the chip (at least kBatchPoints field
 // samples in all, e.g. 2^9 instances of 2^10 points with three waves), the
 // others ("alone", one instance or a few) to the rest: a handle that small is
