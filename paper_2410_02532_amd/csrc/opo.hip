@@ -1459,11 +1459,14 @@ static int init_impl(opo_t **out, int n, const opo_fields_t *f, const opo_crysta
         h->mid = (f64 ? mid_fn<double>(h->mid_cr, h->mid_rr, h->mid_nf)
                       : mid_fn<float>(h->mid_cr, h->mid_rr, h->mid_nf)) != nullptr;
         h->mid = h->mid && (f64 || state <= kLastCache || (long_rows && h->mid_cr == 0));
+        const InstDesc &d0 = h->inst[order[0]];
+        bool one_shape = true;
         for (int i : order) {
             const InstDesc &d = h->inst[i];
-            h->mid = h->mid && d.log2n2 >= kMidMinLog2N2 && d.log2n1 >= kMidMinLog2N1 &&
-                     (f64 || mid_faster_f32(d.nf, d.log2n2, d.log2n1));
+            h->mid = h->mid && d.log2n2 >= kMidMinLog2N2 && d.log2n1 >= kMidMinLog2N1;
+            one_shape = one_shape && d.log2n2 == d0.log2n2 && d.log2n1 == d0.log2n1;
         }
+        if (!f64 && one_shape) h->mid = h->mid && mid_faster_f32(d0.nf, d0.log2n2, d0.log2n1);
         // Three waves, FP32, long columns: a CU holds two workgroups of mid_pass (180 registers)
         // and three of mixed_pass (129). Launches that fit the chip at once only at three stay
         // with mixed_pass (two instances of 2^19, 640 workgroups: 64 us a z-step, 69 with

@@ -75,7 +75,9 @@ inline int batch_split(int nf, int log2nt, int table)
 // rows: three waves gain but for 2^9 points (columns of 2^4, rows of 2^5: 139 / 159, 259 /
 // 306; columns and rows of 2^5 287 / 257), two waves only at 2^11 and 2^12 points (columns
 // of 2^5, rows of 2^6 221 / 181; but 2^4 x 2^5 121 / 141, 2^5 x 2^5 812 / 858, 2^5 x 2^8 182
-// / 193, 2^4 x 2^9 97 / 113, 2^5 x 2^9 102 / 113).
+// / 193, 2^4 x 2^9 97 / 113, 2^5 x 2^9 102 / 113). For batches of one shape: in a mix of
+// shapes mixed_pass is the slower again (2^9 and 2^10 points, a quarter and three quarters of
+// 2^9: three waves 123 / 96 and 162 / 117, two 96 / 89 and 130 / 111, half of each 97 / 100).
 inline bool mid_faster_f32(int nf, int log2n2, int log2n1)
 {
     if (log2n2 >= 6 || log2n1 >= 10) return true;

@@ -227,3 +227,23 @@ def test_crystals_with_their_own_tables(precision, sizes, col):
         tol = TOL[precision] + sum(phase_rounding(c, n * nrt, c["length_mm"] / n) for c, n in zip(ins["crystals"], nzs))
         for x in range(3):
             assert rel_l2(got[i][x], ref[x]) <= tol, (i, x, rel_l2(got[i][x], ref[x]), tol)
+
+
+@pytest.mark.parametrize("sizes, nf, col, order", [
+    ([9] * 128 + [10] * 320, 3, 0, 4), ([9] * 1024 + [10, 10], 2, 0, 4), ([9, 10, 11] * 100, 3, 6, 2)])
+def test_fp32_batches_of_short_columns_and_several_shapes(sizes, nf, col, order):
+    """Short columns of more than one shape: against the oracle, equal members bit for bit."""
+    print("batch short mix nf %d %s x%d order %d" % (nf, sorted(set(sizes)), len(sizes), order), file=sys.stderr, flush=True)
+    member = {l: _instance(1 << l, nf, 20 + l, dk=0.4) for l in set(sizes)}
+    nz, nrt = 5, 2
+    with B.Opo([member[l] for l in sizes], nz, precision="f32", split_order=order, col_log2=col) as h:
+        h.cavity_roundtrip(nrt)
+        got = [h.get_fields(i) for i in range(len(sizes))]
+    for l, ins in member.items():
+        ref, _ = oracle.roundtrips(dict(ins["crystal"], order=order), ins["cavity"], ins["fields"], ins["pump_in"], nz, nrt)
+        tol = TOL["f32"] + phase_rounding(ins["crystal"], nz * nrt * (3 if order == 4 else 1), 5.0 / nz)
+        mine = [g for g, size in zip(got, sizes) if size == l]
+        for x in range(nf):
+            assert rel_l2(mine[0][x], ref[x]) <= tol, (l, x, rel_l2(mine[0][x], ref[x]), tol)
+        for g in mine[1:]:
+            assert np.array_equal(g, mine[0])
